@@ -99,6 +99,18 @@ __device__ __forceinline__ void status_or(uint32_t *p, uint32_t bits)
     __hip_atomic_fetch_or(p, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// ------------------------------------------------------------------ constants
+
+// Read-only model constants in device memory, read through the constant
+// address space: uniform loads of these become scalar loads into SGPRs,
+// which the FP64 multiply-adds take as operands (no LDS or VGPR traffic).
+typedef const __attribute__((address_space(4))) double cdouble;
+
+// Hides the value of a constant pointer from the optimiser at the top of a
+// step loop, so that the loads through it are issued inside every
+// iteration instead of being hoisted (and held in registers) across it.
+#define PSSGP_LAUNDER(ptr) asm volatile("" : "+s"(ptr))
+
 // ------------------------------------------------------------------ FP64 discretisation
 
 // exp(s G1) of one companion-structured block by scaling and squaring a
@@ -161,11 +173,113 @@ __device__ __forceinline__ void expm_companion(const DevBlock &bk, double s, dou
     }
 }
 
+// exp(s G1) of a companion block from the matrices C_k = G1^k / k! of its
+// Taylor series, k = 1..POLY_DEG, computed once per call (poly_consts_kernel)
+// and read as scalar operands. What bounds the FP64 scans is their
+// instruction count: this is one multiply-add per entry and term, where the
+// series evaluated by products with the sparse G1 (expm_companion) takes
+// about three, and dc^2 independent chains hide the latency. (Summed upwards
+// with the power of s in a register: Horner's rule has the constant as the
+// addend, which costs two moves per multiply-add.) s is halved until the
+// remainder at degree POLY_DEG is below 2e-17 (bk.sdeg[2], from the norm of
+// the actual power G1^(POLY_DEG + 1): at order 6 s <= 0.2, while s ||G1||_1 <=
+// 1/2 as in expm_companion means s <= 0.018) and the result squared as often;
+// a wave whose steps are all short leaves out the highest terms. At d = 6,
+// 2 000 steps: filter finish 122 -> 82 us, adjoint passes 110 -> 59 and
+// 145 -> 109 us.
+constexpr int POLY_DEG = 16;
+template <int dc>
+__device__ __forceinline__ void expm_poly(const DevBlock &bk, cdouble *c, double s, double (&X)[dc][dc])
+{
+    int e = 0;
+    (void)frexp(s * bk.rsmax, &e);  // s < 2^e sdeg[2]
+    const int j = (s > bk.sdeg[2]) ? (e > 60 ? 60 : e) : 0;
+    const double ss = ldexp(s, -j);
+#pragma unroll
+    for (int i = 0; i < dc; i++)
+#pragma unroll
+        for (int q = 0; q < dc; q++) X[i][q] = 0.0;
+    double pw = 1.0;
+    auto terms = [&](auto lo, auto hi) {
+#pragma unroll
+        for (int k = decltype(lo)::value; k <= decltype(hi)::value; k++) {
+            pw *= ss;
+#pragma unroll
+            for (int i = 0; i < dc; i++)
+#pragma unroll
+                for (int q = 0; q < dc; q++) X[i][q] = fma(c[(k - 1) * dc * dc + i * dc + q], pw, X[i][q]);
+        }
+    };
+    terms(std::integral_constant<int, 1>(), std::integral_constant<int, 10>());
+    if (!__all(ss <= bk.sdeg[0])) {
+        terms(std::integral_constant<int, 11>(), std::integral_constant<int, 13>());
+        if (!__all(ss <= bk.sdeg[1])) terms(std::integral_constant<int, 14>(), std::integral_constant<int, 16>());
+    }
+#pragma unroll
+    for (int i = 0; i < dc; i++) X[i][i] += 1.0;
+    for (int r = 0; r < j; r++) {
+        double Y[dc][dc];
+#pragma unroll
+        for (int i = 0; i < dc; i++)
+#pragma unroll
+            for (int q = 0; q < dc; q++) {
+                double acc = 0.0;
+#pragma unroll
+                for (int m = 0; m < dc; m++) acc = fma(X[i][m], X[m][q], acc);
+                Y[i][q] = acc;
+            }
+#pragma unroll
+        for (int i = 0; i < dc; i++)
+#pragma unroll
+            for (int q = 0; q < dc; q++) X[i][q] = Y[i][q];
+    }
+}
+
+// Constants of the FP64 transition: the blocks' series, then Pinf.
+template <class LY>
+struct PolyLayout {
+    __host__ __device__ static constexpr int off(int b) { return b == 0 ? 0 : POLY_DEG * LY::bdim(0) * LY::bdim(0); }
+    static constexpr int PINF = POLY_DEG * (LY::bdim(0) * LY::bdim(0) + LY::bdim(1) * LY::bdim(1));
+    static constexpr int TOTAL = PINF + LY::D * LY::D;
+};
+
+// C_k = G1^k / k! of the RBF blocks of one model, and Pinf (one workgroup).
+template <class LY>
+__global__ __launch_bounds__(64) void poly_consts_kernel(DevModel mdl, double *out)
+{
+    static_assert(PolyLayout<LY>::TOTAL <= PSSGP_CONST_DOUBLES, "constants exceed their workspace room");
+    static_assert(LY::bdim(0) <= 8 && LY::bdim(1) <= 8, "one thread per entry");
+    __shared__ double X[64];
+    for (int e = (int)threadIdx.x; e < LY::D * LY::D; e += (int)blockDim.x) out[PolyLayout<LY>::PINF + e] = mdl.Pinf[e];
+    for (int b = 0; b < LY::NB; b++) {
+        const int dc = LY::bdim(b), e = (int)threadIdx.x;
+        const DevBlock &bk = mdl.blk[b];
+        if (bk.kind != BLK_RBF) continue;
+        if (e < dc * dc) X[e] = (e / dc == e % dc) ? 1.0 : 0.0;
+        __syncthreads();
+        for (int k = 1; k <= POLY_DEG; k++) {
+            double acc = 0.0;
+            if (e < dc * dc) {
+                // (X G1)[i][j]: G1 is the superdiagonal and the last row
+                const int i = e / dc, j = e % dc;
+                acc = X[i * dc + dc - 1] * bk.glast[j];
+                if (j > 0) acc = fma(X[i * dc + j - 1], bk.gsup[j - 1], acc);
+                acc /= k;
+                out[PolyLayout<LY>::off(b) + (k - 1) * dc * dc + e] = acc;
+            }
+            __syncthreads();
+            if (e < dc * dc) X[e] = acc;
+            __syncthreads();
+        }
+    }
+}
+
 // Transition F = exp(dt G) and process noise Q = Pinf - F Pinf F^T of one
 // step (supplement eq. ss-gp-formation; stationarity gives the Q form).
 // first: step 0, F = 0 and Q = Pinf (first filter element, section 3).
-// ACC selects the Taylor evaluation for RBF blocks (full FP64 accuracy)
-// instead of the spectral expansion (faster, about 1e-12 absolute).
+// RBF blocks take the Taylor series of the exponential (the spectral
+// expansion is only accurate to about 1e-12): POLY from the matrices at pc,
+// otherwise (no constants at hand, pc unused) by products with the generator.
 // Per-step scales: inverse length-scale of each block and a multiplier of
 // the stationary covariance (1 for a single series, whose constants already
 // hold the variances; the series variance for the batched form, whose
@@ -294,17 +408,20 @@ __device__ __forceinline__ void block_phi(const DevModel &mdl, const StepScale &
 }
 
 // F block of one component (no special cases)
-template <class LY, int b, bool ACC>
-__device__ __forceinline__ void trans_block(const DevModel &mdl, const StepScale &sc, double dt,
+template <class LY, int b, bool POLY>
+__device__ __forceinline__ void trans_block(const DevModel &mdl, cdouble *pc, const StepScale &sc, double dt,
                                             double (&F)[LY::D][LY::D])
 {
     constexpr int dc = LY::bdim(b);
     constexpr int o = LY::boff(b);
     const DevBlock &bk = mdl.blk[b];
     const double s = dt * sc.inv_ell[b];
-    if (ACC && bk.kind == BLK_RBF) {
+    if (dc >= 4 || bk.kind == BLK_RBF) {  // Matern blocks have at most 3 states
         double X[dc][dc];
-        expm_companion<dc>(bk, s, X);
+        if constexpr (POLY)
+            expm_poly<dc>(bk, pc + PolyLayout<LY>::off(b), s, X);
+        else
+            expm_companion<dc>(bk, s, X);
 #pragma unroll
         for (int i = 0; i < dc; i++)
 #pragma unroll
@@ -325,14 +442,21 @@ __device__ __forceinline__ void trans_block(const DevModel &mdl, const StepScale
     }
 }
 
-template <class LY, int b, bool ACC>
-__device__ __forceinline__ void disc_block(const DevModel &mdl, const StepScale &sc, double dt,
+template <class LY, int b, bool POLY>
+__device__ __forceinline__ void disc_block(const DevModel &mdl, cdouble *pc, const StepScale &sc, double dt,
                                            double (&F)[LY::D][LY::D], double (&Q)[LY::D][LY::D])
 {
     constexpr int dc = LY::bdim(b);
     constexpr int o = LY::boff(b);
-    trans_block<LY, b, ACC>(mdl, sc, dt, F);
-    // Q block = Pinf_b - F_b Pinf_b F_b^T
+    trans_block<LY, b, POLY>(mdl, pc, sc, dt, F);
+    // Q block = Pinf_b - F_b Pinf_b F_b^T, Pinf as scalar operands where the
+    // constants are at hand
+    auto pinf = [&](int i, int j) -> double {
+        if constexpr (POLY && dc >= 4)
+            return pc[PolyLayout<LY>::PINF + (o + i) * LY::D + o + j];
+        else
+            return mdl.Pinf[(o + i) * LY::D + o + j];
+    };
     double FP[dc][dc];
 #pragma unroll
     for (int i = 0; i < dc; i++)
@@ -340,14 +464,14 @@ __device__ __forceinline__ void disc_block(const DevModel &mdl, const StepScale 
         for (int j = 0; j < dc; j++) {
             double acc = 0.0;
 #pragma unroll
-            for (int k = 0; k < dc; k++) acc = fma(F[o + i][o + k], mdl.Pinf[(o + k) * LY::D + o + j], acc);
+            for (int k = 0; k < dc; k++) acc = fma(F[o + i][o + k], pinf(k, j), acc);
             FP[i][j] = acc;
         }
 #pragma unroll
     for (int i = 0; i < dc; i++)
 #pragma unroll
         for (int j = i; j < dc; j++) {
-            double acc = mdl.Pinf[(o + i) * LY::D + o + j];
+            double acc = pinf(i, j);
 #pragma unroll
             for (int k = 0; k < dc; k++) acc = fma(-FP[i][k], F[o + j][o + k], acc);
             Q[o + i][o + j] = acc * sc.var_mult;
@@ -355,8 +479,8 @@ __device__ __forceinline__ void disc_block(const DevModel &mdl, const StepScale 
         }
 }
 
-template <class LY, bool ACC>
-__device__ __forceinline__ void discretize(const DevModel &mdl, const StepScale &sc, double dt, bool first,
+template <class LY, bool POLY>
+__device__ __forceinline__ void discretize(const DevModel &mdl, cdouble *pc, const StepScale &sc, double dt, bool first,
                                            double (&F)[LY::D][LY::D], double (&Q)[LY::D][LY::D])
 {
     constexpr int D = LY::D;
@@ -364,8 +488,8 @@ __device__ __forceinline__ void discretize(const DevModel &mdl, const StepScale 
     for (int i = 0; i < D; i++)
 #pragma unroll
         for (int j = 0; j < D; j++) { F[i][j] = 0.0; Q[i][j] = 0.0; }
-    disc_block<LY, 0, ACC>(mdl, sc, dt, F, Q);
-    if constexpr (LY::NB > 1) disc_block<LY, 1, ACC>(mdl, sc, dt, F, Q);
+    disc_block<LY, 0, POLY>(mdl, pc, sc, dt, F, Q);
+    if constexpr (LY::NB > 1) disc_block<LY, 1, POLY>(mdl, pc, sc, dt, F, Q);
     // exact special cases: a zero step is the identity map, step 0 is the prior
     const bool zero = (dt == 0.0);
 #pragma unroll
@@ -379,8 +503,8 @@ __device__ __forceinline__ void discretize(const DevModel &mdl, const StepScale 
 }
 
 // F alone, with the special cases of discretize
-template <class LY, bool ACC>
-__device__ __forceinline__ void transition(const DevModel &mdl, const StepScale &sc, double dt, bool first,
+template <class LY, bool POLY>
+__device__ __forceinline__ void transition(const DevModel &mdl, cdouble *pc, const StepScale &sc, double dt, bool first,
                                            double (&F)[LY::D][LY::D])
 {
     constexpr int D = LY::D;
@@ -388,8 +512,8 @@ __device__ __forceinline__ void transition(const DevModel &mdl, const StepScale 
     for (int i = 0; i < D; i++)
 #pragma unroll
         for (int j = 0; j < D; j++) F[i][j] = 0.0;
-    trans_block<LY, 0, ACC>(mdl, sc, dt, F);
-    if constexpr (LY::NB > 1) trans_block<LY, 1, ACC>(mdl, sc, dt, F);
+    trans_block<LY, 0, POLY>(mdl, pc, sc, dt, F);
+    if constexpr (LY::NB > 1) trans_block<LY, 1, POLY>(mdl, pc, sc, dt, F);
     const bool zero = (dt == 0.0);
 #pragma unroll
     for (int i = 0; i < D; i++)
@@ -439,16 +563,6 @@ __device__ __forceinline__ void unpack_upper(int e, int n, int &i, int &j)
     j = i + e;
 }
 
-// Read-only model constants in device memory, read through the constant
-// address space: uniform loads of these become scalar loads into SGPRs,
-// which the FP64 multiply-adds take as operands (no LDS or VGPR traffic).
-typedef const __attribute__((address_space(4))) double cdouble;
-
-// Hides the value of a constant pointer from the optimiser at the top of a
-// step loop, so that the loads through it are issued inside every
-// iteration instead of being hoisted (and held in registers) across it.
-#define PSSGP_LAUNDER(ptr) asm volatile("" : "+s"(ptr))
-
 // Layout of the constants of the fast transition: per block the first rows
 // of the expansion matrices (R0[r][j] = M_r[0][j], dc^2), 1 / g_i, g_i,
 // l_j (dc each; the last superdiagonal slots unused) and w; then Pinf (D^2,
@@ -497,6 +611,19 @@ template <class LY>
 __global__ __launch_bounds__(256) void consts_kernel(DevModel mdl, double *out)
 {
     consts_build<LY>(mdl, out);
+}
+
+// Fills the constants of one model's transition for a scan of type T.
+template <class LY, typename T>
+void launch_consts(const DevModel &mdl, double *cst, hipStream_t s)
+{
+    if (sizeof(T) == 4) {
+        hipLaunchKernelGGL((consts_kernel<LY>), dim3(1), dim3(256), 0, s, mdl, cst);
+    } else {
+        bool rbf = false;
+        for (int b = 0; b < LY::NB; b++) rbf = rbf || mdl.blk[b].kind == BLK_RBF;
+        if (rbf) hipLaunchKernelGGL((poly_consts_kernel<LY>), dim3(1), dim3(64), 0, s, mdl, cst);
+    }
 }
 
 // Dl = F - I of one block in FP64 from its phi (first row by the expansion,

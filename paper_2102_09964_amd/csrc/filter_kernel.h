@@ -48,7 +48,7 @@ struct FilterParams {
     double *loglik;
     T *rec;             // F_RECS: per-step records (RecLayout, tile layout)
     double *ll_terms;  // batched: per-segment log-likelihood partials, at each segment's first step
-    const double *cst;  // model constants of the FP32 transition (ConstLayout)
+    const double *cst;  // model constants of the transition
     WsCtl *ctl;
     T *aggp;
     T *inclp;
@@ -66,8 +66,8 @@ struct TileRange {
 };
 
 // Transition of a step, Dl = F - I (F = 0 at a series start, so Dl = -I
-// there) and Q, rounded to U: for FP32 scans (T) from the expansion of F
-// with the constants at cst, for FP64 scans by the FP64 discretisation.
+// there) and Q, rounded to U, with the constants at cst: for FP32 scans (T)
+// from the expansion of F, for FP64 scans by the FP64 discretisation.
 template <class LY, typename U, typename T = U>
 __device__ __forceinline__ void step_transition(const DevModel &mdl, cdouble *cst, const StepScale &sc,
                                                 double dt, bool first, U (&Dl)[LY::D][LY::D],
@@ -76,7 +76,7 @@ __device__ __forceinline__ void step_transition(const DevModel &mdl, cdouble *cs
     constexpr int D = LY::D;
     if constexpr (sizeof(T) == 8) {
         double F64[D][D], Q64[D][D];
-        discretize<LY, true>(mdl, sc, dt, first, F64, Q64);
+        discretize<LY, true>(mdl, cst, sc, dt, first, F64, Q64);
 #pragma unroll
         for (int i = 0; i < D; i++)
 #pragma unroll
@@ -310,11 +310,12 @@ __device__ __forceinline__ void filter_tile_fold(const FilterParams<T> &p, const
         in.yc = yn;
         in.oc = on;
     }
-    if constexpr (sizeof(T) == 8 && D >= 7) {
-        // FP64 at d >= 7: the operator reads the predecessor's entries by
+    if constexpr (sizeof(T) == 8 && D >= 6) {
+        // FP64 at d >= 6: the operator reads the predecessor's entries by
         // shuffles where it uses them (agg_combine_lane); a shuffled copy of
-        // the whole aggregate spilled 3.3 KB per lane. (In FP32 the d = 8
-        // scan does not spill that way; there the first tile's FP64
+        // the whole aggregate spilled 3.3 KB per lane at d = 8 and 0.6 KB at
+        // d = 6 (there 272 -> 260 us of the fold at 300 000 steps). (In FP32
+        // the d = 8 scan does not spill that way; there the first tile's FP64
         // combinations of a series-start prefix made this form slower.)
         for (int o = 1; o < PSSGP_WAVE; o <<= 1) {
             const bool other_from_start = __shfl_up((int)from_start, o, PSSGP_WAVE) != 0;
@@ -634,7 +635,7 @@ __global__ __launch_bounds__(256) void discretize_kernel(DevModel mdl, const dou
     double F[D][D], Q[D][D];
     const double dt = (k > 0) ? t[k] - t[k - 1] : 0.0;
     if (!(dt >= 0.0)) status_or(&ctl->status, (dt < 0.0) ? PSSGP_STATUS_UNSORTED : PSSGP_STATUS_NONFINITE);
-    discretize<LY, true>(mdl, model_scale(mdl), dt, k == 0, F, Q);
+    discretize<LY, false>(mdl, (cdouble *)nullptr, model_scale(mdl), dt, k == 0, F, Q);
 #pragma unroll
     for (int i = 0; i < D; i++)
 #pragma unroll
@@ -677,7 +678,7 @@ int launch_filter_t(const DevModel &mdl, const FilterLaunch &a, hipStream_t s)
     FilterParams<T> p = filter_params<LY, T>(a);
     const dim3 grid(a.ntiles), block(PSSGP_WAVE);
     pass_event(a.ev, 0, s);
-    if constexpr (sizeof(T) == 4) hipLaunchKernelGGL((consts_kernel<LY>), dim3(1), dim3(256), 0, s, mdl, a.ws.cst);
+    launch_consts<LY, T>(mdl, a.ws.cst, s);
     hipLaunchKernelGGL((filter_fold_kernel<LY, T, T>), grid, block, 0, s, p, mdl);
     int rc = (int)hipGetLastError();
     if (rc) return rc;

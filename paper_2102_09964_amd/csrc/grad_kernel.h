@@ -135,7 +135,7 @@ struct GradParams {
     int chunk;
     int ntiles;
     const T *rec;
-    const double *cst;  // FP32 scans: model constants of the transition (ConstLayout)
+    const double *cst;  // model constants of the transition
     int noise_fixed;    // per-step noise variances: the model's noise variance enters nowhere
     double *grad;
     WsCtl *ctl;
@@ -176,13 +176,12 @@ __global__ __launch_bounds__(PSSGP_WAVE) void grad_fold_kernel(GradParams<T> p, 
             {
                 double F64[D][D];
                 const double dt = (k > 0) ? p.t[k] - p.t[k - 1] : 0.0;
-                if constexpr (sizeof(T) == 4) {
-                    cdouble *c = (cdouble *)p.cst;
-                    PSSGP_LAUNDER(c);
+                cdouble *c = (cdouble *)p.cst;
+                PSSGP_LAUNDER(c);
+                if constexpr (sizeof(T) == 4)
                     transition_fast<LY>(mdl, c, model_scale(mdl), dt, k == 0, F64);
-                } else {
-                    transition<LY, true>(mdl, model_scale(mdl), dt, k == 0, F64);
-                }
+                else
+                    transition<LY, true>(mdl, c, model_scale(mdl), dt, k == 0, F64);
 #pragma unroll
                 for (int i = 0; i < D; i++)
 #pragma unroll
@@ -284,15 +283,15 @@ __global__ __launch_bounds__(PSSGP_WAVE) void grad_finish_kernel(GradParams<T> p
         PSSGP_RELOAD_CONSTANTS();
         const double dt = (k > 0) ? p.t[k] - p.t[k - 1] : 0.0;
         double F64[D][D], Q64[D][D];
+        cdouble *c = (cdouble *)p.cst;
+        PSSGP_LAUNDER(c);
         if constexpr (sizeof(T) == 4) {
-            // the FP32 scans' transition (constants at cst): F = I + (F - I)
-            cdouble *c = (cdouble *)p.cst;
-            PSSGP_LAUNDER(c);
+            // the FP32 scans' transition: F = I + (F - I)
             discretize_fast<LY, double>(mdl, c, model_scale(mdl), dt, k == 0, F64, Q64);
 #pragma unroll
             for (int i = 0; i < D; i++) F64[i][i] += 1.0;
         } else {
-            discretize<LY, true>(mdl, model_scale(mdl), dt, k == 0, F64, Q64);
+            discretize<LY, true>(mdl, c, model_scale(mdl), dt, k == 0, F64, Q64);
         }
         const bool obs = p.mask ? (p.mask[k] != 0) : true;
         const T *rp = p.rec + rec_index<D>(tile, p.chunk, (int)(k - k0), lane);

@@ -415,6 +415,29 @@ int pssgp_build_devmodel(const pssgp_model *spec, DevModel *out, double *tdiag)
             b.gsup[j] = (j + 1 < dc) ? cp.G1[j * dc + j + 1] : 0.0;
         }
         b.gnorm = gn;
+        if (b.kind == BLK_RBF) {
+            // remainder ||G1^(K+1)|| s^(K+1) / (K+1)! <= 2e-17
+            static const int deg[3] = {10, 13, 16};
+            double X[PSSGP_MAXD * PSSGP_MAXD], Y[PSSGP_MAXD * PSSGP_MAXD], fact = 1.0;
+            for (int i = 0; i < dc * dc; i++) X[i] = (i / dc == i % dc) ? 1.0 : 0.0;
+            for (int k = 1, q = 0; k <= deg[2] + 1; k++) {
+                double norm = 0.0;
+                for (int j = 0; j < dc; j++) {
+                    double col = 0.0;
+                    for (int i = 0; i < dc; i++) {
+                        double acc = 0.0;
+                        for (int r = 0; r < dc; r++) acc += X[i * dc + r] * cp.G1[r * dc + j];
+                        Y[i * dc + j] = acc;
+                        col += std::fabs(acc);
+                    }
+                    norm = std::fmax(norm, col);
+                }
+                for (int i = 0; i < dc * dc; i++) X[i] = Y[i];
+                fact *= k;
+                if (k == deg[q] + 1) b.sdeg[q++] = std::pow(2e-17 * fact / norm, 1.0 / k);
+            }
+            b.rsmax = 1.0 / b.sdeg[2];
+        }
         if (tdiag)
             for (int i = 0; i < dc; i++) tdiag[off + i] = cp.D[i] * std::pow(cp.ell, -i);
         off += dc;

@@ -51,6 +51,10 @@ struct DevBlock {
     double gsup[PSSGP_MAXD];    // G1[i][i+1], i < dim-1
     double glast[PSSGP_MAXD];   // G1[dim-1][j]
     double gnorm;               // ||G1||_1
+    // RBF: longest steps (times over the length-scale) at which the Taylor
+    // series of exp(s G1) of degree 10, 13 and 16 is exact to rounding, and
+    // the reciprocal of the last
+    double sdeg[3], rsmax;
 };
 
 struct DevModel {

@@ -27,7 +27,7 @@ __global__ __launch_bounds__(128) void plain_filter_elements(DevModel mdl, const
     if (i < n) {
         double F[D][D], Q[D][D], h[D];
         const double dt = (i > 0) ? t[i] - t[i - 1] : 0.0;
-        discretize<LY, true>(mdl, model_scale(mdl), dt, i == 0, F, Q);
+        discretize<LY, false>(mdl, (cdouble *)nullptr, model_scale(mdl), dt, i == 0, F, Q);
         for (int j = 0; j < D; j++) h[j] = mdl.H[j];
         const bool obs = mask ? (mask[i] != 0) : true;
 #pragma unroll
@@ -94,7 +94,7 @@ __global__ __launch_bounds__(128) void plain_filter_finish(DevModel mdl, const d
     // prediction-error term from the moments before step i
     double F[D][D], Q[D][D];
     const double dt = (i > 0) ? t[i] - t[i - 1] : 0.0;
-    discretize<LY, true>(mdl, model_scale(mdl), dt, i == 0, F, Q);
+    discretize<LY, false>(mdl, (cdouble *)nullptr, model_scale(mdl), dt, i == 0, F, Q);
     double mp[D], FP[D][D], Pp[D][D];
     mat_vec<D, double>(F, ex.b, mp);
     mat_mul<D, double>(F, ex.C, FP);
@@ -141,7 +141,7 @@ __global__ __launch_bounds__(128) void plain_smoother_elements(DevModel mdl, con
         OneSeries sv;
         sv.init(mdl, n);
         uint32_t bad = 0;
-        smoother_element<LY, double, OneSeries>(mdl, (cdouble *)nullptr, sv, t, m + (n - 1 - j), P + (n - 1 - j), (size_t)n,
+        smoother_element<LY, double, OneSeries, false>(mdl, (cdouble *)nullptr, sv, t, m + (n - 1 - j), P + (n - 1 - j), (size_t)n,
                                                  n - 1 - j, e, bad);
     }
     Y[j] = e;

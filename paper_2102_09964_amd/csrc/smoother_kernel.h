@@ -42,7 +42,7 @@ struct SmoothParams {
     T *aggp;
     T *inclp;
     T *lanep;
-    const double *cst;  // model constants of the FP32 transition (ConstLayout)
+    const double *cst;  // model constants of the transition
     const T *slane;     // fused call: lane records written by the filter's finish
 };
 
@@ -271,7 +271,7 @@ int launch_smoother_t(const DevModel &mdl, const SmoothLaunch &a, hipStream_t s)
         // elements from the filter of the same call: no transition needed
         hipLaunchKernelGGL((smoother_fold_kernel<LY, T, true>), grid, block, 0, s, p, mdl);
     } else {
-        if constexpr (sizeof(T) == 4) hipLaunchKernelGGL((consts_kernel<LY>), dim3(1), dim3(256), 0, s, mdl, a.ws.cst);
+        launch_consts<LY, T>(mdl, a.ws.cst, s);
         hipLaunchKernelGGL((smoother_fold_kernel<LY, T, false>), grid, block, 0, s, p, mdl);
     }
     if constexpr (smoother_by_rows<LY::D, T>()) {

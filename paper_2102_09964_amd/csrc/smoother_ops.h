@@ -261,9 +261,9 @@ __device__ __forceinline__ void from_smoother_coords(const T (&ms)[D], const T (
 // transition comes as Dl = F - I. The last step of a series takes the
 // transition F = 0, Q = Pinf, for which the same formulas give exactly its
 // element (0, m, P); every lane runs the same instruction stream. FP32
-// scans use the expansion of the transition (constants at cst), FP64 scans
-// the FP64 discretisation.
-template <class LY, typename T, class SV>
+// scans use the expansion of the transition, FP64 scans the FP64
+// discretisation (constants at cst; POLY as in discretize).
+template <class LY, typename T, class SV, bool POLY = true>
 __device__ __forceinline__ void smoother_element(const DevModel &mdl, cdouble *cst, const SV &sv,
                                                  const double *t, const T *mk, const T *pk, size_t st, int64_t k,
                                                  SAgg<LY::D, T> &e, uint32_t &bad)
@@ -275,7 +275,7 @@ __device__ __forceinline__ void smoother_element(const DevModel &mdl, cdouble *c
     const double dt = t[kn] - t[k];
     double Dl[D][D], Q[D][D];
     if constexpr (sizeof(T) == 8) {
-        discretize<LY, true>(mdl, sv.sc, dt, is_last, Dl, Q);
+        discretize<LY, POLY>(mdl, cst, sv.sc, dt, is_last, Dl, Q);
 #pragma unroll
         for (int i = 0; i < D; i++) Dl[i][i] -= 1.0;
     } else {
