@@ -243,35 +243,40 @@ struct PolyLayout {
     static constexpr int TOTAL = PINF + LY::D * LY::D;
 };
 
-// C_k = G1^k / k! of the RBF blocks of one model, and Pinf (one workgroup).
+// C_k = G1^k / k! of block b, one thread per row: row i of C_k is row i of
+// C_{k-1} times G1 / k, and G1 is the superdiagonal and the last row.
+template <class LY, int b>
+__device__ __forceinline__ void poly_block(const DevModel &mdl, double *out)
+{
+    constexpr int dc = LY::bdim(b);
+    const DevBlock &bk = mdl.blk[b];
+    const int i = (int)threadIdx.x;
+    if (bk.kind != BLK_RBF || i >= dc) return;
+    double x[dc];
+#pragma unroll
+    for (int j = 0; j < dc; j++) x[j] = (j == i) ? 1.0 : 0.0;
+    out += PolyLayout<LY>::off(b) + i * dc;
+#pragma unroll
+    for (int k = 1; k <= POLY_DEG; k++) {
+        const double last = x[dc - 1];
+#pragma unroll
+        for (int j = dc - 1; j >= 0; j--) {
+            double acc = last * bk.glast[j];
+            if (j > 0) acc = fma(x[j - 1], bk.gsup[j - 1], acc);
+            x[j] = acc * (1.0 / k);
+            out[(k - 1) * dc * dc + j] = x[j];
+        }
+    }
+}
+
+// Constants of the FP64 transition of one model (one wave).
 template <class LY>
 __global__ __launch_bounds__(64) void poly_consts_kernel(DevModel mdl, double *out)
 {
     static_assert(PolyLayout<LY>::TOTAL <= PSSGP_CONST_DOUBLES, "constants exceed their workspace room");
-    static_assert(LY::bdim(0) <= 8 && LY::bdim(1) <= 8, "one thread per entry");
-    __shared__ double X[64];
+    poly_block<LY, 0>(mdl, out);
+    if constexpr (LY::NB > 1) poly_block<LY, 1>(mdl, out);
     for (int e = (int)threadIdx.x; e < LY::D * LY::D; e += (int)blockDim.x) out[PolyLayout<LY>::PINF + e] = mdl.Pinf[e];
-    for (int b = 0; b < LY::NB; b++) {
-        const int dc = LY::bdim(b), e = (int)threadIdx.x;
-        const DevBlock &bk = mdl.blk[b];
-        if (bk.kind != BLK_RBF) continue;
-        if (e < dc * dc) X[e] = (e / dc == e % dc) ? 1.0 : 0.0;
-        __syncthreads();
-        for (int k = 1; k <= POLY_DEG; k++) {
-            double acc = 0.0;
-            if (e < dc * dc) {
-                // (X G1)[i][j]: G1 is the superdiagonal and the last row
-                const int i = e / dc, j = e % dc;
-                acc = X[i * dc + dc - 1] * bk.glast[j];
-                if (j > 0) acc = fma(X[i * dc + j - 1], bk.gsup[j - 1], acc);
-                acc /= k;
-                out[PolyLayout<LY>::off(b) + (k - 1) * dc * dc + e] = acc;
-            }
-            __syncthreads();
-            if (e < dc * dc) X[e] = acc;
-            __syncthreads();
-        }
-    }
 }
 
 // Transition F = exp(dt G) and process noise Q = Pinf - F Pinf F^T of one
