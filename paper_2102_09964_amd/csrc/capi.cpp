@@ -33,10 +33,48 @@ struct Plan {
     size_t total = 0;
 };
 
-int chunk_of(const pssgp_options *o)
+// Default chunk of a scan over n steps. FP32: 16. FP64: as many tiles (one
+// wave each) as the chip has SIMDs (256 CUs x 4), or fewer where even
+// kMinDefaultChunk steps per lane do not give as many, and 16 at most. With a
+// fixed 16 a series of n steps is n / 1 024 waves, which below 2^20 steps
+// leaves SIMDs idle while every lane runs its 16 steps one after the other;
+// with fewer steps per lane the chain is shorter on the same number of
+// launches. Measured (FP64, us with 16 / with this rule): filter + smoother,
+// 1 536 steps at d = 2 59 / 39, 131 101 steps at d = 8 1 139 / 955, 300 007
+// steps at d = 6 639 / 524; loglik + gradient, 2 000 steps at d = 6 698 / 531.
+// Below 4 the lane scan and the passes' starts dominate (1, 2 and 4 are within
+// 10 % of each other). In FP32 fewer steps per lane round the lane-start
+// moments more often in FP32, and a default that moved with n would move the
+// log-likelihood in its eighth digit: there the choice stays the caller's
+// (or the tuner's). At d = 8 in FP64 the lane records are 76 KB a tile: three
+// quarters of the tiles, so that the calls on the 64 MiB of static scratch
+// fit as they do with 16.
+constexpr int kMinDefaultChunk = 4;
+
+int64_t fill_tiles(int d, bool f64) { return (f64 && d >= 8) ? 768 : 1024; }
+
+int default_chunk(int64_t n, int d, bool f64)
 {
-    int c = (o && o->chunk) ? (int)o->chunk : kDefaultChunk;
-    return c;
+    if (!f64) return kDefaultChunk;
+    const int64_t lanes = 64 * fill_tiles(d, f64);
+    const int64_t c = (n + lanes - 1) / lanes;
+    return (int)(c < kMinDefaultChunk ? kMinDefaultChunk : (c > kDefaultChunk ? kDefaultChunk : c));
+}
+
+int chunk_of(const pssgp_options *o, int64_t n, int d, bool f64)
+{
+    return (o && o->chunk) ? (int)o->chunk : default_chunk(n, d, f64);
+}
+
+// Tiles that the workspace of a default-chunk call is sized for: the most
+// that any n' <= n takes (the default grows with n, so the tile count alone
+// would not), so that a workspace for n serves every shorter series too.
+int64_t alloc_tiles(int64_t ntiles, int64_t n, int d, bool f64, const pssgp_options *o)
+{
+    if (!f64 || (o && o->chunk)) return ntiles;
+    const int64_t small = (n + 64 * kMinDefaultChunk - 1) / (64 * kMinDefaultChunk), full = fill_tiles(d, f64);
+    const int64_t most = small < full ? small : full;
+    return ntiles > most ? ntiles : most;
 }
 
 // Sizes (in T elements) of the per-tile payloads.
@@ -53,11 +91,17 @@ Plan make_plan(int d, int ncomp, int64_t n, pssgp_dtype dtype, int op, const pss
     Plan p;
     p.d = d;
     p.ns = d * (d + 1) / 2;
-    p.chunk = chunk_of(opts);
-    p.tsize = dtype == PSSGP_F64 ? 8 : 4;
+    const bool f64 = dtype == PSSGP_F64;
+    p.chunk = chunk_of(opts, n, d, f64);
+    p.tsize = f64 ? 8 : 4;
     const int64_t per_tile = (int64_t)64 * p.chunk;
     p.ntiles = (int)((n + per_tile - 1) / per_tile);
-    const size_t nt = (size_t)(p.ntiles > 0 ? p.ntiles : 1);
+    const int64_t nta = alloc_tiles(p.ntiles, n, d, f64, opts);
+    const size_t nt = (size_t)(nta > 0 ? nta : 1);
+    // steps of the per-step regions, whole tiles (one more with the FP64
+    // default, which keeps the size from falling where the chunk grows)
+    const bool fixed = !f64 || (opts && opts->chunk);
+    const size_t steps = (size_t)((p.ntiles > 0 ? p.ntiles : 1) + (fixed ? 0 : 1)) * per_tile;
     size_t off = ctl_bytes();
     auto take = [&](size_t bytes) {
         size_t o = off;
@@ -96,7 +140,7 @@ Plan make_plan(int d, int ncomp, int64_t n, pssgp_dtype dtype, int op, const pss
         p.off_fagg2 = take(nt * filter_agg_elems(d) * p.tsize);
         p.off_lane = take(nt * 64 * filter_agg_elems(d) * p.tsize);
         p.off_part = take(nt * sizeof(double) * n_params(ncomp));
-        p.off_hand = take(nt * 64 * (size_t)p.chunk * (d * d + d + d * (d + 1) / 2) * p.tsize);
+        p.off_hand = take(steps * (d * d + d + d * (d + 1) / 2) * p.tsize);
         p.off_slane = take(nt * 64 * (size_t)smooth_agg_elems(d) * p.tsize);
         p.total = off;
         return p;
@@ -113,7 +157,7 @@ Plan make_plan(int d, int ncomp, int64_t n, pssgp_dtype dtype, int op, const pss
     }
     p.off_part = take(nt * sizeof(double) * n_params(ncomp));
     if (op == PSSGP_OP_LOGLIK_GRAD) {
-        p.off_rec = take(nt * 64 * (size_t)p.chunk * grad_rec_elems(d) * p.tsize);  // tile layout
+        p.off_rec = take(steps * grad_rec_elems(d) * p.tsize);  // tile layout
         p.off_incl2 = take(nt * (d + d * (d + 1) / 2) * p.tsize);
         p.off_agg2 = take(nt * grad_agg_elems(d) * p.tsize);
         p.off_lane2 = take(nt * 64 * grad_agg_elems(d) * p.tsize);
@@ -286,8 +330,9 @@ int make_batch_plan(const pssgp_batch_group *groups, int ngroups, int64_t n_seri
             return PSSGP_EINVAL;
         }
     bp.ngroups = ngroups;
-    bp.chunk = chunk_of(opts);
-    bp.tsize = dtype == PSSGP_F64 ? 8 : 4;
+    const bool f64 = dtype == PSSGP_F64;
+    bp.chunk = chunk_of(opts, off[n_series], 0, f64);  // (d <= 3)
+    bp.tsize = f64 ? 8 : 4;
     int64_t expect = 0;
     int prev_d = 0;
     for (int gi = 0; gi < ngroups; gi++) {
@@ -342,8 +387,12 @@ int make_batch_plan(const pssgp_batch_group *groups, int ngroups, int64_t n_seri
         return PSSGP_EINVAL;
     }
     const int d = bp.dmax;
-    const size_t nt = (size_t)(bp.total_tiles > 0 ? bp.total_tiles : 1);
     const int64_t n = off[n_series];
+    // (each group ends with a tile of its own)
+    const int more = (!f64 || (opts && opts->chunk)) ? 0 : ngroups;
+    const int64_t nta = alloc_tiles(bp.total_tiles, n, d, f64, opts) + more;
+    const size_t nt = (size_t)(nta > 0 ? nta : 1);
+    const size_t steps = (size_t)((bp.total_tiles > 0 ? bp.total_tiles : 1) + more) * 64 * bp.chunk;
     size_t o = ctl_bytes();
     auto take = [&](size_t bytes) {
         size_t r = o;
@@ -364,7 +413,7 @@ int make_batch_plan(const pssgp_batch_group *groups, int ngroups, int64_t n_seri
         // smoother elements of every step in the tile layout; the slots of
         // the second group (larger state) start past the first group's
         // elements because the groups ascend in state size
-        bp.off_hand = take(nt * 64 * (size_t)bp.chunk * (d * d + d + d * (d + 1) / 2) * bp.tsize);
+        bp.off_hand = take(steps * (d * d + d + d * (d + 1) / 2) * bp.tsize);
         bp.off_slane = take(nt * 64 * (size_t)smooth_agg_elems(d) * bp.tsize);
     }
     bp.total = o;
