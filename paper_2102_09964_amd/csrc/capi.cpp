@@ -27,7 +27,7 @@ struct Plan {
     size_t off_incl2 = 0, off_lane2 = 0, off_part2 = 0, off_agg2 = 0;
     size_t off_x = 0, off_xraw = 0;  // plain baseline element arrays
     size_t off_gagg = 0, off_gcarry = 0;  // carry pass group scratch
-    size_t off_hand = 0;             // predict: filter-to-smoother handover
+    size_t off_hand = 0, off_bound = 0;  // predict: filter-to-smoother handover (steps, lane ends)
     size_t off_fagg2 = 0;            // second buffer of filter tile aggregates (team carry)
     size_t off_slane = 0;            // predict: the smoother's lane records
     size_t total = 0;
@@ -133,14 +133,15 @@ Plan make_plan(int d, int ncomp, int64_t n, pssgp_dtype dtype, int op, const pss
     }
     if (op == PSSGP_OP_PREDICT) {
         // filter then smoother on one stream: the scans share their regions
-        // (the filter's are the larger); the handover holds the smoother
-        // elements of every step, written by the filter in the tile layout
+        // (the filter's are the larger); the handover is FP64 whatever the
+        // scan type (HandLayout)
         p.off_incl = take(nt * filter_incl_elems(d) * p.tsize);
         p.off_agg = take(nt * filter_agg_elems(d) * p.tsize);
         p.off_fagg2 = take(nt * filter_agg_elems(d) * p.tsize);
         p.off_lane = take(nt * 64 * filter_agg_elems(d) * p.tsize);
         p.off_part = take(nt * sizeof(double) * n_params(ncomp));
-        p.off_hand = take(steps * (d * d + d + d * (d + 1) / 2) * p.tsize);
+        p.off_hand = take(steps * (d + 1) * sizeof(double));
+        p.off_bound = take(nt * 64 * (size_t)smooth_incl_elems(d) * sizeof(double));
         p.off_slane = take(nt * 64 * (size_t)smooth_agg_elems(d) * p.tsize);
         p.total = off;
         return p;
@@ -304,7 +305,7 @@ struct BatchPlan {
     BatchGroup g[2];
     BatchModel bm[2];
     size_t off_incl = 0, off_lane = 0, off_part = 0, off_terms = 0, off_cst = 0, off_agg = 0, total = 0;
-    size_t off_gagg = 0, off_gcarry = 0, off_hand = 0, off_slane = 0;
+    size_t off_gagg = 0, off_gcarry = 0, off_hand = 0, off_bound = 0, off_slane = 0;
 };
 
 int make_batch_plan(const pssgp_batch_group *groups, int ngroups, int64_t n_series, const int64_t *off,
@@ -410,10 +411,11 @@ int make_batch_plan(const pssgp_batch_group *groups, int ngroups, int64_t n_seri
     bp.off_cst = take(2 * PSSGP_CONST_DOUBLES * sizeof(double));
     if (op != PSSGP_OP_SMOOTH) bp.off_terms = take((size_t)(n > 0 ? n : 1) * sizeof(double));
     if (op == PSSGP_OP_PREDICT) {
-        // smoother elements of every step in the tile layout; the slots of
-        // the second group (larger state) start past the first group's
-        // elements because the groups ascend in state size
-        bp.off_hand = take(steps * (d * d + d + d * (d + 1) / 2) * bp.tsize);
+        // the handover (HandLayout); the slots of the second group (larger
+        // state) start past the first group's values because the groups
+        // ascend in state size
+        bp.off_hand = take(steps * (d + 1) * sizeof(double));
+        bp.off_bound = take(nt * 64 * (size_t)smooth_incl_elems(d) * sizeof(double));
         bp.off_slane = take(nt * 64 * (size_t)smooth_agg_elems(d) * bp.tsize);
     }
     bp.total = o;
@@ -483,10 +485,9 @@ int run_batched(const pssgp_batch_group *groups, int ngroups, int64_t n_series, 
     a.ws.cst = (double *)(b + bp.off_cst);
     a.ws.agg2 = nullptr;
     if (op == PSSGP_OP_PREDICT) {
-        a.m = b + bp.off_hand;
+        a.hand = (double *)(b + bp.off_hand);
+        a.bound = (double *)(b + bp.off_bound);
         a.slane = b + bp.off_slane;
-        a.P = nullptr;
-        a.tiled = 1;
     }
     const bool zero_ll = (op != PSSGP_OP_SMOOTH && a.n == 0);
     rc = launch_ws_init(a.ws.ctl, zero_ll ? loglik : nullptr,
@@ -822,7 +823,6 @@ int pssgp_predict(const pssgp_model *model, const double *t, const void *y, cons
     rc = launch_ws_init(sw.ctl, n == 0 ? loglik : nullptr, n == 0 ? 1 : 0, s);
     if ((rc = hip_err((hipError_t)rc, "workspace init"))) return rc;
     if (n == 0) return PSSGP_OK;
-    void *hand = b + p.off_hand;
     FilterLaunch a{};
     a.ev = opts ? opts->pass_events : nullptr;
     a.t = t;
@@ -832,11 +832,12 @@ int pssgp_predict(const pssgp_model *model, const double *t, const void *y, cons
     a.n = n;
     a.chunk = p.chunk;
     a.ntiles = p.ntiles;
-    a.m = hand;
+    a.m = nullptr;
     a.P = nullptr;
     a.loglik = loglik;
     a.rec = nullptr;
-    a.tiled = 1;
+    a.hand = (double *)(b + p.off_hand);
+    a.bound = (double *)(b + p.off_bound);
     a.slane = b + p.off_slane;
     a.ws = sw;
     rc = check_launch(launch_filter(dm, b0, b1, dtype == PSSGP_F64, a, s), "filter launch");
@@ -844,14 +845,15 @@ int pssgp_predict(const pssgp_model *model, const double *t, const void *y, cons
     SmoothLaunch sm{};
     sm.ev = opts ? opts->pass_events + 4 : nullptr;
     sm.t = t;
-    sm.m = hand;
-    sm.P = nullptr;
+    sm.y = y;
+    sm.mask = mask;
     sm.n = n;
     sm.chunk = p.chunk;
     sm.ntiles = p.ntiles;
     sm.f_mean = f_mean;
     sm.f_var = f_var;
-    sm.tiled = 1;
+    sm.hand = a.hand;
+    sm.bound = a.bound;
     sm.slane = b + p.off_slane;
     sm.ws = sw;
     return check_launch(launch_smoother(dm, b0, b1, dtype == PSSGP_F64, sm, s), "smoother launch");

@@ -25,6 +25,9 @@ template <int D, typename T>
 constexpr int fold_waves() { return sizeof(T) == 8 ? 1 : (D >= 6 ? 1 : 2); }
 template <int D, typename T>
 constexpr int finish_waves() { return sizeof(T) == 8 ? 1 : (D >= 6 ? 1 : 2); }
+// the smoother of a fused call works in FP64 for both scan types
+template <int D>
+constexpr int fused_waves() { return D >= 6 ? 1 : 2; }
 template <int D, typename T>
 constexpr int smoother_waves() { return sizeof(T) == 8 ? 1 : (D >= 7 ? 1 : 2); }
 
@@ -110,6 +113,12 @@ typedef const __attribute__((address_space(4))) double cdouble;
 // step loop, so that the loads through it are issued inside every
 // iteration instead of being hoisted (and held in registers) across it.
 #define PSSGP_LAUNDER(ptr) asm volatile("" : "+s"(ptr))
+
+// Whether the passes read the constants again in every step: with up to 3
+// states they are few (28 doubles at d = 3) and stay in scalar registers,
+// and a step, which is short there, does not wait for them.
+template <int D>
+constexpr bool reload_constants() { return D > 3; }
 
 // ------------------------------------------------------------------ FP64 discretisation
 
@@ -783,6 +792,28 @@ __device__ __forceinline__ void transition_fast(const DevModel &mdl, cdouble *cs
     if constexpr (LY::NB > 1) block(std::integral_constant<int, 1>());
 }
 
+// The same without the selects: F = I + Dl, which at a series start is 0 and
+// at a zero step I exactly, as dl_fast_block's first row is then.
+template <class LY>
+__device__ __forceinline__ void transition_plain(const DevModel &mdl, cdouble *cst, const StepScale &sc, double dt,
+                                                 bool first, double (&F)[LY::D][LY::D])
+{
+    auto block = [&](auto bc) {
+        constexpr int b = decltype(bc)::value;
+        constexpr int dc = LY::bdim(b);
+        constexpr int o = LY::boff(b);
+        double phi[dc], dl[dc][dc];
+        block_phi<LY, b>(mdl, sc, dt, phi);
+        dl_fast_block<LY, b>(cst, phi, first, dt == 0.0, dl);
+#pragma unroll
+        for (int i = 0; i < dc; i++)
+#pragma unroll
+            for (int j = 0; j < dc; j++) F[o + i][o + j] = dl[i][j] + (i == j ? 1.0 : 0.0);
+    };
+    block(std::integral_constant<int, 0>());
+    if constexpr (LY::NB > 1) block(std::integral_constant<int, 1>());
+}
+
 // ------------------------------------------------------------------ register linear algebra
 
 template <int D, typename T>
@@ -1094,6 +1125,33 @@ __device__ __forceinline__ void model_to_lds(const DevModel &src, DevModel &dst)
 
 #define PSSGP_RELOAD_CONSTANTS() asm volatile("" ::: "memory")
 
+// ------------------------------------------------------------------ step inputs
+
+// Optional per-step arrays (observation mask, noise variances) read without
+// a branch: a missing array is replaced by one that is always there and at
+// least as long (the times), whose values are then ignored. A load inside a
+// branch made the compiler wait for every outstanding memory operation,
+// the previous step's element stores included, right after the load.
+struct OptInputs {
+    const uint8_t *mask;
+    const double *noise;
+    bool has_mask, has_noise;
+    __device__ __forceinline__ OptInputs(const uint8_t *m, const double *nk, const double *t)
+        : mask(m ? m : (const uint8_t *)t), noise(nk ? nk : t), has_mask(m != nullptr), has_noise(nk != nullptr)
+    {
+    }
+    __device__ __forceinline__ bool observed(int64_t k) const
+    {
+        const uint8_t b = mask[k];
+        return !has_mask || b != 0;
+    }
+    __device__ __forceinline__ double noise_var(int64_t k) const
+    {
+        const double r = noise[k];
+        return has_noise ? r : 0.0;
+    }
+};
+
 // ------------------------------------------------------------------ series views
 //
 // The scans see their input through a series view that gives, per step, the
@@ -1134,6 +1192,11 @@ struct ManySeries {
         sc.inv_ell[1] = 0.0;
         sc.var_mult = prm[3 * s + 1];
         R = prm[3 * s + 2];
+        // waited for here, inside the branch of seek that crosses into another
+        // series: left pending, they make the compiler wait at the branch's
+        // join, in every step, for all outstanding memory operations (the
+        // next step's inputs and the stores of the steps before)
+        asm volatile("" ::"v"(beg), "v"(end), "v"(sc.inv_ell[0]), "v"(sc.var_mult), "v"(R));
     }
     // position on the series containing step k (binary search)
     __device__ __forceinline__ void locate(int64_t k)

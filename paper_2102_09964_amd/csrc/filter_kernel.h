@@ -30,9 +30,10 @@
 #include "tile_scan_team.h"
 
 // Finish-pass outputs: filter moments in the [entry][n] layout, per-step
-// records for the adjoint (RecLayout, tile layout), smoother elements in the
-// tile layout for the smoother of the same call.
-enum : int { F_MOMENTS = 1, F_RECS = 2, F_ELEMS = 4 };
+// records for the adjoint (RecLayout, tile layout), or what the smoother of
+// the same call needs (HandLayout: per-step predicted P h and h m, the lanes'
+// end moments and smoother elements).
+enum : int { F_MOMENTS = 1, F_RECS = 2, F_SMOOTH = 4 };
 
 template <typename T>
 struct FilterParams {
@@ -54,7 +55,9 @@ struct FilterParams {
     T *inclp;
     T *lanep;
     double *partials;
-    T *slane;  // fused call: the smoother's lane records, written by the finish (lane_aggregate_handover)
+    double *hand;   // F_SMOOTH: per-step handover to the smoother (HandLayout)
+    double *bound;  // F_SMOOTH: end moments of the lanes (HandLayout)
+    T *slane;       // F_SMOOTH: the smoother's lane records
 };
 
 // Tile geometry: steps [k_begin, k_end) split into ntiles tiles; workspace
@@ -89,31 +92,6 @@ __device__ __forceinline__ void step_transition(const DevModel &mdl, cdouble *cs
     }
 }
 
-// Optional per-step arrays (observation mask, noise variances) read without
-// a branch: a missing array is replaced by one that is always there and at
-// least as long (the times), whose values are then ignored. A load inside a
-// branch made the compiler wait for every outstanding memory operation,
-// the previous step's element stores included, right after the load.
-struct OptInputs {
-    const uint8_t *mask;
-    const double *noise;
-    bool has_mask, has_noise;
-    __device__ __forceinline__ OptInputs(const uint8_t *m, const double *nk, const double *t)
-        : mask(m ? m : (const uint8_t *)t), noise(nk ? nk : t), has_mask(m != nullptr), has_noise(nk != nullptr)
-    {
-    }
-    __device__ __forceinline__ bool observed(int64_t k) const
-    {
-        const uint8_t b = mask[k];
-        return !has_mask || b != 0;
-    }
-    __device__ __forceinline__ double noise_var(int64_t k) const
-    {
-        const double r = noise[k];
-        return has_noise ? r : 0.0;
-    }
-};
-
 // Per-lane view of the step inputs with the next step's values loaded one
 // iteration ahead.
 template <typename T>
@@ -136,55 +114,58 @@ struct StepInputs {
     }
 };
 
-// Smoother element of step k (supplement, Proposition 2), built by the
-// filter right after predicting step k + 1, from what that prediction
-// already holds: the filtered moments (m, P) of step k and, in FP64,
-// Y = F P, mp = F m and Pp = F P F^T + Q of step k + 1:
-//   Pp = C C^T (Cholesky), Y = C^-1 F P, L = P - Y^T Y,
-//   E = (C^-T Y)^T = P F^T Pp^-1, g = m - E mp.
-// At the last step of a series the caller passes the prior transition
-// (F = 0, Q = Pinf), for which these give exactly the element (0, m, P).
+// Smoother element of a lane: the map from the smoothed moments of the lane's
+// last step to those of the step before its first one (supplement,
+// Proposition 2, for the whole run of steps at once). The finish pass runs,
+// next to the filter, the fixed-point smoother of that earlier state: its
+// moments (m0, P0) given the lane's observations so far and its
+// cross-covariance G with the current state (row: current state), which
+// start as the lane's entering moments and P and are updated per step by
+// G <- F G, w = G^T h, m0 += w v / S, P0 -= w w^T / S, G -= K w^T. With (m, P)
+// the filter moments of the last step and P = C C^T,
+//   Z = C^-1 G, L = P0 - Z^T Z, E = (C^-T Z)^T = G^T P^-1, g = m0 - E m.
+// This is what composing the steps' elements gives, without forming one per
+// step (no Cholesky factor, solves and three matrix products per step). A
+// series start inside the lane has F = 0, so G = 0 and E = 0 from there on.
 // e receives the element rounded to T, in the smoother's coordinates
-// z' = S z, S = I + e_0 e_B^T (smoother_shear_col; B = 0: identity).
-// (m, P) come in U (the filter carries them in FP64).
-template <int D, int B, typename T, typename U = T>
-__device__ __forceinline__ void smoother_element_from_prediction(const U (&m)[D], const U (&P)[D][D],
-                                                                 double (&Y)[D][D], const double (&mp)[D],
-                                                                 const double (&Pp)[D][D], SAgg<D, T> &e,
-                                                                 uint32_t &bad)
+// z' = S z, S = I + e_0 e_B^T (smoother_shear_col; B = 0: identity); C the
+// factor with the reciprocals rd of its diagonal.
+template <int D, int B, typename T>
+__device__ __forceinline__ void lane_smoother_element(const double (&m0)[D], double (&P0)[D][D], double (&G)[D][D],
+                                                      const double (&m)[D], const double (&P)[D][D],
+                                                      double (&C)[D][D], double (&rd)[D], SAgg<D, T> &e,
+                                                      uint32_t &bad)
 {
-    // Y holds F P on entry and is overwritten
-    double C[D][D];
+    // G is overwritten
 #pragma unroll
     for (int i = 0; i < D; i++)
 #pragma unroll
-        for (int j = 0; j <= i; j++) C[i][j] = Pp[i][j];
-    double rd[D];  // reciprocals of the Cholesky diagonal
+        for (int j = 0; j <= i; j++) C[i][j] = P[i][j];
     if (!cholesky<D, double>(C, rd)) bad |= PSSGP_STATUS_CHOLESKY;
 #pragma unroll
     for (int j = 0; j < D; j++)
 #pragma unroll
         for (int i = 0; i < D; i++) {
-            double acc = Y[i][j];
+            double acc = G[i][j];
 #pragma unroll
-            for (int q = 0; q < i; q++) acc = fma(-C[i][q], Y[q][j], acc);
-            Y[i][j] = acc * rd[i];
+            for (int q = 0; q < i; q++) acc = fma(-C[i][q], G[q][j], acc);
+            G[i][j] = acc * rd[i];
         }
-    // L' = S P S^T - (Y S^T)^T (Y S^T); Y S^T is column 0 plus column B
+    // L' = S P0 S^T - (Z S^T)^T (Z S^T); Z S^T is column 0 plus column B
     if constexpr (B > 0) {
 #pragma unroll
-        for (int q = 0; q < D; q++) Y[q][0] += Y[q][B];
+        for (int q = 0; q < D; q++) G[q][0] += G[q][B];
     }
 #pragma unroll
     for (int i = 0; i < D; i++)
 #pragma unroll
         for (int j = i; j < D; j++) {
-            double acc = (double)P[i][j];
+            double acc = P0[i][j];
             if constexpr (B > 0) {
-                if (i == 0) acc += (double)P[B][j] + (j == 0 ? (double)P[0][B] + (double)P[B][B] : 0.0);
+                if (i == 0) acc += P0[j < B ? j : B][j < B ? B : j] + (j == 0 ? P0[0][B] + P0[B][B] : 0.0);
             }
 #pragma unroll
-            for (int q = 0; q < D; q++) acc = fma(-Y[q][i], Y[q][j], acc);
+            for (int q = 0; q < D; q++) acc = fma(-G[q][i], G[q][j], acc);
             e.L[i][j] = T(acc);
             e.L[j][i] = e.L[i][j];
         }
@@ -192,38 +173,24 @@ __device__ __forceinline__ void smoother_element_from_prediction(const U (&m)[D]
     for (int j = 0; j < D; j++)
 #pragma unroll
         for (int i = D - 1; i >= 0; i--) {
-            double acc = Y[i][j];
+            double acc = G[i][j];
 #pragma unroll
-            for (int q = i + 1; q < D; q++) acc = fma(-C[q][i], Y[q][j], acc);
-            Y[i][j] = acc * rd[i];
+            for (int q = i + 1; q < D; q++) acc = fma(-C[q][i], G[q][j], acc);
+            G[i][j] = acc * rd[i];
         }
-    // Y = (S E)^T: g' = S m - (S E) mp, E' = (S E) S^-1 (column B minus column 0)
+    // G = (S E)^T: g' = S m0 - (S E) m, E' = (S E) S^-1 (column B minus column 0)
 #pragma unroll
     for (int i = 0; i < D; i++) {
-        double acc = (double)m[i];
+        double acc = m0[i];
         if constexpr (B > 0) {
-            if (i == 0) acc += (double)m[B];
+            if (i == 0) acc += m0[B];
         }
 #pragma unroll
-        for (int q = 0; q < D; q++) acc = fma(-Y[q][i], mp[q], acc);
+        for (int q = 0; q < D; q++) acc = fma(-G[q][i], m[q], acc);
         e.g[i] = T(acc);
 #pragma unroll
-        for (int j = 0; j < D; j++) e.E[i][j] = T((B > 0 && j == B) ? Y[B][i] - Y[0][i] : Y[j][i]);
+        for (int j = 0; j < D; j++) e.E[i][j] = T((B > 0 && j == B) ? G[B][i] - G[0][i] : G[j][i]);
     }
-}
-
-// The smoother element of a step is handed over (stored in the tile layout
-// with non-temporal stores: it is read back only after the whole filter, and
-// with ordinary stores the caches fetched every line before writing it,
-// which doubled the pass's HBM traffic) and, where the smoother takes lane
-// aggregates from the filter
-// (lane_aggregate_handover), also appended to the lane's running smoother
-// aggregate: acc <- acc (x) e (acc covers the lane's earlier steps).
-template <int D, typename T, bool LANEAGG>
-__device__ __forceinline__ void hand_over_element(const SAgg<D, T> &e, T *out, SAgg<D, T> &acc)
-{
-    sagg_store_nt<D, T>(out, e, PSSGP_WAVE);
-    if constexpr (LANEAGG) sagg_combine<D, T>(acc, e, acc);
 }
 
 // Predicted moments of one step in FP64 from (m, P) (in T) and the FP64
@@ -265,6 +232,57 @@ __device__ __forceinline__ void predict_step(const T (&m)[D], const T (&P)[D][D]
         }
 }
 
+// One step of the fixed-point smoother of the state before the lane
+// (lane_smoother_element), in two parts so that the transition's operands are
+// dead before the conditioning: G <- F G with Dl = F - I, and the update with
+// gain K, innovation v, w = 1 / S (0 at a missing step) and r = R / S (1
+// there). h (I - K h) = r h: the observed row of G is scaled by r, since
+// 1 - h K would lose log10(S / R) digits. P0 is kept in its upper triangle;
+// B as in smoother_shear_col.
+template <int D, class SP>
+__device__ __forceinline__ void fixed_point_predict(const double (&Dl)[D][D], double (&G)[D][D])
+{
+#pragma unroll
+    for (int c = 0; c < D; c++) {
+        double g[D];
+#pragma unroll
+        for (int i = 0; i < D; i++) {
+            double acc = G[i][c];
+#pragma unroll
+            for (int q = 0; q < D; q++)
+                if (SP::dl(i, q)) acc = fma(Dl[i][q], G[q][c], acc);
+            g[i] = acc;
+        }
+#pragma unroll
+        for (int i = 0; i < D; i++) G[i][c] = g[i];
+    }
+}
+
+template <int D, int B, class SP>
+__device__ __forceinline__ void fixed_point_update(const double (&K)[D], double v, double w, double r,
+                                                   double (&m0)[D], double (&P0)[D][D], double (&G)[D][D])
+{
+    double wh[D];
+#pragma unroll
+    for (int c = 0; c < D; c++) {
+        double acc = 0.0;
+#pragma unroll
+        for (int i = 0; i < D; i++)
+            if (SP::obs(i)) acc += G[i][c];
+        wh[c] = acc;
+#pragma unroll
+        for (int i = 1; i < D; i++) G[i][c] = fma(-K[i], acc, G[i][c]);
+        G[0][c] = B > 0 ? fma(r, acc, -G[B][c]) : r * acc;
+    }
+#pragma unroll
+    for (int i = 0; i < D; i++) {
+        const double a = wh[i] * w;
+        m0[i] = fma(a, v, m0[i]);
+#pragma unroll
+        for (int j = i; j < D; j++) P0[i][j] = fma(-a, wh[j], P0[i][j]);
+    }
+}
+
 // Fold pass of one tile: each lane folds its chunk into an aggregate, the
 // wave scans the 64 chunk aggregates (inclusive, time order) and stores them
 // at lanep; lane 63 then holds the tile aggregate.
@@ -294,13 +312,13 @@ __device__ __forceinline__ void filter_tile_fold(const FilterParams<T> &p, const
         const T yn = p.y[kn];
         const bool on = opt.observed(kn);
         const T R = T(opt.noise_var(k));
-        PSSGP_RELOAD_CONSTANTS();
+        if constexpr (reload_constants<D>()) PSSGP_RELOAD_CONSTANTS();
         sv.seek(k);
         const bool first = sv.first(k);
         from_start = from_start || first;
         const double dt = first ? 0.0 : in.tc - in.tp;
         cdouble *c = cst;
-        PSSGP_LAUNDER(c);
+        if constexpr (reload_constants<D>()) PSSGP_LAUNDER(c);
         T Dl[D][D], Q[D][D];
         step_transition<LY, T, T>(mdl, c, sv.sc, dt, first, Dl, Q);
         const T yk = in.oc ? in.yc : T(0);
@@ -378,10 +396,8 @@ __device__ __forceinline__ void filter_tile_finish(const FilterParams<T> &p, con
     for (int i = 0; i < D; i++) h[i] = T(LY::hobs(i));
     uint32_t bad = 0;
 
-    // smoother lane aggregate accumulated from the handed-over elements
-    constexpr bool LANEAGG = (MODE & F_ELEMS) != 0 && lane_aggregate_handover<D>();
-    SAgg<D, T> sacc;
-    if constexpr (LANEAGG) sagg_identity<D, T>(sacc);
+    constexpr bool SMOOTH = (MODE & F_SMOOTH) != 0;
+    using HL = HandLayout<D>;
 
     T m0[D], P0[D][D];
     moments_load<D, T>(p.inclp + (size_t)slot * INCL, m0, P0);
@@ -404,6 +420,16 @@ __device__ __forceinline__ void filter_tile_finish(const FilterParams<T> &p, con
 #pragma unroll
         for (int j = 0; j < D; j++) P[i][j] = (double)P0[i][j];
     }
+    // fixed-point smoother of the state before the lane (lane_smoother_element)
+    double fm[D], fP[D][D], fG[D][D];
+    if constexpr (SMOOTH) {
+#pragma unroll
+        for (int i = 0; i < D; i++) {
+            fm[i] = m[i];
+#pragma unroll
+            for (int j = 0; j < D; j++) fP[i][j] = fG[i][j] = P[i][j];
+        }
+    }
 
     double ll = 0.0;  // FP64 per-lane sum of the log-likelihood terms
     // many series: one FP64 partial sum of the terms per series segment of
@@ -417,21 +443,18 @@ __device__ __forceinline__ void filter_tile_finish(const FilterParams<T> &p, con
     asm volatile("" ::"v"(in.tc), "v"(in.tp), "v"(in.yc), "v"((int)in.oc));
     const OptInputs opt(p.mask, p.noise_k, p.t);
     for (int64_t k = k0; k < k1; k++) {
-        // the last step of the lane loads the time of the next lane's first
-        // step, which its smoother element needs after the loop: no load
-        // after the loop waits behind the element stores
-        const int64_t kn = (k + 1 < tr.k_end) ? k + 1 : k;
+        const int64_t kn = (k + 1 < k1) ? k + 1 : k;
         const double tn = p.t[kn];
         const T yn = p.y[kn];
         const bool on = opt.observed(kn);
         const T Rk = T(opt.noise_var(k));
-        PSSGP_RELOAD_CONSTANTS();
+        if constexpr (reload_constants<D>()) PSSGP_RELOAD_CONSTANTS();
         sv.seek(k);
         const bool first = sv.first(k);
         const double dt = first ? 0.0 : in.tc - in.tp;
         if (!(dt >= 0.0)) bad |= (dt < 0.0) ? PSSGP_STATUS_UNSORTED : PSSGP_STATUS_NONFINITE;
         cdouble *c = cst;
-        PSSGP_LAUNDER(c);
+        if constexpr (reload_constants<D>()) PSSGP_LAUNDER(c);
         double Dl[D][D], Q[D][D];
         step_transition<LY, double, T>(mdl, c, sv.sc, dt, first, Dl, Q);
         const bool obs = in.oc;
@@ -444,19 +467,11 @@ __device__ __forceinline__ void filter_tile_finish(const FilterParams<T> &p, con
         // predict in FP64 (mp = F m, Y = F P, Pp = F P F^T + Q)
         double mp[D], Y[D][D], Pp[D][D];
         predict_step<D, double, Sparsity<LY>>(m, P, Dl, Q, mp, Y, Pp);
+        if constexpr (SMOOTH) fixed_point_predict<D, Sparsity<LY>>(Dl, fG);
         // the loads of this iteration are waited for here, before the
-        // element stores: the wait counter is in order, so a wait after
+        // handover stores: the wait counter is in order, so a wait after
         // the stores would also wait for all of them
         asm volatile("" ::"v"(tn), "v"(yn), "v"((int)on), "v"(Rk));
-        if constexpr ((MODE & F_ELEMS) != 0) {
-            // smoother element of the previous step of this lane
-            if (k > k0) {
-                SAgg<D, T> e;
-                smoother_element_from_prediction<D, smoother_shear_col<LY>(), T, double>(m, P, Y, mp, Pp, e, bad);
-                hand_over_element<D, T, LANEAGG>(e, p.m + elem_index<D>(slot, p.chunk, (int)(k - 1 - k0), lane),
-                                                 sacc);
-            }
-        }
         // conditioning on y_k in FP64 (symmetric form): the subtraction
         // that cancels when the noise is small against the predicted
         // variance is done in FP64
@@ -501,6 +516,14 @@ __device__ __forceinline__ void filter_tile_finish(const FilterParams<T> &p, con
         double K[D];
 #pragma unroll
         for (int i = 0; i < D; i++) K[i] = Ph[i] * w;
+        if constexpr (SMOOTH) {
+            // non-temporal: read back by the smoother after all of it is written
+            double *hp = p.hand + HL::step(slot, p.chunk, (int)(k - k0), lane);
+#pragma unroll
+            for (int i = 0; i < D; i++) __builtin_nontemporal_store(Ph[i], hp + i * PSSGP_WAVE);
+            __builtin_nontemporal_store(hm, hp + D * PSSGP_WAVE);
+            fixed_point_update<D, smoother_shear_col<LY>(), Sparsity<LY>>(K, v, w, obs ? (double)R * w : 1.0, fm, fP, fG);
+        }
         if constexpr ((MODE & F_RECS) != 0) {
             constexpr int NS = RecLayout<D>::NS;
             constexpr size_t W = PSSGP_WAVE;
@@ -538,38 +561,46 @@ __device__ __forceinline__ void filter_tile_finish(const FilterParams<T> &p, con
                 for (int j = i; j < D; j++) p.P[(size_t)sidx<D>(i, j) * p.n + k] = T(P[i][j]);
         }
     }
-    if constexpr ((MODE & F_ELEMS) != 0) {
-        // element of the lane's last step: predict the next step (the first of
-        // the next lane), or take the prior transition at a series end
+    if constexpr (SMOOTH) {
+        // the lane's smoother element (identity for a lane without steps) and
+        // its end moments, the covariance as its Cholesky factor
+        SAgg<D, T> sacc;
+        sagg_identity<D, T>(sacc);
         if (k1 > k0) {
+            // a series that ends with the lane: the fixed-point smoother has
+            // seen all its observations (E = 0)
             sv.seek(k1 - 1);
             const bool end = (k1 >= tr.k_end) || sv.last(k1 - 1);
-            const double dt = end ? 0.0 : in.tc - in.tp;  // t[k1] - t[k1 - 1]
-            cdouble *c = cst;
-            PSSGP_LAUNDER(c);
-            double Dl[D][D], Q[D][D], mp[D], Y[D][D], Pp[D][D];
-            step_transition<LY, double, T>(mdl, c, sv.sc, dt, end, Dl, Q);
-            predict_step<D, double, Sparsity<LY>>(m, P, Dl, Q, mp, Y, Pp);
-            SAgg<D, T> e;
-            smoother_element_from_prediction<D, smoother_shear_col<LY>(), T, double>(m, P, Y, mp, Pp, e, bad);
-            hand_over_element<D, T, LANEAGG>(e, p.m + elem_index<D>(slot, p.chunk, (int)(k1 - 1 - k0), lane),
-                                             sacc);
+#pragma unroll
+            for (int i = 0; i < D; i++)
+#pragma unroll
+                for (int j = 0; j < D; j++) fG[i][j] = end ? 0.0 : fG[i][j];
+            double C[D][D], rd[D];
+            lane_smoother_element<D, smoother_shear_col<LY>(), T>(fm, fP, fG, m, P, C, rd, sacc, bad);
+            double *bp = p.bound + HL::lane(slot, lane);
+#pragma unroll
+            for (int i = 0; i < D; i++) {
+                bp[i * PSSGP_WAVE] = m[i];
+#pragma unroll
+                for (int j = 0; j <= i; j++)
+                    bp[(D + sidx<D>(j, i)) * PSSGP_WAVE] = (i == j) ? rd[i] : C[i][j];
+            }
         }
-        // the smoother's fold pass over this tile, done here: the wave scans
-        // the lanes' smoother aggregates (identity for a lane without steps)
-        // as suffixes (inclusive, reverse time order) into the lane records
-        // at slane, and lane 0 stores the tile aggregate in the scan region
-        // the two scans share (the filter's carry has consumed it)
-        if constexpr (LANEAGG) {
-            constexpr int SAGG = SAggLayout<D>::SIZE;
+        // the smoother's fold pass over this tile: the wave scans the lanes'
+        // elements as suffixes (inclusive, reverse time order) into the lane
+        // records at slane, and lane 0 stores the tile aggregate in the scan
+        // region the two scans share (the filter's carry has consumed it);
+        // with smoother_by_rows a launch of its own does that scan
+        constexpr int SAGG = SAggLayout<D>::SIZE;
+        if constexpr (!smoother_by_rows<D, T>()) {
             for (int o = 1; o < PSSGP_WAVE; o <<= 1) {
                 SAgg<D, T> other;
                 sagg_shfl_down<D, T>(sacc, other, o);
                 if (lane + o < PSSGP_WAVE) sagg_combine<D, T>(sacc, other, sacc);
             }
-            sagg_store<D, T>(lane_rec(p.slane, slot, SAGG, lane), sacc, PSSGP_WAVE);
             if (lane == 0) sagg_store<D, T>(p.aggp + (size_t)slot * SAGG, sacc);
         }
+        sagg_store<D, T>(lane_rec(p.slane, slot, SAGG, lane), sacc, PSSGP_WAVE);
     }
     if constexpr (SEG) {
         if (p.ll_terms && k1 > k0) p.ll_terms[seg_k] = seg;
@@ -668,6 +699,8 @@ FilterParams<T> filter_params(const FilterLaunch &a)
     p.aggp = (T *)a.ws.aggp;
     p.lanep = (T *)a.ws.lanep;
     p.partials = a.ws.partials;
+    p.hand = a.hand;
+    p.bound = a.bound;
     p.slane = (T *)a.slane;
     return p;
 }
@@ -700,8 +733,8 @@ int launch_filter_t(const DevModel &mdl, const FilterLaunch &a, hipStream_t s)
         pass_event(a.ev, 2, s);
         // lane-start moments (the lane's exclusive prefix applied to the
         // tile's carry, once per lane) in FP64
-        if (a.m && a.tiled)
-            hipLaunchKernelGGL((filter_finish_kernel<LY, T, double, F_ELEMS>), grid, block, 0, s, p, mdl);
+        if (a.hand)
+            hipLaunchKernelGGL((filter_finish_kernel<LY, T, double, F_SMOOTH>), grid, block, 0, s, p, mdl);
         else if (a.m)
             hipLaunchKernelGGL((filter_finish_kernel<LY, T, double, F_MOMENTS>), grid, block, 0, s, p, mdl);
         else

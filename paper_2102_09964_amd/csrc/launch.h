@@ -48,8 +48,9 @@ struct FilterLaunch {
     void *P;         // nullable
     double *loglik;  // nullable
     void *rec;       // nullable: per-step records of the adjoint (tile layout)
-    int tiled;       // write smoother elements to m (P unused) in the tile layout of the handover
-    void *slane;     // tiled: the smoother's lane records, written by the finish (lane_aggregate_handover)
+    double *hand;    // nullable: fused call, per-step handover to the smoother (HandLayout; m, P unused)
+    double *bound;   // hand: the lanes' end moments
+    void *slane;     // hand: the smoother's lane records
     ScanWs ws;
 };
 
@@ -65,8 +66,11 @@ struct SmoothLaunch {
     void *f_var;
     void *ms;  // nullable
     void *Ps;  // nullable
-    int tiled; // m holds the smoother elements in the tile layout (P unused)
-    const void *slane;  // tiled: the smoother's lane records written by the filter's finish
+    const void *y;        // hand: the filter's observations
+    const uint8_t *mask;  // hand: their mask (nullable)
+    const double *hand;   // nullable: fused call, what the filter's finish wrote (m, P unused)
+    const double *bound;
+    void *slane;
     ScanWs ws;
 };
 
@@ -123,8 +127,9 @@ struct BatchLaunch {
     void *f_var;
     double *loglik;           // device [n_series]
     void *ll_terms;           // workspace [n]: log-likelihood partials at segment starts
-    int tiled;                // m: smoother-element handover (filter then smoother in one call)
-    void *slane;              // tiled: the smoother's lane records (written by the filter's finish)
+    double *hand;             // nullable: filter then smoother in one call, the handover (HandLayout)
+    double *bound;
+    void *slane;              // hand: the smoother's lane records (written by the filter's finish)
     ScanWs ws;
 };
 
@@ -132,7 +137,7 @@ int launch_batched_filter(const BatchLaunch &a, bool f64, hipStream_t s);
 // the filter without moment outputs (log-likelihood only)
 int launch_batched_loglik(const BatchLaunch &a, bool f64, hipStream_t s);
 int launch_batched_smooth(const BatchLaunch &a, bool f64, hipStream_t s);
-// filter writing the handover, then the smoother reading it (a.tiled = 1;
+// filter writing the handover, then the smoother reading it (a.hand;
 // a.ev, when set, holds 8 events: filter passes, then smoother passes)
 int launch_batched_predict(const BatchLaunch &a, bool f64, hipStream_t s);
 

@@ -43,7 +43,10 @@ struct SmoothParams {
     T *inclp;
     T *lanep;
     const double *cst;  // model constants of the transition
-    const T *slane;     // fused call: lane records written by the filter's finish
+    const T *y;             // fused call: the filter's inputs
+    const uint8_t *mask;
+    const double *hand;     // fused call: the filter's handover (HandLayout)
+    const double *bound;
 };
 
 struct STileRange {
@@ -56,7 +59,7 @@ struct STileRange {
 // right, the wave scans the 64 chunk aggregates as suffixes (inclusive,
 // reverse time order) and stores them at lanep; lane 0 then holds the tile
 // aggregate.
-template <class LY, typename T, bool ELEMS, class SV>
+template <class LY, typename T, class SV>
 __device__ __forceinline__ void smoother_tile_fold(const SmoothParams<T> &p, const DevModel &mdl,
                                                    cdouble *cst, SV &sv, const STileRange &tr, int tile)
 {
@@ -70,19 +73,14 @@ __device__ __forceinline__ void smoother_tile_fold(const SmoothParams<T> &p, con
     uint32_t bad = 0;  // reported by the finish pass
     SAgg<D, T> agg;
     sagg_identity<D, T>(agg);
-    // (a fused call with lane aggregates has its fold pass done by the
-    // filter's finish pass and does not launch this one)
+    // (a fused call has its fold pass done by the filter's finish pass)
     for (int64_t k = k1 - 1; k >= k0; k--) {
-        PSSGP_RELOAD_CONSTANTS();
+        if constexpr (reload_constants<D>()) PSSGP_RELOAD_CONSTANTS();
         sv.seek(k);
         SAgg<D, T> e;
-        if constexpr (ELEMS) {
-            sagg_load_nt<D, T>(p.m + elem_index<D>(slot, p.chunk, (int)(k - k0), lane), e, PSSGP_WAVE);
-        } else {
-            cdouble *c = cst;
-            PSSGP_LAUNDER(c);
-            smoother_element<LY, T, SV>(mdl, c, sv, p.t, p.m + k, p.P + k, (size_t)p.n, k, e, bad);
-        }
+        cdouble *c = cst;
+        if constexpr (reload_constants<D>()) PSSGP_LAUNDER(c);
+        smoother_element<LY, T, SV>(mdl, c, sv, p.t, p.m + k, p.P + k, (size_t)p.n, k, e, bad);
         sagg_combine<D, T>(e, agg, agg);
     }
     if constexpr (smoother_by_rows<D, T>()) {
@@ -102,16 +100,7 @@ __device__ __forceinline__ void smoother_tile_fold(const SmoothParams<T> &p, con
 // Finish pass of one tile: each lane takes the smoothed moments entering
 // the tile from the right (carry pass), applies its exclusive lane suffix
 // and runs the backward RTS recursion over its chunk.
-// Steps whose handed-over elements the smoother finish loads ahead of their
-// use, per group (small states only: their per-step work is short against a
-// load's latency).
-template <int D>
-constexpr int smoother_prefetch_group()
-{
-    return D <= 2 ? 4 : (D == 3 ? 2 : 1);
-}
-
-template <class LY, typename T, bool FULL, bool ELEMS, class SV>
+template <class LY, typename T, bool FULL, class SV>
 __device__ __forceinline__ void smoother_tile_finish(const SmoothParams<T> &p, const DevModel &mdl,
                                                      cdouble *cst, SV &sv, const STileRange &tr, int tile,
                                                      T *s_out)
@@ -139,8 +128,13 @@ __device__ __forceinline__ void smoother_tile_finish(const SmoothParams<T> &p, c
         sagg_load<D, T>(lane_rec(p.lanep, slot, AGG, lane + 1), excl, PSSGP_WAVE);
         sagg_apply<D, T>(excl, ms, Ps, ms, Ps);
     }
-    // one step of the backward recursion from its element
-    auto step_out = [&](const SAgg<D, T> &e, int64_t k) {
+    for (int64_t k = k1 - 1; k >= k0; k--) {
+        if constexpr (reload_constants<D>()) PSSGP_RELOAD_CONSTANTS();
+        sv.seek(k);
+        SAgg<D, T> e;
+        cdouble *c = cst;
+        if constexpr (reload_constants<D>()) PSSGP_LAUNDER(c);
+        smoother_element<LY, T, SV>(mdl, c, sv, p.t, p.m + k, p.P + k, (size_t)p.n, k, e, bad);
         sagg_apply<D, T>(e, ms, Ps, ms, Ps);
         T Ph[D];
         mat_vec<D, T>(Ps, h, Ph);
@@ -157,50 +151,6 @@ __device__ __forceinline__ void smoother_tile_finish(const SmoothParams<T> &p, c
 #pragma unroll
                 for (int j = i; j < D; j++) p.Ps[(size_t)sidx<D>(i, j) * p.n + k] = Po[i][j];
         }
-    };
-    // (single series only: in the batched form, chunk 16 over series of
-    // uneven lengths, the grouping measured 5 % slower)
-    constexpr int G = std::is_same<SV, OneSeries>::value ? smoother_prefetch_group<D>() : 1;
-    if constexpr (ELEMS && G > 1) {
-        // small states: the elements of the next G steps are loaded while
-        // the current G are processed (a lane's recursion is otherwise one
-        // dependent load per step); indices below k0 are clamped to k0, so
-        // every load is in the tile's region and none sits in a branch
-        auto load = [&](int64_t k, SAgg<D, T> &e) {
-            const int j = k >= k0 ? (int)(k - k0) : 0;
-            sagg_load_nt<D, T>(p.m + elem_index<D>(slot, p.chunk, j, lane), e, PSSGP_WAVE);
-        };
-        SAgg<D, T> cur[G], nxt[G];
-#pragma unroll
-        for (int g = 0; g < G; g++) load(k1 - 1 - g, cur[g]);
-        for (int64_t kb = k1 - 1; kb >= k0; kb -= G) {
-#pragma unroll
-            for (int g = 0; g < G; g++) load(kb - G - g, nxt[g]);
-#pragma unroll
-            for (int g = 0; g < G; g++) {
-                const int64_t k = kb - g;
-                if (k >= k0) {
-                    sv.seek(k);
-                    step_out(cur[g], k);
-                }
-            }
-#pragma unroll
-            for (int g = 0; g < G; g++) cur[g] = nxt[g];
-        }
-    } else {
-        for (int64_t k = k1 - 1; k >= k0; k--) {
-            PSSGP_RELOAD_CONSTANTS();
-            sv.seek(k);
-            SAgg<D, T> e;
-            if constexpr (ELEMS) {
-                sagg_load_nt<D, T>(p.m + elem_index<D>(slot, p.chunk, (int)(k - k0), lane), e, PSSGP_WAVE);
-            } else {
-                cdouble *c = cst;
-                PSSGP_LAUNDER(c);
-                smoother_element<LY, T, SV>(mdl, c, sv, p.t, p.m + k, p.P + k, (size_t)p.n, k, e, bad);
-            }
-            step_out(e, k);
-        }
     }
     __syncthreads();
     for (int i = lane; i < tile_len; i += PSSGP_WAVE) {
@@ -213,9 +163,287 @@ __device__ __forceinline__ void smoother_tile_finish(const SmoothParams<T> &p, c
     if (bad) status_or(&p.ctl->status, bad);
 }
 
-// ELEMS: the smoother elements come from the filter of the same call (tile
-// layout at p.m) instead of being built from the filter moments.
-template <class LY, typename T, bool ELEMS>
+// Smoother pass of a fused call: one tile. Up to the lane's last step it is
+// the RTS smoother (the smoothed moments there come from the carry and the
+// lane's exclusive suffix); inside the lane the same recursion runs in the
+// form of Bryson and Frazier, on the pair (lambda, Lambda) with
+//   m^s = m + P lambda,   P^s = P - P Lambda P
+// for the filter moments (m, P) of the step, in FP64:
+//   lambda = P^-1 (m^s - m), Lambda = P^-1 (P - P^s) P^-1   at the lane's end,
+//   step k, from the filtered to the predicted moments, with the predicted
+//   P h, S = h P h^T + R, K = P h / S:
+//     Lambda <- (I - K h)^T Lambda (I - K h) + h^T h / S
+//     lambda <- (I - K h)^T lambda + h^T v / S
+//   and over the transition before it, Lambda <- F^T Lambda F, lambda <- F^T lambda.
+// f needs only P h and h m of the step, so that the filter hands over D + 1
+// values per step instead of the D^2 + D + D (D + 1) / 2 of a smoother element
+// and forms no element per step. With r = R / S (1 at a missing step) the
+// filtered P h is r times the predicted one, f_var = r h P h^T - r^2 (P h)^T
+// Lambda (P h) and f_mean = h m + h P h^T v / S + r (P h)^T lambda.
+// f_var is a difference, which FP64 carries: against RTS in extended
+// precision its error is that of RTS in FP64 (3e-15 to 4e-13 over gaps from
+// 1e-3 to 3 length-scales and noise variances down to 1e-6).
+// Handover and elements together: filter finish + smoother of 2^22 steps at
+// d = 6 (FP32, chunk 64) 473 + 167 us with an element per step (63 values; a
+// Cholesky factor, two solves and a composition), 313 + 185 us in this form,
+// which is bound by its instructions (973 per step, of them 330 for F).
+template <class LY, typename T, class SV>
+__device__ __forceinline__ void smoother_tile_fused(const SmoothParams<T> &p, const DevModel &mdl, cdouble *cst,
+                                                    SV &sv, const STileRange &tr, int tile, T *s_out)
+{
+    constexpr int D = LY::D;
+    constexpr int AGG = SAggLayout<D>::SIZE;
+    constexpr int INCL = SAggLayout<D>::INCL;
+    constexpr int B = smoother_shear_col<LY>();
+    using SP = Sparsity<LY>;
+    using HL = HandLayout<D>;
+    const int lane = lane_id();
+    const int slot = tr.slot_base + tile;
+    const int64_t chunk_id = (int64_t)slot * PSSGP_WAVE + lane;
+    const int64_t k0 = tr.k_begin + ((int64_t)tile * PSSGP_WAVE + lane) * p.chunk;
+    const int64_t k1 = (k0 + p.chunk < tr.k_end) ? k0 + p.chunk : tr.k_end;
+    const int64_t tile_start = tr.k_begin + (int64_t)tile * PSSGP_WAVE * p.chunk;
+    const int tile_len = PSSGP_WAVE * p.chunk;
+    // a lane's outputs in LDS are chunk + 1 apart: with chunk, a multiple of
+    // 4 as a rule, a write of the wave would go to a few banks only
+    const int row = p.chunk + 1, half = PSSGP_WAVE * row;
+    T *so = s_out + lane * row;
+    if (k0 < k1) {
+        // inputs of the lane's last step, requested first
+        const OptInputs opt(p.mask, nullptr, p.t);
+        const double *hp = p.hand + HL::step(slot, p.chunk, 0, lane);
+        constexpr size_t ST = (size_t)HL::STEP * PSSGP_WAVE;
+        double ph[D], hm, tc = p.t[k1 - 1], tp = p.t[k1 - 1 > tr.k_begin ? k1 - 2 : k1 - 1];
+        T yc = p.y[k1 - 1];
+        bool oc = opt.observed(k1 - 1);
+        const double *hq = hp + (size_t)(k1 - 1 - k0) * ST;
+#pragma unroll
+        for (int i = 0; i < D; i++) ph[i] = __builtin_nontemporal_load(hq + i * PSSGP_WAVE);
+        hm = __builtin_nontemporal_load(hq + D * PSSGP_WAVE);
+        double lam[D], Lam[D][D];
+        {
+            T msT[D], PsT[D][D];
+            gl_load<D, T>(p.inclp + (size_t)slot * INCL, msT, PsT);
+            if (lane < PSSGP_WAVE - 1) {
+                SAgg<D, T> excl;
+                sagg_load<D, T>(lane_rec(p.lanep, slot, AGG, lane + 1), excl, PSSGP_WAVE);
+                sagg_apply<D, T>(excl, msT, PsT, msT, PsT);
+            }
+            double msd[D], Psd[D][D], ms[D], Ps[D][D];
+#pragma unroll
+            for (int i = 0; i < D; i++) {
+                msd[i] = (double)msT[i];
+#pragma unroll
+                for (int j = 0; j < D; j++) Psd[i][j] = (double)PsT[i][j];
+            }
+            from_smoother_coords<D, B, double>(msd, Psd, ms, Ps);
+            const double *bp = p.bound + HL::lane(slot, lane);
+            double C[D][D], rd[D];
+#pragma unroll
+            for (int i = 0; i < D; i++) {
+                ms[i] -= bp[i * PSSGP_WAVE];
+#pragma unroll
+                for (int j = 0; j < i; j++) C[i][j] = bp[(D + sidx<D>(j, i)) * PSSGP_WAVE];
+                rd[i] = bp[(D + sidx<D>(i, i)) * PSSGP_WAVE];
+            }
+            // X = C^-1 P^s, then N = I - C^-1 X^T = C^-1 (P - P^s) C^-T
+            auto forward = [&](double (&x)[D]) {
+#pragma unroll
+                for (int i = 0; i < D; i++) {
+#pragma unroll
+                    for (int q = 0; q < i; q++) x[i] = fma(-C[i][q], x[q], x[i]);
+                    x[i] *= rd[i];
+                }
+            };
+            auto backward = [&](double (&x)[D]) {
+#pragma unroll
+                for (int i = D - 1; i >= 0; i--) {
+#pragma unroll
+                    for (int q = i + 1; q < D; q++) x[i] = fma(-C[q][i], x[q], x[i]);
+                    x[i] *= rd[i];
+                }
+            };
+            // rows of Ps (symmetric) solved as right-hand sides: Lam[j][.] = C^-1 Ps[.][j]
+#pragma unroll
+            for (int j = 0; j < D; j++) {
+#pragma unroll
+                for (int i = 0; i < D; i++) Lam[j][i] = Ps[i][j];
+                forward(Lam[j]);
+            }
+#pragma unroll
+            for (int j = 0; j < D; j++) {
+                double x[D];
+#pragma unroll
+                for (int i = 0; i < D; i++) x[i] = Lam[i][j];
+                forward(x);
+#pragma unroll
+                for (int i = 0; i < D; i++) Ps[i][j] = (i == j ? 1.0 : 0.0) - x[i];
+            }
+#pragma unroll
+            for (int j = 0; j < D; j++) {
+#pragma unroll
+                for (int i = 0; i < D; i++) Lam[j][i] = i <= j ? Ps[i][j] : Ps[j][i];
+                backward(Lam[j]);
+            }
+#pragma unroll
+            for (int j = 0; j < D; j++) {
+                double x[D];
+#pragma unroll
+                for (int i = 0; i < D; i++) x[i] = Lam[i][j];
+                backward(x);
+#pragma unroll
+                for (int i = 0; i < D; i++) Ps[i][j] = x[i];
+            }
+            forward(ms);
+            backward(ms);
+            // a series ends with the lane: nothing after it
+            sv.seek(k1 - 1);
+            const bool end = (k1 >= tr.k_end) || sv.last(k1 - 1);
+#pragma unroll
+            for (int i = 0; i < D; i++) {
+                lam[i] = end ? 0.0 : ms[i];
+#pragma unroll
+                for (int j = i; j < D; j++) {
+                    Lam[i][j] = end ? 0.0 : Ps[i][j];
+                    Lam[j][i] = Lam[i][j];
+                }
+            }
+        }
+        for (int64_t k = k1 - 1;; k--) {
+            // the next step's inputs, one iteration ahead
+            const int64_t kn = k > k0 ? k - 1 : k0;
+            double nph[D];
+            const double *q = k > k0 ? hq - ST : hq;
+            hq = q;
+#pragma unroll
+            for (int i = 0; i < D; i++) nph[i] = __builtin_nontemporal_load(q + i * PSSGP_WAVE);
+            const double nhm = __builtin_nontemporal_load(q + D * PSSGP_WAVE);
+            const double tn = p.t[kn > tr.k_begin ? kn - 1 : kn];
+            const T yn = p.y[kn];
+            const bool on = opt.observed(kn);
+            if constexpr (reload_constants<D>()) PSSGP_RELOAD_CONSTANTS();
+            sv.seek(k);
+            const double R = (double)T(sv.R);
+            // in the coordinates z' = S z (identity for one component) the
+            // observation row is the first unit vector: P h is summed into
+            // its first entry, Lambda' = S^-T Lambda S^-1, lambda' = S^-T lambda
+            if constexpr (B > 0) {
+                ph[0] += ph[B];
+                lam[B] -= lam[0];
+#pragma unroll
+                for (int j = 0; j < D; j++) Lam[B][j] -= Lam[0][j];
+#pragma unroll
+                for (int j = 0; j < D; j++) Lam[j][B] = (j == B) ? Lam[B][B] - Lam[B][0] : Lam[B][j];
+            }
+            const double hph = ph[0];
+            const double S = R + hph;
+            const double w = oc ? rcp64(S) : 0.0;
+            const double v = oc ? (double)yc - hm : 0.0;
+            const double r = oc ? R * w : 1.0;
+            // q = Lambda P h and s = Lambda (I - K h) e_0, whose first factor
+            // 1 - K_0 is r: formed as a difference it would lose log10(S / R)
+            // digits
+            double su[D], phl = 0.0, phq = 0.0, ul = 0.0;
+#pragma unroll
+            for (int i = 0; i < D; i++) {
+                double acc = 0.0;
+#pragma unroll
+                for (int j = 1; j < D; j++) acc = fma(Lam[i][j], ph[j], acc);
+                su[i] = fma(-w, acc, r * Lam[i][0]);
+                phq = fma(fma(Lam[i][0], hph, acc), ph[i], phq);
+                if (i > 0) ul = fma(lam[i], ph[i], ul);
+            }
+            phl = fma(lam[0], hph, ul);
+            // f outputs staged in LDS for coalesced stores
+            so[k - k0] = T(fma(r, phl, fma(hph * w, v, hm)));
+            so[half + (k - k0)] = T(r * fma(-r, phq, hph));
+            if (k == k0) break;
+            {
+                double us = 0.0;
+#pragma unroll
+                for (int i = 1; i < D; i++) {
+                    us = fma(ph[i], su[i], us);
+                    Lam[0][i] = su[i];
+                    Lam[i][0] = su[i];
+                }
+                Lam[0][0] = fma(-w, us, fma(r, su[0], w));
+                lam[0] = fma(w, v - ul, r * lam[0]);
+            }
+            if constexpr (B > 0) {
+                lam[B] += lam[0];
+#pragma unroll
+                for (int j = 0; j < D; j++) Lam[B][j] += Lam[0][j];
+#pragma unroll
+                for (int j = 0; j < D; j++) Lam[j][B] = (j == B) ? Lam[B][B] + Lam[B][0] : Lam[B][j];
+            }
+            // over the transition into step k (F = 0 at a series start)
+            cdouble *cc = cst;
+            if constexpr (reload_constants<D>()) PSSGP_LAUNDER(cc);
+            const bool first = sv.first(k);
+            double F[D][D];
+            if constexpr (sizeof(T) == 8)
+                transition<LY, true>(mdl, cc, sv.sc, first ? 0.0 : tc - tp, first, F);
+            else
+                transition_plain<LY>(mdl, cc, sv.sc, first ? 0.0 : tc - tp, first, F);
+            double X[D][D], nl[D];
+#pragma unroll
+            for (int i = 0; i < D; i++) {
+                double acc = 0.0;
+#pragma unroll
+                for (int q3 = 0; q3 < D; q3++)
+                    if (SP::dl(q3, i)) acc = fma(F[q3][i], lam[q3], acc);
+                nl[i] = acc;
+#pragma unroll
+                for (int j = 0; j < D; j++) {
+                    double x = 0.0;
+#pragma unroll
+                    for (int q3 = 0; q3 < D; q3++)
+                        if (SP::dl(q3, j)) x = fma(Lam[i][q3], F[q3][j], x);
+                    X[i][j] = x;
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < D; i++) {
+                lam[i] = nl[i];
+#pragma unroll
+                for (int j = i; j < D; j++) {
+                    double x = 0.0;
+#pragma unroll
+                    for (int q3 = 0; q3 < D; q3++)
+                        if (SP::dl(q3, i)) x = fma(F[q3][i], X[q3][j], x);
+                    Lam[i][j] = x;
+                    Lam[j][i] = x;
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < D; i++) ph[i] = nph[i];
+            hm = nhm;
+            tc = tp;
+            tp = tn;
+            yc = yn;
+            oc = on;
+        }
+    }
+    __syncthreads();
+    // step i of the tile is step j of lane l, i = l chunk + j
+    const int dl = PSSGP_WAVE / p.chunk, dj = PSSGP_WAVE % p.chunk;
+    int l = lane / p.chunk, j = lane % p.chunk;
+    for (int i = lane; i < tile_len; i += PSSGP_WAVE) {
+        const int64_t k = tile_start + i;
+        if (k < tr.k_end) {
+            p.f_mean[k] = s_out[l * row + j];
+            p.f_var[k] = s_out[half + l * row + j];
+        }
+        l += dl;
+        j += dj;
+        if (j >= p.chunk) {
+            j -= p.chunk;
+            l++;
+        }
+    }
+}
+
+template <class LY, typename T>
 __global__ __launch_bounds__(PSSGP_WAVE, (smoother_waves<LY::D, T>())) void smoother_fold_kernel(SmoothParams<T> p,
                                                                                            DevModel mdl_arg)
 {
@@ -224,10 +452,10 @@ __global__ __launch_bounds__(PSSGP_WAVE, (smoother_waves<LY::D, T>())) void smoo
     OneSeries sv;
     sv.init(mdl, p.n);
     STileRange tr{0, p.n, p.ntiles, 0};
-    smoother_tile_fold<LY, T, ELEMS, OneSeries>(p, mdl, (cdouble *)p.cst, sv, tr, (int)blockIdx.x);
+    smoother_tile_fold<LY, T, OneSeries>(p, mdl, (cdouble *)p.cst, sv, tr, (int)blockIdx.x);
 }
 
-template <class LY, typename T, bool FULL, bool ELEMS>
+template <class LY, typename T, bool FULL>
 __global__ __launch_bounds__(PSSGP_WAVE, (smoother_waves<LY::D, T>())) void smoother_finish_kernel(SmoothParams<T> p,
                                                                                              DevModel mdl_arg)
 {
@@ -237,8 +465,22 @@ __global__ __launch_bounds__(PSSGP_WAVE, (smoother_waves<LY::D, T>())) void smoo
     sv.init(mdl, p.n);
     STileRange tr{0, p.n, p.ntiles, 0};
     extern __shared__ __align__(16) unsigned char pssgp_dyn_smem[];
-    smoother_tile_finish<LY, T, FULL, ELEMS, OneSeries>(p, mdl, (cdouble *)p.cst, sv, tr, (int)blockIdx.x,
-                                                        reinterpret_cast<T *>(pssgp_dyn_smem));
+    smoother_tile_finish<LY, T, FULL, OneSeries>(p, mdl, (cdouble *)p.cst, sv, tr, (int)blockIdx.x,
+                                                 reinterpret_cast<T *>(pssgp_dyn_smem));
+}
+
+template <class LY, typename T>
+__global__ __launch_bounds__(PSSGP_WAVE, (fused_waves<LY::D>())) void smoother_fused_kernel(SmoothParams<T> p,
+                                                                                          DevModel mdl_arg)
+{
+    __shared__ DevModel mdl;
+    model_to_lds(mdl_arg, mdl);
+    OneSeries sv;
+    sv.init(mdl, p.n);
+    STileRange tr{0, p.n, p.ntiles, 0};
+    extern __shared__ __align__(16) unsigned char pssgp_dyn_smem[];
+    smoother_tile_fused<LY, T, OneSeries>(p, mdl, (cdouble *)p.cst, sv, tr, (int)blockIdx.x,
+                                          reinterpret_cast<T *>(pssgp_dyn_smem));
 }
 
 template <class LY, typename T>
@@ -260,24 +502,22 @@ int launch_smoother_t(const DevModel &mdl, const SmoothLaunch &a, hipStream_t s)
     p.aggp = (T *)a.ws.aggp;
     p.lanep = (T *)a.ws.lanep;
     p.cst = a.ws.cst;
-    p.slane = (const T *)a.slane;
+    p.y = (const T *)a.y;
+    p.mask = a.mask;
+    p.hand = a.hand;
+    p.bound = a.bound;
     const dim3 grid(a.ntiles), block(PSSGP_WAVE);
     pass_event(a.ev, 0, s);
-    if (a.tiled && lane_aggregate_handover<LY::D>()) {
+    if (a.hand) {
         // the filter's finish pass of the same call did this pass (lane
         // records at slane, tile aggregates at aggp)
-        p.lanep = const_cast<T *>(p.slane);
-    } else if (a.tiled) {
-        // elements from the filter of the same call: no transition needed
-        hipLaunchKernelGGL((smoother_fold_kernel<LY, T, true>), grid, block, 0, s, p, mdl);
+        p.lanep = (T *)a.slane;
     } else {
         launch_consts<LY, T>(mdl, a.ws.cst, s);
-        hipLaunchKernelGGL((smoother_fold_kernel<LY, T, false>), grid, block, 0, s, p, mdl);
+        hipLaunchKernelGGL((smoother_fold_kernel<LY, T>), grid, block, 0, s, p, mdl);
     }
-    if constexpr (smoother_by_rows<LY::D, T>()) {
-        if (!(a.tiled && lane_aggregate_handover<LY::D>()))
-            hipLaunchKernelGGL((rows_lane_scan<LY::D, T>), grid, dim3(PSSGP_WAVE * LY::D), 0, s, p.lanep, p.aggp, 0);
-    }
+    if constexpr (smoother_by_rows<LY::D, T>())
+        hipLaunchKernelGGL((rows_lane_scan<LY::D, T>), grid, dim3(PSSGP_WAVE * LY::D), 0, s, p.lanep, p.aggp, 0);
     int rc = (int)hipGetLastError();
     if (rc) return rc;
     pass_event(a.ev, 1, s);
@@ -288,13 +528,13 @@ int launch_smoother_t(const DevModel &mdl, const SmoothLaunch &a, hipStream_t s)
                                                          a.ws.gcarry, s);
     if (rc) return rc;
     pass_event(a.ev, 2, s);
-    const size_t smem = (size_t)2 * PSSGP_WAVE * a.chunk * sizeof(T);
-    if (a.tiled)
-        hipLaunchKernelGGL((smoother_finish_kernel<LY, T, false, true>), grid, block, smem, s, p, mdl);
+    const size_t smem = (size_t)2 * PSSGP_WAVE * (a.hand ? a.chunk + 1 : a.chunk) * sizeof(T);
+    if (a.hand)
+        hipLaunchKernelGGL((smoother_fused_kernel<LY, T>), grid, block, smem, s, p, mdl);
     else if (a.ms && a.Ps)
-        hipLaunchKernelGGL((smoother_finish_kernel<LY, T, true, false>), grid, block, smem, s, p, mdl);
+        hipLaunchKernelGGL((smoother_finish_kernel<LY, T, true>), grid, block, smem, s, p, mdl);
     else
-        hipLaunchKernelGGL((smoother_finish_kernel<LY, T, false, false>), grid, block, smem, s, p, mdl);
+        hipLaunchKernelGGL((smoother_finish_kernel<LY, T, false>), grid, block, smem, s, p, mdl);
     rc = (int)hipGetLastError();
     pass_event(a.ev, 3, s);
     return rc;
