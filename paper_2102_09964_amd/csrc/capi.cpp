@@ -510,9 +510,9 @@ constexpr int kQPDefaultChunk = 256;
 constexpr int kQPMaxChunk = 4096;
 
 struct QPPlan {
-    int chunk = kQPDefaultChunk, G = 0;
+    int chunk = kQPDefaultChunk, G = 0, sub = kQPDefaultChunk, nsub = 1;
     size_t tsize = 4;
-    size_t off_f[2] = {0, 0}, off_s[2] = {0, 0}, off_elem = 0, off_part = 0, total = 0;
+    size_t off_f[2] = {0, 0}, off_s[2] = {0, 0}, off_elem = 0, off_hand = 0, off_bound = 0, off_part = 0, total = 0;
 };
 
 int qp_check_opts(const pssgp_options *opts)
@@ -529,9 +529,21 @@ QPPlan qp_plan(int d, int64_t n, pssgp_dtype dtype, bool elems, const pssgp_opti
 {
     QPPlan p;
     p.chunk = (opts && opts->chunk) ? (int)opts->chunk : kQPDefaultChunk;
-    p.tsize = dtype == PSSGP_F64 ? 8 : 4;
+    p.tsize = (dtype == PSSGP_F64) ? 8 : 4;
     p.G = (int)((n + p.chunk - 1) / p.chunk);
+    // sub-chunks of the smoother: as many teams as put one wave of four on
+    // every SIMD, of 16 steps at least (each costs the filter about two and a
+    // half steps for its element)
+    const int most = (p.chunk + 15) / 16;
+    p.nsub = 4096 / (p.G > 0 ? p.G : 1);
+    p.nsub = p.nsub < 1 ? 1 : (p.nsub > most ? most : p.nsub);
+    p.sub = (p.chunk + p.nsub - 1) / p.nsub;
+    p.nsub = (p.chunk + p.sub - 1) / p.sub;
+    // sized for the most sub-chunks of any shorter series, so that a workspace
+    // for n serves those too
     const size_t G = (size_t)(p.G > 0 ? p.G : 1);
+    size_t ns = G > 4096 ? G : 4096;
+    ns = ns < G * (size_t)most ? ns : G * (size_t)most;
     size_t off = ctl_bytes();
     auto take = [&](size_t bytes) {
         size_t o = off;
@@ -542,9 +554,11 @@ QPPlan qp_plan(int d, int64_t n, pssgp_dtype dtype, bool elems, const pssgp_opti
     p.off_f[0] = take(G * nf_f * p.tsize);
     p.off_f[1] = take(G * nf_f * p.tsize);
     if (elems) {
+        p.off_elem = take(ns * nf_s * p.tsize);
         p.off_s[0] = take(G * nf_s * p.tsize);
         p.off_s[1] = take(G * nf_s * p.tsize);
-        p.off_elem = take((size_t)(n > 0 ? n : 1) * nf_s * p.tsize);
+        p.off_hand = take((size_t)(n > 0 ? n : 1) * (d + 2) * sizeof(double));
+        p.off_bound = take(ns * d * (d + 2) * sizeof(double));
     }
     p.off_part = take(G * sizeof(double));
     p.total = off;
@@ -601,6 +615,10 @@ int qp_run(const pssgp_model *model, const double *t, const void *y, const uint8
     q.sagg[0] = elems ? b + p.off_s[0] : nullptr;
     q.sagg[1] = elems ? b + p.off_s[1] : nullptr;
     q.elem = elems ? b + p.off_elem : nullptr;
+    q.sub = p.sub;
+    q.nsub = p.nsub;
+    q.hand = elems ? (double *)(b + p.off_hand) : nullptr;
+    q.bound = elems ? (double *)(b + p.off_bound) : nullptr;
     q.partials = (double *)(b + p.off_part);
     q.loglik = loglik;
     q.f_mean = f_mean;

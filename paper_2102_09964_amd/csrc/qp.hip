@@ -12,14 +12,24 @@
 //                   A = 0, so the prefix of chunk g - 1 holds the filter
 //                   moments entering chunk g
 //   filter finish   each team re-runs its chunk from those moments as a
-//                   Kalman filter in FP64, sums the log-likelihood terms and
-//                   writes the smoother element of every step
+//                   Kalman filter in FP64 and sums the log-likelihood terms;
+//                   next to it runs the fixed-point smoother of the state
+//                   before each sub-chunk of steps, which gives one smoother
+//                   element per sub-chunk (qp_element), and P h, h m of every
+//                   step go to the smoother
 //   loglik          one workgroup sums the per-chunk partials in chunk order
-//   smoother fold   each team composes its chunk's elements right to left
-//   smoother scan   suffix scan of the chunk aggregates (Hillis-Steele)
-//   smoother finish each team runs the RTS recursion backwards from the
-//                   smoothed moments after its chunk and writes f_mean,
-//                   f_var
+//   smoother join   each team joins the elements of its chunk's sub-chunks
+//   smoother scan   suffix scan of the chunks' elements (Hillis-Steele)
+//   smoother finish each team runs the recursion of Bryson and Frazier
+//                   backwards over a sub-chunk, as the one-lane scans do
+//                   (smoother_tile_fused), and writes f_mean, f_var
+// What bounds these passes at the default chunk is the chain of steps of one
+// team (256 steps at 2^18 are one wave on every fourth SIMD), so the smoother,
+// which needs no further filter aggregate for it, works on sub-chunks.
+// 262 107 steps at 16 states (FP32, chunk 256, sub-chunks of 64 steps):
+// fold 774, ten filter levels of 67, finish 1665, join 16, ten smoother levels
+// of 37, smoother finish 193 us, the call 3.65 ms; with a smoother element per
+// step, folded and run again over the chunks, the call took 8.12 ms.
 // Every team of a wave runs the same number of iterations (steps past a
 // chunk's end are identity steps), so control flow is uniform.
 #include <hip/hip_runtime.h>
@@ -48,8 +58,12 @@ struct QPArgs {
     int chunk;
     int G;          // chunks
     T *fagg[2];     // filter chunk aggregates / prefixes (ping-pong)
-    T *sagg[2];     // smoother chunk aggregates / suffixes (ping-pong)
-    T *elem;        // smoother elements of every step (rows of 2 D + 1)
+    int sub;        // steps per sub-chunk of the smoother
+    int nsub;       // sub-chunks per chunk
+    T *elem;        // smoother elements of the sub-chunks
+    T *sagg[2];     // smoother elements of the chunks / suffixes (ping-pong)
+    double *hand;   // per step: P h (D values), h m, one unused
+    double *bound;  // per sub-chunk, by rows: Cholesky factor of its end covariance, its diagonal's reciprocal, end mean
     double *partials;
     double *loglik;
     T *f_mean;
@@ -158,11 +172,10 @@ __global__ __launch_bounds__(64) void qp_filter_level(const T *in, T *out, int G
 }
 
 // Filter finish: moments entering the chunk from the prefix of chunk g - 1,
-// then a Kalman filter in FP64 over the chunk. ELEMS: write the smoother
-// element of every step (iteration it builds the element of step k - 1
-// from the prediction of step k; one extra iteration predicts past the
-// chunk for the element of its last step).
-template <class L, typename T, bool ELEMS>
+// then a Kalman filter in FP64 over the chunk. SMOOTH: the fixed-point smoother
+// of the state before every sub-chunk (G, m0, P0 as in lane_smoother_element)
+// and the handover.
+template <class L, typename T, bool SMOOTH>
 __global__ __launch_bounds__(64) void qp_filter_finish(QPArgs<T> a, QPDev m, const T *prefix)
 {
     extern __shared__ __align__(16) double qp_lds[];
@@ -186,43 +199,40 @@ __global__ __launch_bounds__(64) void qp_filter_finish(QPArgs<T> a, QPDev m, con
     uint32_t bad = 0;
     double ll = 0.0;
     constexpr int NFS = D * qsagg_fields<L>();
+    double m0[R], P0[R][D], G[R][D];
+    const double h0 = m.h[0];
     QPInputs<T> in;
     in.start(a, k0);
-    for (int it = 0; it <= a.chunk; it++) {
+    for (int it = 0; it < a.chunk; it++) {
+        if constexpr (SMOOTH) {
+            if (it % a.sub == 0) {
+#pragma unroll
+                for (int s = 0; s < R; s++) {
+                    m0[s] = mf[s];
+#pragma unroll
+                    for (int j = 0; j < D; j++) P0[s][j] = G[s][j] = P[s][j];
+                }
+            }
+        }
         const int64_t k = k0 + it;
         const bool real = k < k1;
-        const bool next = ELEMS && k == k1 && k1 > k0;  // element of the chunk's last step
-        const bool end = next && k1 >= a.n;             // past the series end: prior transition
         double tn;
         T yn;
         uint8_t mn;
         in.fetch(k, tn, yn, mn);
-        const double dt = (real || (next && !end)) ? in.dt(k) : 0.0;
+        const double dt = real ? in.dt(k) : 0.0;
         if (real && !(dt >= 0.0)) bad |= (dt < 0.0) ? PSSGP_STATUS_UNSORTED : PSSGP_STATUS_NONFINITE;
         const bool obs = real && in.observed();
         const double yk = obs ? (double)in.yc : 0.0;
         in.advance(tn, yn, mn);
         QPStep<L::J> st;
-        qp_step<L::J>(m, dt, (real && k == 0) || end, !(real || next), st);
+        qp_step<L::J>(m, dt, real && k == 0, !real, st);
         // prediction in FP64: Y = F P, mp = F m, Pp = F P F^T + Q
         double Y[R][D], mp[R], Pp[R][D];
         qp_left_F<L, double, double>(st, P, Y, true);
         qp_left_F_vec<L, double, double>(st, mf, mp);
         qp_right_Ft_plus_Q<L, double>(st, Y, Pp);
-        if constexpr (ELEMS) {
-            // every team of the wave builds an element (the LDS transposes
-            // need uniform control flow); only those of steps k0..k1-1 are
-            // kept
-            const bool keep = k > k0 && (real || next);
-            QSAgg<L, T> e;
-            uint32_t ebad = 0;
-            qp_element<L, T>(m, mf, P, Y, mp, Pp, e, tbuf, ebad);
-            // the next step's loads are waited for before the element stores
-            // (the wait counter is in order)
-            asm volatile("" ::"v"(tn), "v"(yn), "v"((int)mn));
-            qsagg_store<L, T, T>(a.elem + (size_t)(keep ? k - 1 : 0) * NFS, e, keep);
-            bad |= keep ? ebad : 0u;
-        }
+        if constexpr (SMOOTH) qp_left_F<L, double, double>(st, G, G, true);
         // conditioning on y_k in FP64
         double c[D];
         qp_obs_combo<L, double>(m, Pp, c);
@@ -240,14 +250,83 @@ __global__ __launch_bounds__(64) void qp_filter_finish(QPArgs<T> a, QPDev m, con
         double K[D];
 #pragma unroll
         for (int j = 0; j < D; j++) K[j] = c[j] * w;
+        if constexpr (SMOOTH) {
+            // the next step's loads are waited for before the stores (the wait
+            // counter is in order)
+            asm volatile("" ::"v"(tn), "v"(yn), "v"((int)mn));
+            double wh[D];
+            qp_obs_combo<L, double>(m, G, wh);  // G^T h
+            double *hp = a.hand + (size_t)(real ? k : 0) * (D + 2);
+#pragma unroll
+            for (int s = 0; s < R; s++) {
+                const int row = team_lane() + QP_TEAM * s;
+                const double cr = qp_pick<D>(c, row), Kr = cr * w, whr = qp_pick<D>(wh, row);
+                if (real && row < D) hp[row] = cr;
+                m0[s] = fma(whr * w, v, m0[s]);
+#pragma unroll
+                for (int j = 0; j < D; j++) {
+                    P0[s][j] = fma(-(whr * w), wh[j], P0[s][j]);
+                    G[s][j] = fma(-Kr, wh[j], G[s][j]);
+                }
+            }
+            if (real && team_lane() == 0) hp[D] = hm;
+            // row 0 of G from h G = r G^T h, r = R / S: as a difference it
+            // would lose log10(S / R) digits
+            const double rs = obs ? m.R * w : 1.0;
+            double g0[D];
+#pragma unroll
+            for (int j = 0; j < D; j++) g0[j] = rs * wh[j];
+            sfor<1, L::NO>([&](auto qc) {
+                constexpr int r = L::obs_row(decltype(qc)::value);
+                const double hr = m.h[r];
+#pragma unroll
+                for (int j = 0; j < D; j++) g0[j] = fma(-hr, team_get<r % QP_TEAM>(G[r / QP_TEAM][j]), g0[j]);
+            });
+#pragma unroll
+            for (int j = 0; j < D; j++) G[0][j] = (obs && team_lane() == 0) ? g0[j] / h0 : G[0][j];
+        }
         if (real) {
 #pragma unroll
             for (int s = 0; s < R; s++) {
                 const int row = team_lane() + QP_TEAM * s;
-                const double cr = qp_pick<D>(c, row), Kr = qp_pick<D>(K, row);
+                const double cr = qp_pick<D>(c, row), Kr = cr * w;
                 mf[s] = fma(Kr, v, mp[s]);
 #pragma unroll
                 for (int j = 0; j < D; j++) P[s][j] = fma(S * Kr, K[j], fma(-cr, K[j], fma(-Kr, c[j], Pp[s][j])));
+            }
+        }
+        if constexpr (SMOOTH) {
+            if ((it + 1) % a.sub == 0 || it + 1 == a.chunk) {
+                // the sub-chunk's element (every team of the wave builds one:
+                // the LDS transposes need uniform control flow) and end moments
+                const int q = it / a.sub;
+                const int64_t s0 = k0 + (int64_t)q * a.sub;
+                const bool any = s0 < k1, end = k + 1 >= a.n;
+                const size_t es = (size_t)g * a.nsub + q;
+                if (end) {
+#pragma unroll
+                    for (int s = 0; s < R; s++)
+#pragma unroll
+                        for (int j = 0; j < D; j++) G[s][j] = 0.0;
+                }
+                QSAgg<L, T> e;
+                double Cl[R][D], rd[D];
+                uint32_t ebad = 0;
+                qp_element<L, T>(m, m0, P0, G, mf, P, Cl, rd, e, tbuf, ebad);
+                bad |= any ? ebad : 0u;
+                if (!any) qsagg_identity<L, T>(e);
+                qsagg_store<L, T, T>(a.elem + es * NFS, e, g < a.G);
+                double *bp = a.bound + es * (size_t)(D * (D + 2));
+#pragma unroll
+                for (int s = 0; s < R; s++) {
+                    const int row = team_lane() + QP_TEAM * s;
+                    if (any && row < D) {
+#pragma unroll
+                        for (int j = 0; j < D; j++) bp[row * (D + 2) + j] = Cl[s][j];
+                        bp[row * (D + 2) + D] = qp_pick<D>(rd, row);
+                        bp[row * (D + 2) + D + 1] = mf[s];
+                    }
+                }
             }
         }
     }
@@ -270,23 +349,24 @@ __global__ __launch_bounds__(256) void qp_loglik_sum(const double *partials, int
     }
 }
 
+// The smoother element of each chunk from its sub-chunks' (the scan's levels
+// then run over the chunks: over the sub-chunks they took 100 instead of 41 us
+// each at 2^18 steps)
 template <class L, typename T>
-__global__ __launch_bounds__(64) void qp_smoother_fold(QPArgs<T> a)
+__global__ __launch_bounds__(64) void qp_smoother_join(QPArgs<T> a)
 {
     const int g = team_id();
-    const int64_t k0 = (int64_t)g * a.chunk;
-    const int64_t k1 = min(k0 + (int64_t)a.chunk, a.n);
     constexpr int NFS = L::D * qsagg_fields<L>();
+    const bool on = g < a.G;
+    const T *base = a.elem + (size_t)(on ? g : 0) * a.nsub * NFS;
     QSAgg<L, T> acc;
-    qsagg_identity<L, T>(acc);
-    for (int it = 0; it < a.chunk; it++) {
-        const int64_t k = k0 + a.chunk - 1 - it;
-        const bool real = k < k1;
+    qsagg_load<L, T, T>(base + (size_t)(a.nsub - 1) * NFS, acc, on);
+    for (int q = a.nsub - 2; q >= 0; q--) {
         QSAgg<L, T> e;
-        qsagg_load<L, T, T>(a.elem + (size_t)(real ? k : 0) * NFS, e, real);
+        qsagg_load<L, T, T>(base + (size_t)q * NFS, e, on);
         qsagg_combine<L, T>(e, acc, acc);
     }
-    qsagg_store<L, T, T>(a.sagg[0] + (size_t)g * NFS, acc, g < a.G);
+    qsagg_store<L, T, T>(a.sagg[0] + (size_t)g * NFS, acc, on);
 }
 
 // one level of the smoother suffix: out[g] = in[g] (x) in[g + o]
@@ -303,41 +383,207 @@ __global__ __launch_bounds__(64) void qp_smoother_level(const T *in, T *out, int
     qsagg_store<L, T, T>(out + (size_t)g * NFS, x, g < G);
 }
 
-// Smoother finish: smoothed moments after the chunk from the suffix of
-// chunk g + 1 (none after the last chunk: the last element has E = 0),
-// then the RTS recursion backwards; f = h_0 z'_0 in the smoother's
-// coordinates.
+// Smoother finish of one sub-chunk: the smoothed moments of its last step from
+// the elements after it (none after the series' end), then the
+// recursion of (lambda, Lambda) backwards (smoother_tile_fused has the
+// formulas); row i of Lambda on team lane i, in FP64. In the coordinates
+// z' = S z the observation row is h_0 times the first unit vector.
 template <class L, typename T>
 __global__ __launch_bounds__(64) void qp_smoother_finish(QPArgs<T> a, QPDev m, const T *suffix)
 {
+    extern __shared__ __align__(16) double qp_lds[];
     constexpr int D = L::D, R = L::RPL;
-    const int g = team_id();
-    const int64_t k0 = (int64_t)g * a.chunk;
-    const int64_t k1 = min(k0 + (int64_t)a.chunk, a.n);
+    static_assert(R == 1, "one row per lane");
+    double *tbuf = qp_lds + (threadIdx.x >> 4) * (D * D);
+    const int es = team_id(), ns = a.G * a.nsub;
+    const int g = es / a.nsub, q = es - g * a.nsub;
+    const int64_t kc = (int64_t)g * a.chunk;
+    const int64_t k0 = kc + (int64_t)q * a.sub;
+    const int64_t k1 = min(min(k0 + (int64_t)a.sub, kc + (int64_t)a.chunk), a.n);
+    const bool any = es < ns && k0 < k1;
+    const int row = team_lane();
     constexpr int NFS = D * qsagg_fields<L>();
-    T ms[R], Ps[R][D];
-    {
-        QSAgg<L, T> suf;
-        const bool has = g + 1 < a.G;
-        qsagg_load<L, T, T>(suffix + (size_t)(has ? g + 1 : 0) * NFS, suf, has);
-#pragma unroll
-        for (int s = 0; s < R; s++) {
-            ms[s] = has ? suf.g[s] : T(0);
-#pragma unroll
-            for (int j = 0; j < D; j++) Ps[s][j] = has ? suf.L_[s][j] : T(0);
-        }
-    }
     const double h0 = m.h[0];
-    for (int it = 0; it < a.chunk; it++) {
-        const int64_t k = k0 + a.chunk - 1 - it;
-        const bool real = k < k1;
-        QSAgg<L, T> e;
-        qsagg_load<L, T, T>(a.elem + (size_t)(real ? k : 0) * NFS, e, real);
-        qsagg_apply<L, T>(e, ms, Ps);
-        if (real && team_lane() == 0) {
-            a.f_mean[k] = T(h0 * (double)ms[0]);
-            a.f_var[k] = T(h0 * h0 * (double)Ps[0][0]);
+    double u[D], ur = 0.0;  // shear S = I + e_0 u^T (u: observed rows other than 0)
+#pragma unroll
+    for (int j = 0; j < D; j++) u[j] = 0.0;
+    sfor<1, L::NO>([&](auto qc) {
+        constexpr int r = L::obs_row(decltype(qc)::value);
+        u[r] = m.u[r];
+    });
+    ur = qp_pick<D>(u, row);
+    double lam[R], Lam[R][D];
+    {
+        const bool has = any && k1 < a.n;
+        double ms[R], Ps[R][D];
+        {
+            // the suffix after the chunk, then the chunk's later sub-chunks
+            // (every team of the wave runs the same number of them)
+            const bool nxt = any && g + 1 < a.G;
+            QSAgg<L, T> suf;
+            qsagg_load<L, T, T>(suffix + (size_t)(nxt ? g + 1 : 0) * NFS, suf, nxt);
+            T gm[R], Lm[R][D];
+            gm[0] = nxt ? suf.g[0] : T(0);
+#pragma unroll
+            for (int j = 0; j < D; j++) Lm[0][j] = nxt ? suf.L_[0][j] : T(0);
+            for (int i = a.nsub - 1; i >= 1; i--) {
+                const bool use = any && i > q;
+                qsagg_load<L, T, T>(a.elem + (size_t)(use ? g * a.nsub + i : 0) * NFS, suf, use);
+                T g2[R], L2[R][D];
+                g2[0] = gm[0];
+#pragma unroll
+                for (int j = 0; j < D; j++) L2[0][j] = Lm[0][j];
+                qsagg_apply<L, T>(suf, g2, L2);
+                gm[0] = use ? g2[0] : gm[0];
+#pragma unroll
+                for (int j = 0; j < D; j++) Lm[0][j] = use ? L2[0][j] : Lm[0][j];
+            }
+            ms[0] = has ? (double)gm[0] : 0.0;
+#pragma unroll
+            for (int j = 0; j < D; j++) Ps[0][j] = has ? (double)Lm[0][j] : 0.0;
         }
+        // back to the filter's coordinates: m = S^-1 m', P = S^-1 P' S^-T
+        {
+            double r0[D], rm = 0.0;
+#pragma unroll
+            for (int j = 0; j < D; j++) r0[j] = 0.0;
+            sfor<1, L::NO>([&](auto qc) {
+                constexpr int r = L::obs_row(decltype(qc)::value);
+#pragma unroll
+                for (int j = 0; j < D; j++) r0[j] = fma(u[r], team_get<r>(Ps[0][j]), r0[j]);
+                rm = fma(u[r], team_get<r>(ms[0]), rm);
+            });
+            ms[0] -= row == 0 ? rm : 0.0;
+            double c0 = 0.0;
+#pragma unroll
+            for (int j = 0; j < D; j++) {
+                Ps[0][j] -= row == 0 ? r0[j] : 0.0;
+                c0 = fma(u[j], Ps[0][j], c0);
+            }
+            Ps[0][0] -= c0;
+        }
+        const double *bp = a.bound + (size_t)(any ? es : 0) * (D * (D + 2));
+        double Cl[R][D], Ct[R][D], rdr[R], rd[D];
+        const bool ok = any && row < D;
+#pragma unroll
+        for (int j = 0; j < D; j++) Cl[0][j] = ok ? bp[row * (D + 2) + j] : (row == j ? 1.0 : 0.0);
+        rdr[0] = ok ? bp[row * (D + 2) + D] : 1.0;
+        ms[0] -= ok ? bp[row * (D + 2) + D + 1] : 0.0;
+        qp_gather<L, double, double>(rdr, rd);
+        qp_transpose<L, double>(Cl, Ct, tbuf);
+        // N = I - C^-1 P^s C^-T, Lambda = C^-T N C^-1, lambda = P^-1 (m^s - m)
+        qp_forward<L>(Cl, rd, Ps);
+        qp_transpose<L, double>(Ps, Ps, tbuf);
+        qp_forward<L>(Cl, rd, Ps);
+#pragma unroll
+        for (int j = 0; j < D; j++) Ps[0][j] = (row == j ? 1.0 : 0.0) - Ps[0][j];
+        qp_backward<L>(Ct, rd, Ps);
+        qp_transpose<L, double>(Ps, Ps, tbuf);
+        qp_backward<L>(Ct, rd, Ps);
+        qp_symmetrize<L, double>(Ps, tbuf);
+        sfor<0, D>([&](auto kk) {
+            constexpr int k = decltype(kk)::value;
+            ms[0] = row == k ? ms[0] * rd[k] : ms[0];
+            const double x = team_get<k>(ms[0]);
+            ms[0] = fma(-(row > k ? Cl[0][k] : 0.0), x, ms[0]);
+        });
+        sfor<0, D>([&](auto kk) {
+            constexpr int k = D - 1 - decltype(kk)::value;
+            ms[0] = row == k ? ms[0] * rd[k] : ms[0];
+            const double x = team_get<k>(ms[0]);
+            ms[0] = fma(-(row < k ? Ct[0][k] : 0.0), x, ms[0]);
+        });
+        lam[0] = has && row < D ? ms[0] : 0.0;
+#pragma unroll
+        for (int j = 0; j < D; j++) Lam[0][j] = has && row < D ? Ps[0][j] : 0.0;
+    }
+    // inputs of a step (clamped into the series): P h and h m, the times of
+    // the step and of the one before it, its observation and mask
+    struct In {
+        double ph[D], hm, tc, tp;
+        T y;
+        uint8_t mk;
+    };
+    const uint8_t *mk = a.mask ? a.mask : (const uint8_t *)a.t;
+    auto fetch = [&](int64_t k, In &x) {
+        const int64_t c = k < 0 ? 0 : (k < a.n ? k : a.n - 1);
+        const double *hp = a.hand + (size_t)c * (D + 2);
+#pragma unroll
+        for (int j = 0; j < D; j++) x.ph[j] = hp[j];
+        x.hm = hp[D];
+        x.tc = a.t[c];
+        x.tp = a.t[c > 0 ? c - 1 : 0];
+        x.y = a.y[c];
+        x.mk = mk[c];
+    };
+    In x, nx;
+    fetch(k0 + a.sub - 1, x);
+    for (int it = 0; it < a.sub; it++) {
+        const int64_t k = k0 + a.sub - 1 - it;
+        const bool real = any && k < k1;
+        fetch(k - 1, nx);
+        const bool obs = real && (!a.mask || x.mk != 0);
+        // Lambda' = S^-T Lambda S^-1, lambda' = S^-T lambda, P h in z'
+        {
+            double l0[D];
+            qp_row<L, 0>(Lam, l0);
+            const double lm0 = team_get<0>(lam[0]);
+            lam[0] = fma(-ur, lm0, lam[0]);
+#pragma unroll
+            for (int j = 0; j < D; j++) Lam[0][j] = fma(-ur, l0[j], Lam[0][j]);
+            sfor<1, L::NO>([&](auto qc) {
+                constexpr int r = L::obs_row(decltype(qc)::value);
+                Lam[0][r] = fma(-u[r], Lam[0][0], Lam[0][r]);
+                x.ph[0] = fma(u[r], x.ph[r], x.ph[0]);
+            });
+        }
+        const double hph = h0 * x.ph[0], S = m.R + hph;
+        const double w = obs ? 1.0 / S : 0.0;
+        const double v = obs ? (double)x.y - x.hm : 0.0;
+        const double r = obs ? m.R * w : 1.0;
+        const double hw = h0 * w;
+        double tt = 0.0;
+#pragma unroll
+        for (int j = 1; j < D; j++) tt = fma(Lam[0][j], x.ph[j], tt);
+        const double phr = qp_pick<D>(x.ph, row);  // 0 on the lanes past D
+        const double sr = fma(-hw, tt, r * Lam[0][0]);
+        const double phq = team_sum(fma(Lam[0][0], x.ph[0], tt) * phr);
+        const double rest = row == 0 ? 0.0 : phr;
+        const double us = team_sum(rest * sr), ul = team_sum(rest * lam[0]);
+        const double lam0 = team_get<0>(lam[0]), s0 = team_get<0>(sr);
+        const double phl = fma(x.ph[0], lam0, ul);
+        if (real && row == 0) {
+            a.f_mean[k] = T(fma(r, phl, fma(hph * w, v, x.hm)));
+            a.f_var[k] = T(r * fma(-r, phq, hph));
+        }
+        // the observation's update; for a step past the end it is the identity
+        {
+            const double l00 = fma(-hw, us, fma(r, s0, h0 * hw));
+            double col[R], l0[D];
+            col[0] = row == 0 ? l00 : sr;
+            qp_gather<L, double, double>(col, l0);  // row 0 of Lambda'
+#pragma unroll
+            for (int j = 0; j < D; j++) Lam[0][j] = row == 0 ? l0[j] : Lam[0][j];
+            Lam[0][0] = col[0];
+            const double lm0 = fma(hw, v - ul, r * lam0);
+            lam[0] = row == 0 ? lm0 : lam[0];
+            // Lambda = S^T Lambda' S, lambda = S^T lambda'
+            lam[0] = fma(ur, lm0, lam[0]);
+#pragma unroll
+            for (int j = 0; j < D; j++) Lam[0][j] = fma(ur, l0[j], Lam[0][j]);
+            sfor<1, L::NO>([&](auto qc) {
+                constexpr int rr = L::obs_row(decltype(qc)::value);
+                Lam[0][rr] = fma(u[rr], Lam[0][0], Lam[0][rr]);
+            });
+        }
+        // over the transition into the step (none past the end)
+        if (it + 1 < a.sub) {
+            QPStep<L::J> st;
+            qp_step<L::J>(m, real && k > 0 ? x.tc - x.tp : 0.0, real && k == 0, !real, st);
+            qp_right_F<L>(st, Lam, Lam);
+            qp_left_Ft<L>(st, Lam, lam);
+        }
+        x = nx;
     }
 }
 
@@ -353,9 +599,13 @@ QPArgs<T> qp_args(const QPLaunch &q)
     a.G = q.G;
     a.fagg[0] = (T *)q.fagg[0];
     a.fagg[1] = (T *)q.fagg[1];
+    a.sub = q.sub;
+    a.nsub = q.nsub;
+    a.elem = (T *)q.elem;
     a.sagg[0] = (T *)q.sagg[0];
     a.sagg[1] = (T *)q.sagg[1];
-    a.elem = (T *)q.elem;
+    a.hand = q.hand;
+    a.bound = q.bound;
     a.partials = q.partials;
     a.loglik = q.loglik;
     a.f_mean = (T *)q.f_mean;
@@ -382,16 +632,16 @@ int qp_launch_t(const QPDev &m, const QPLaunch &q, hipStream_t s)
         src ^= 1;
     }
     if (q.ev && q.ev[2]) (void)hipEventRecord((hipEvent_t)q.ev[2], s);
-    if (q.elem)
+    if (q.hand)
         hipLaunchKernelGGL((qp_filter_finish<L, T, true>), grid, block, lds_finish, s, a, m, (const T *)a.fagg[src]);
     else
         hipLaunchKernelGGL((qp_filter_finish<L, T, false>), grid, block, lds_finish, s, a, m, (const T *)a.fagg[src]);
     hipLaunchKernelGGL(qp_loglik_sum, dim3(1), dim3(256), 0, s, (const double *)a.partials, q.G, q.loglik);
     if (q.ev && q.ev[3]) (void)hipEventRecord((hipEvent_t)q.ev[3], s);
     int rc = (int)hipGetLastError();
-    if (rc || !q.elem) return rc;
+    if (rc || !q.hand) return rc;
     if (q.ev && q.ev[4]) (void)hipEventRecord((hipEvent_t)q.ev[4], s);
-    hipLaunchKernelGGL((qp_smoother_fold<L, T>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((qp_smoother_join<L, T>), grid, block, 0, s, a);
     if (q.ev && q.ev[5]) (void)hipEventRecord((hipEvent_t)q.ev[5], s);
     src = 0;
     for (int o = 1; o < q.G; o <<= 1) {
@@ -399,8 +649,9 @@ int qp_launch_t(const QPDev &m, const QPLaunch &q, hipStream_t s)
                            q.G, o);
         src ^= 1;
     }
+    const dim3 sgrid((unsigned)(((int64_t)q.G * q.nsub + TEAMS - 1) / TEAMS));
     if (q.ev && q.ev[6]) (void)hipEventRecord((hipEvent_t)q.ev[6], s);
-    hipLaunchKernelGGL((qp_smoother_finish<L, T>), grid, block, 0, s, a, m, (const T *)a.sagg[src]);
+    hipLaunchKernelGGL((qp_smoother_finish<L, T>), sgrid, block, lds_finish, s, a, m, (const T *)a.sagg[src]);
     if (q.ev && q.ev[7]) (void)hipEventRecord((hipEvent_t)q.ev[7], s);
     return (int)hipGetLastError();
 }

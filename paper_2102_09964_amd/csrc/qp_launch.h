@@ -17,8 +17,11 @@ struct QPLaunch {
     int chunk;
     int G;              // chunks of `chunk` steps
     void *fagg[2];      // G filter aggregates each (ping-pong)
-    void *sagg[2];      // G smoother aggregates each (ping-pong)
-    void *elem;         // n smoother elements; NULL: log-likelihood only
+    int sub, nsub;      // smoother: steps per sub-chunk, sub-chunks per chunk
+    void *elem;         // G nsub smoother elements of the sub-chunks
+    void *sagg[2];      // G smoother elements each (ping-pong)
+    double *hand;       // n (d + 2) values handed to the smoother; NULL: log-likelihood only
+    double *bound;      // G nsub d (d + 2): end moments of the sub-chunks
     double *partials;   // G
     double *loglik;     // device double[1]
     void *f_mean;

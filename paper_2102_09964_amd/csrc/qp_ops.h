@@ -83,6 +83,53 @@ __device__ __forceinline__ void qp_right_Ft_plus_Q(const QPStep<L::J> &st, const
         for (int k = 0; k < L::D; k++) Z[s][k] = out[s][k];
 }
 
+// Y = X F: column k of X (F - I) mixes the columns of k's block, inside the
+// lane
+template <class L>
+__device__ __forceinline__ void qp_right_F(const QPStep<L::J> &st, const double (&X)[L::RPL][L::D],
+                                           double (&Y)[L::RPL][L::D])
+{
+    double out[L::RPL][L::D];
+#pragma unroll
+    for (int s = 0; s < L::RPL; s++)
+#pragma unroll
+        for (int k = 0; k < L::D; k++) {
+            const int b0 = k < 4 ? (k & ~1) : (k & ~3);
+            const int bn = k < 4 ? 2 : 4;
+            double acc = X[s][k];
+#pragma unroll
+            for (int l = 0; l < 4; l++)
+                if (l < bn) acc = fma(X[s][b0 + l], qp_dl_at<L>(st, b0 + l, k), acc);
+            out[s][k] = acc;
+        }
+#pragma unroll
+    for (int s = 0; s < L::RPL; s++)
+#pragma unroll
+        for (int k = 0; k < L::D; k++) Y[s][k] = out[s][k];
+}
+
+// Y = F^T X and y = F^T x (the rows of one block of F^T are the lanes of one
+// DPP quad)
+template <class L>
+__device__ __forceinline__ void qp_left_Ft(const QPStep<L::J> &st, double (&X)[L::RPL][L::D], double (&x)[L::RPL])
+{
+#pragma unroll
+    for (int s = 0; s < L::RPL; s++) {
+        double dl[4];
+        qp_dl_col<L>(st, team_lane() + QP_TEAM * s, dl);
+        auto mix = [&](double v) {
+            double acc = v;
+            acc = fma(dl[0], quad_get<0>(v), acc);
+            acc = fma(dl[1], quad_get<1>(v), acc);
+            acc = fma(dl[2], quad_get<2>(v), acc);
+            return fma(dl[3], quad_get<3>(v), acc);
+        };
+#pragma unroll
+        for (int j = 0; j < L::D; j++) X[s][j] = mix(X[s][j]);
+        x[s] = mix(x[s]);
+    }
+}
+
 // row K of a row-distributed matrix, on every lane
 template <class L, int K, typename T, typename U>
 __device__ __forceinline__ void qp_row(const T (&X)[L::RPL][L::D], U (&out)[L::D])
@@ -436,7 +483,7 @@ __device__ __forceinline__ void qp_fold(QAgg<L, T> &a, const QPDev &m, const QPS
 #pragma unroll
     for (int s = 0; s < L::RPL; s++) {
         const int row = team_lane() + QP_TEAM * s;
-        const double cr = qp_pick<L::D>(c, row), Kr = qp_pick<L::D>(K, row), vr = qp_pick<L::D>(v, row);
+        const double cr = qp_pick<L::D>(c, row), Kr = cr * w, vr = qp_pick<L::D>(v, row);
         a.b[s] = T(fma(Kr, res, (double)b1[s]));
         a.eta[s] = T(fma(vr, res * w, (double)a.eta[s]));
 #pragma unroll
@@ -694,23 +741,78 @@ __device__ __forceinline__ void qsagg_apply(const QSAgg<L, T> &x, T (&g)[L::RPL]
     }
 }
 
-// Smoother element of a step (supplement, Proposition 2) in FP64 from the
-// filtered moments (m, P) of the step and the prediction of the next step
-// through its transition, Y = F P, mp = F m, Pp = F P F^T + Q:
-//   Pp = C C^T (Cholesky), Y <- C^-1 Y, L = P - Y^T Y, E^T = C^-T Y,
-//   g = m - E mp,
+// Y <- C^-1 Y (forward substitution, rows in order); C lower triangular by
+// rows, rd the reciprocals of its diagonal
+template <class L>
+__device__ __forceinline__ void qp_forward(const double (&Cl)[L::RPL][L::D], const double (&rd)[L::D],
+                                           double (&Y)[L::RPL][L::D])
+{
+    constexpr int D = L::D, R = L::RPL;
+    sfor<0, D>([&](auto kc) {
+        constexpr int k = decltype(kc)::value;
+#pragma unroll
+        for (int s = 0; s < R; s++) {
+            const bool own = team_lane() + QP_TEAM * s == k;
+#pragma unroll
+            for (int j = 0; j < D; j++) Y[s][j] = own ? Y[s][j] * rd[k] : Y[s][j];
+        }
+        double yk[D];
+        qp_row<L, k>(Y, yk);
+#pragma unroll
+        for (int s = 0; s < R; s++) {
+            const int row = team_lane() + QP_TEAM * s;
+            const double lik = row > k ? Cl[s][k] : 0.0;
+#pragma unroll
+            for (int j = 0; j < D; j++) Y[s][j] = fma(-lik, yk[j], Y[s][j]);
+        }
+    });
+}
+
+// Y <- C^-T Y (back substitution, rows in reverse order); Ct = C^T by rows
+template <class L>
+__device__ __forceinline__ void qp_backward(const double (&Ct)[L::RPL][L::D], const double (&rd)[L::D],
+                                            double (&Y)[L::RPL][L::D])
+{
+    constexpr int D = L::D, R = L::RPL;
+    sfor<0, D>([&](auto kc) {
+        constexpr int k = D - 1 - decltype(kc)::value;
+#pragma unroll
+        for (int s = 0; s < R; s++) {
+            const bool own = team_lane() + QP_TEAM * s == k;
+#pragma unroll
+            for (int j = 0; j < D; j++) Y[s][j] = own ? Y[s][j] * rd[k] : Y[s][j];
+        }
+        double zk[D];
+        qp_row<L, k>(Y, zk);
+#pragma unroll
+        for (int s = 0; s < R; s++) {
+            const int row = team_lane() + QP_TEAM * s;
+            const double lki = row < k ? Ct[s][k] : 0.0;
+#pragma unroll
+            for (int j = 0; j < D; j++) Y[s][j] = fma(-lki, zk[j], Y[s][j]);
+        }
+    });
+}
+
+// Smoother element of a run of steps (supplement, Proposition 2) in FP64: the
+// map from the smoothed moments of its last step to those of the step before
+// its first. From the fixed-point smoother of that earlier state, its moments
+// (m0, P0) given the run's observations and its cross-covariance G with the
+// state of the last step (row: last step), and the filter moments (mf, P) of
+// the last step:
+//   P = C C^T (Cholesky), Z = C^-1 G, L = P0 - Z^T Z, E^T = C^-T Z,
+//   g = m0 - E mf,
 // then in the smoother's coordinates z' = S z, S = I + e_0 u^T (first
-// coordinate f / h_0): E' = S E S^-1, g' = S g, L' = S L S^T. P is
-// overwritten (L); Y is consumed. At the end of the series the caller
-// passes the prior transition (F = 0, Q = I), which gives (0, m, P).
+// coordinate f / h_0): E' = S E S^-1, g' = S g, L' = S L S^T. P0 and G are
+// consumed; Cl and rd receive the factor and the reciprocals of its diagonal.
+// A run that ends the series comes with G = 0 (E = 0).
 template <class L, typename T>
 __device__ __forceinline__ void qp_element(const QPDev &m, const double (&mf)[L::RPL], double (&P)[L::RPL][L::D],
                                            double (&Y)[L::RPL][L::D], const double (&mp)[L::RPL],
-                                           const double (&Pp)[L::RPL][L::D], QSAgg<L, T> &e, double *tbuf,
-                                           uint32_t &bad)
+                                           const double (&Pp)[L::RPL][L::D], double (&Cl)[L::RPL][L::D],
+                                           double (&rd)[L::D], QSAgg<L, T> &e, double *tbuf, uint32_t &bad)
 {
     constexpr int D = L::D, R = L::RPL;
-    double Cl[R][D], rd[D];
 #pragma unroll
     for (int s = 0; s < R; s++)
 #pragma unroll
@@ -737,25 +839,7 @@ __device__ __forceinline__ void qp_element(const QPDev &m, const double (&mf)[L:
             for (int s = 0; s < R; s++) Cl[s][j] = fma(-l[s], lj, Cl[s][j]);
         });
     });
-    // Y <- C^-1 Y (forward substitution, rows in order)
-    sfor<0, D>([&](auto kc) {
-        constexpr int k = decltype(kc)::value;
-#pragma unroll
-        for (int s = 0; s < R; s++) {
-            const bool own = team_lane() + QP_TEAM * s == k;
-#pragma unroll
-            for (int j = 0; j < D; j++) Y[s][j] = own ? Y[s][j] * rd[k] : Y[s][j];
-        }
-        double yk[D];
-        qp_row<L, k>(Y, yk);
-#pragma unroll
-        for (int s = 0; s < R; s++) {
-            const int row = team_lane() + QP_TEAM * s;
-            const double lik = row > k ? Cl[s][k] : 0.0;
-#pragma unroll
-            for (int j = 0; j < D; j++) Y[s][j] = fma(-lik, yk[j], Y[s][j]);
-        }
-    });
+    qp_forward<L>(Cl, rd, Y);
     // L = P - Y^T Y
     {
         double YT[R][D], G[R][D];
@@ -767,28 +851,10 @@ __device__ __forceinline__ void qp_element(const QPDev &m, const double (&mf)[L:
             for (int j = 0; j < D; j++) P[s][j] -= G[s][j];
         qp_symmetrize<L, double>(P, tbuf);
     }
-    // E^T = C^-T Y (back substitution, rows in reverse order)
     {
-        double CT[R][D];
-        qp_transpose<L, double>(Cl, CT, tbuf);
-        sfor<0, D>([&](auto kc) {
-            constexpr int k = D - 1 - decltype(kc)::value;
-#pragma unroll
-            for (int s = 0; s < R; s++) {
-                const bool own = team_lane() + QP_TEAM * s == k;
-#pragma unroll
-                for (int j = 0; j < D; j++) Y[s][j] = own ? Y[s][j] * rd[k] : Y[s][j];
-            }
-            double zk[D];
-            qp_row<L, k>(Y, zk);
-#pragma unroll
-            for (int s = 0; s < R; s++) {
-                const int row = team_lane() + QP_TEAM * s;
-                const double lki = row < k ? CT[s][k] : 0.0;
-#pragma unroll
-                for (int j = 0; j < D; j++) Y[s][j] = fma(-lki, zk[j], Y[s][j]);
-            }
-        });
+        double Ct[R][D];
+        qp_transpose<L, double>(Cl, Ct, tbuf);
+        qp_backward<L>(Ct, rd, Y);
     }
     double E[R][D];
     qp_transpose<L, double>(Y, E, tbuf);

@@ -151,42 +151,63 @@ struct QPStep {
     double cm[J + 1], sn[J + 1];
     double fm[4], fa[4];  // (F00 - 1, F01, F10, F11 - 1)
     double qm[3], qa[3];  // (Q00, Q01, Q11)
-    bool first, pad;
 };
 
 // Matern-3/2 block of rate lam over dt in the coordinates (f, f' / lam):
-// F - I and Q = I - F F^T, accurate for small x = lam dt.
+// F - I and Q = I - F F^T, accurate for small x = lam dt. One expm1 gives all:
+// e^-x = 1 + expm1(-x) and 1 - e^-2x = -expm1(-x) (2 + expm1(-x)).
 __device__ __forceinline__ void qp_matern32(double lam, double dt, double (&f)[4], double (&q)[3])
 {
     const double x = lam * dt;
-    const double e = exp(-x);
     const double em1 = expm1(-x);
+    const double e = 1.0 + em1;
     f[0] = em1 + x * e;   // e (1 + x) - 1
     f[1] = x * e;
     f[2] = -x * e;
     f[3] = em1 - x * e;   // e (1 - x) - 1
     const double e2 = e * e;
-    const double om = -expm1(-2.0 * x);  // 1 - e^-2x
+    const double om = -em1 * (2.0 + em1);
     q[0] = om - e2 * (2.0 * x + 2.0 * x * x);
     q[1] = 2.0 * x * x * e2;
     q[2] = om + e2 * (2.0 * x - 2.0 * x * x);
 }
 
+// The harmonics come from one sincos of half the base angle: cos th - 1 =
+// -2 sin^2(th / 2), then by the addition theorem in the differences cos - 1,
+// whose terms all have the size of the result for short steps. (A sincos per
+// harmonic and three exponentials per Matern block were two fifths of the
+// fold's instructions.) first and pad are applied here, to the scalars: F = 0
+// and Q = I are F_m = 0 without rotation, the identity is F_m = I.
 template <int J>
 __device__ __forceinline__ void qp_step(const QPDev &m, double dt, bool first, bool pad, QPStep<J> &st)
 {
-    st.first = first;
-    st.pad = pad;
-    const double th = m.w0 * dt;
+    double s, c;
+    sincos(0.5 * (m.w0 * dt), &s, &c);
+    st.cm[0] = 0.0;
+    st.sn[0] = 0.0;
+    const bool special = first || pad;
+    const double cm1 = special ? 0.0 : -2.0 * s * s, sn1 = special ? 0.0 : 2.0 * s * c;
 #pragma unroll
-    for (int j = 0; j <= J; j++) {
-        double s, c;
-        sincos(0.5 * j * th, &s, &c);
-        st.cm[j] = -2.0 * s * s;  // cos(j th) - 1
-        st.sn[j] = 2.0 * s * c;   // sin(j th)
+    for (int j = 1; j <= J; j++) {
+        const double a = st.cm[j - 1], b = st.sn[j - 1];
+        st.cm[j] = fma(a, cm1, a + cm1) - b * sn1;
+        st.sn[j] = fma(b, cm1, b) + fma(a, sn1, sn1);
     }
     qp_matern32(m.lam_m, dt, st.fm, st.qm);
     qp_matern32(m.lam_a, dt, st.fa, st.qa);
+    const double d = pad ? 0.0 : -1.0, p = pad ? 0.0 : 1.0;
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        const double v = (i == 0 || i == 3) ? d : 0.0;
+        st.fm[i] = special ? v : st.fm[i];
+        st.fa[i] = special ? v : st.fa[i];
+    }
+#pragma unroll
+    for (int i = 0; i < 3; i++) {
+        const double v = i == 1 ? 0.0 : p;
+        st.qm[i] = special ? v : st.qm[i];
+        st.qa[i] = special ? v : st.qa[i];
+    }
 }
 
 // (F - I)[i][k] of harmonic block j from its cm = cos(j th) - 1 and
@@ -228,9 +249,37 @@ __device__ __forceinline__ void qp_dl_row(const QPStep<L::J> &st, int row, doubl
             const double va = a == 0 ? (b == 0 ? st.fa[0] : st.fa[1]) : (b == 0 ? st.fa[2] : st.fa[3]);
             v0 = (ir < 2) ? vm : va;
         }
-        double v = (jr == 0) ? v0 : vh;
-        if (st.first) v = (q == ir) ? -1.0 : 0.0;
-        dl[q] = (st.pad || row >= L::D) ? 0.0 : v;
+        const double v = (jr == 0) ? v0 : vh;
+        dl[q] = row >= L::D ? 0.0 : v;
+    }
+}
+
+// (F - I)[quad base + q][row] for this lane's row, q = 0..3: the column of
+// this row's block, as qp_dl_row gives its row.
+template <class L>
+__device__ __forceinline__ void qp_dl_col(const QPStep<L::J> &st, int row, double (&dl)[4])
+{
+    const int jr = row >> 2, ir = row & 3;
+    double cmj = st.cm[0], snj = st.sn[0];
+#pragma unroll
+    for (int jj = 1; jj <= L::J; jj++) {
+        cmj = (jr == jj) ? st.cm[jj] : cmj;
+        snj = (jr == jj) ? st.sn[jj] : snj;
+    }
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        double vh = 0.0;
+#pragma unroll
+        for (int i = 0; i < 4; i++) vh = (ir == i) ? qp_dl_harm<L::J>(st, cmj, snj, q, i) : vh;
+        double v0 = 0.0;
+        if ((q >> 1) == (ir >> 1)) {
+            const int a = q & 1, b = ir & 1;
+            const double vm = a == 0 ? (b == 0 ? st.fm[0] : st.fm[1]) : (b == 0 ? st.fm[2] : st.fm[3]);
+            const double va = a == 0 ? (b == 0 ? st.fa[0] : st.fa[1]) : (b == 0 ? st.fa[2] : st.fa[3]);
+            v0 = (ir < 2) ? vm : va;
+        }
+        const double v = (jr == 0) ? v0 : vh;
+        dl[q] = row >= L::D ? 0.0 : v;
     }
 }
 
@@ -248,8 +297,7 @@ __device__ __forceinline__ double qp_dl_at(const QPStep<L::J> &st, int k, int l)
         const int j = k >> 2;
         v = qp_dl_harm<L::J>(st, st.cm[j], st.sn[j], k & 3, l & 3);
     }
-    if (st.first) v = (k == l) ? -1.0 : 0.0;
-    return st.pad ? 0.0 : v;
+    return v;
 }
 
 // Q[row][k] (runtime row, compile-time k): block diagonal in 2 x 2 blocks,
@@ -266,7 +314,6 @@ __device__ __forceinline__ double qp_q_at(const QPStep<L::J> &st, int row, int k
         vm = a == 0 ? st.qm[1] : st.qm[2];
         va = a == 0 ? st.qa[1] : st.qa[2];
     }
-    double v = ((row >> 1) == 1) ? va : vm;
-    if (st.first) v = (row == k) ? 1.0 : 0.0;
-    return (st.pad || row >= L::D || (row >> 1) != (k >> 1)) ? 0.0 : v;
+    const double v = ((row >> 1) == 1) ? va : vm;
+    return (row >= L::D || (row >> 1) != (k >> 1)) ? 0.0 : v;
 }
