@@ -525,11 +525,30 @@ int qp_check_opts(const pssgp_options *opts)
     return PSSGP_OK;
 }
 
+// Default chunk. FP32: kQPDefaultChunk. FP64 (as with the one-lane scans, the
+// FP32 log-likelihood would move with it): one team per quarter of a wave on
+// every SIMD (4 096 teams) at 8 states and half of that at 12 and 16, where a
+// level of the scan costs more than the steps it saves, from qp_least to
+// kQPDefaultChunk steps. Measured (FP64, ms at chunk 16 / 32 / 64 / 128 / 256):
+// 8 states, 65 000 steps 0.43 / 0.41 / 0.53 / 0.83 / 1.44, 260 000 steps 1.52 /
+// 1.01 / 0.72 / 0.94 / 1.48; 16 states, 20 000 steps 3.4 / 2.6 / 2.1 / 2.6 / 3.8,
+// 260 000 steps 26 / 12.8 / 6.4 / 4.7 / 5.2.
+int64_t qp_least(int d) { return d <= 10 ? 16 : 64; }
+int64_t qp_teams(int d) { return d <= 10 ? 4096 : 2048; }
+
+int qp_default_chunk(int d, int64_t n, bool f64)
+{
+    if (!f64) return kQPDefaultChunk;
+    const int64_t c = (n + qp_teams(d) - 1) / qp_teams(d);
+    return (int)(c < qp_least(d) ? qp_least(d) : (c > kQPDefaultChunk ? kQPDefaultChunk : c));
+}
+
 QPPlan qp_plan(int d, int64_t n, pssgp_dtype dtype, bool elems, const pssgp_options *opts)
 {
     QPPlan p;
-    p.chunk = (opts && opts->chunk) ? (int)opts->chunk : kQPDefaultChunk;
-    p.tsize = (dtype == PSSGP_F64) ? 8 : 4;
+    const bool f64 = dtype == PSSGP_F64, fixed = !f64 || (opts && opts->chunk);
+    p.chunk = (opts && opts->chunk) ? (int)opts->chunk : qp_default_chunk(d, n, f64);
+    p.tsize = f64 ? 8 : 4;
     p.G = (int)((n + p.chunk - 1) / p.chunk);
     // sub-chunks of the smoother: as many teams as put one wave of four on
     // every SIMD, of 16 steps at least (each costs the filter about two and a
@@ -539,9 +558,14 @@ QPPlan qp_plan(int d, int64_t n, pssgp_dtype dtype, bool elems, const pssgp_opti
     p.nsub = p.nsub < 1 ? 1 : (p.nsub > most ? most : p.nsub);
     p.sub = (p.chunk + p.nsub - 1) / p.nsub;
     p.nsub = (p.chunk + p.sub - 1) / p.sub;
-    // sized for the most sub-chunks of any shorter series, so that a workspace
-    // for n serves those too
-    const size_t G = (size_t)(p.G > 0 ? p.G : 1);
+    // sized for the most chunks and sub-chunks of any shorter series, so that
+    // a workspace for n serves those too
+    size_t G = (size_t)(p.G > 0 ? p.G : 1);
+    if (!fixed) {
+        const int64_t small = (n + qp_least(d) - 1) / qp_least(d), full = qp_teams(d);
+        const size_t least = (size_t)(small < full ? small : full);
+        G = G > least ? G : least;
+    }
     size_t ns = G > 4096 ? G : 4096;
     ns = ns < G * (size_t)most ? ns : G * (size_t)most;
     size_t off = ctl_bytes();

@@ -35,6 +35,23 @@ def test_workspace_monotone_and_static_scratch(name, dtype):
             assert P.workspace_bytes(m, n, dtype, P.OP_LOGLIK) <= P.STATIC_SCRATCH_BYTES, n
 
 
+@pytest.mark.parametrize("chunk", [0, 100])
+@pytest.mark.parametrize("dtype", [P.F32, P.F64])
+@pytest.mark.parametrize("J", [1, 2, 3])
+def test_quasiperiodic_workspace_monotone(J, dtype, chunk):
+    """Chunks and the smoother's sub-chunks both follow from n."""
+    m = P.make_model([(5, J, 1.0, 1.0, 1.0, 50.0), (MATERN32, 0, 20.0, 0.3)], 0.01)
+    o = P.make_options(chunk=chunk) if chunk else None
+    rng = np.random.default_rng(6)
+    ns = set(int(v) for v in np.exp(rng.uniform(0, np.log(2e6), 400)))
+    for q in (4096 * 16, 2048 * 64, 256 * 4096 // 3, 256 * 2048, 100 * 4096 // 5):
+        ns |= {q + j for j in (-1, 0, 1)}
+    ns = sorted(n for n in ns if n > 0)
+    for op in (P.OP_LOGLIK, P.OP_PREDICT):
+        b = [P.workspace_bytes(m, n, dtype, op, o) for n in ns]
+        assert all(x <= y for x, y in zip(b, b[1:])), op
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("n", [1, 255, 257, 262144, 262145, 1048577])
 def test_default_equals_explicit(n):
