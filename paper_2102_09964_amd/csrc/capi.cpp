@@ -134,13 +134,13 @@ Plan make_plan(int d, int ncomp, int64_t n, pssgp_dtype dtype, int op, const pss
     if (op == PSSGP_OP_PREDICT) {
         // filter then smoother on one stream: the scans share their regions
         // (the filter's are the larger); the handover is FP64 whatever the
-        // scan type (HandLayout)
+        // scan type (HandLayout; d > 3 in FP32: lane_overlap)
         p.off_incl = take(nt * filter_incl_elems(d) * p.tsize);
         p.off_agg = take(nt * filter_agg_elems(d) * p.tsize);
         p.off_fagg2 = take(nt * filter_agg_elems(d) * p.tsize);
         p.off_lane = take(nt * 64 * filter_agg_elems(d) * p.tsize);
         p.off_part = take(nt * sizeof(double) * n_params(ncomp));
-        p.off_hand = take(steps * (d + 1) * sizeof(double));
+        p.off_hand = take((steps + (p.tsize == 4 && d > 3 ? nt * 64 : 0)) * (d + 1) * sizeof(double));
         p.off_bound = take(nt * 64 * (size_t)smooth_incl_elems(d) * sizeof(double));
         p.off_slane = take(nt * 64 * (size_t)smooth_agg_elems(d) * p.tsize);
         p.total = off;

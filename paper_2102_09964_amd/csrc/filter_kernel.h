@@ -397,7 +397,8 @@ __device__ __forceinline__ void filter_tile_finish(const FilterParams<T> &p, con
     uint32_t bad = 0;
 
     constexpr bool SMOOTH = (MODE & F_SMOOTH) != 0;
-    using HL = HandLayout<D>;
+    constexpr bool OVER = SMOOTH && lane_overlap<D, T>() > 0;
+    using HL = HandLayout<D, T>;
 
     T m0[D], P0[D][D];
     moments_load<D, T>(p.inclp + (size_t)slot * INCL, m0, P0);
@@ -420,7 +421,8 @@ __device__ __forceinline__ void filter_tile_finish(const FilterParams<T> &p, con
 #pragma unroll
         for (int j = 0; j < D; j++) P[i][j] = (double)P0[i][j];
     }
-    // fixed-point smoother of the state before the lane (lane_smoother_element)
+    // fixed-point smoother of the state before the lane (of its first step with
+    // OVER; lane_smoother_element)
     double fm[D], fP[D][D], fG[D][D];
     if constexpr (SMOOTH) {
 #pragma unroll
@@ -442,8 +444,19 @@ __device__ __forceinline__ void filter_tile_finish(const FilterParams<T> &p, con
     // loop's first use of them carries no wait into later iterations
     asm volatile("" ::"v"(in.tc), "v"(in.tp), "v"(in.yc), "v"((int)in.oc));
     const OptInputs opt(p.mask, p.noise_k, p.t);
-    for (int64_t k = k0; k < k1; k++) {
-        const int64_t kn = (k + 1 < k1) ? k + 1 : k;
+    // a series that ends with the lane: the fixed-point smoother has seen all
+    // its observations (E = 0), and there is no step after to end the run with
+    bool end = false;
+    if constexpr (SMOOTH) {
+        if (k1 > k0) {
+            SV se = sv;
+            se.seek(k1 - 1);
+            end = (k1 >= tr.k_end) || se.last(k1 - 1);
+        }
+    }
+    const int64_t ke = (OVER && k1 > k0 && !end) ? k1 + 1 : k1;
+    for (int64_t k = k0; k < ke; k++) {
+        const int64_t kn = (k + 1 < ke) ? k + 1 : k;
         const double tn = p.t[kn];
         const T yn = p.y[kn];
         const bool on = opt.observed(kn);
@@ -467,7 +480,13 @@ __device__ __forceinline__ void filter_tile_finish(const FilterParams<T> &p, con
         // predict in FP64 (mp = F m, Y = F P, Pp = F P F^T + Q)
         double mp[D], Y[D][D], Pp[D][D];
         predict_step<D, double, Sparsity<LY>>(m, P, Dl, Q, mp, Y, Pp);
-        if constexpr (SMOOTH) fixed_point_predict<D, Sparsity<LY>>(Dl, fG);
+        // (with OVER, the fixed-point smoother of the lane's first step is
+        // overwritten below; a branch around it costs 5 % of the call at d = 6
+        // and gains 2 % at d = 8)
+        const bool fixed = !(OVER && D > 6) || k > k0;
+        if constexpr (SMOOTH) {
+            if (fixed) fixed_point_predict<D, Sparsity<LY>>(Dl, fG);
+        }
         // the loads of this iteration are waited for here, before the
         // handover stores: the wait counter is in order, so a wait after
         // the stores would also wait for all of them
@@ -501,7 +520,7 @@ __device__ __forceinline__ void filter_tile_finish(const FilterParams<T> &p, con
             lg = (double)__builtin_amdgcn_logf((float)(6.283185307179586 * S)) * 0.6931471805599453;
         else
             lg = log(6.283185307179586 * S);
-        const double term = obs ? -0.5 * (lg + v * v * w) : 0.0;
+        const double term = (obs && (!OVER || k < k1)) ? -0.5 * (lg + v * v * w) : 0.0;
         if constexpr (SEG) {
             if (first && k > k0) {
                 if (p.ll_terms) p.ll_terms[seg_k] = seg;
@@ -510,7 +529,7 @@ __device__ __forceinline__ void filter_tile_finish(const FilterParams<T> &p, con
             }
             seg += term;
         } else {
-            if (p.ll_terms) p.ll_terms[k] = term;
+            if (p.ll_terms && (!OVER || k < k1)) p.ll_terms[k] = term;
         }
         ll += term;
         double K[D];
@@ -552,6 +571,18 @@ __device__ __forceinline__ void filter_tile_finish(const FilterParams<T> &p, con
                 P[i][j] = c;
                 P[j][i] = c;
             }
+        if constexpr (OVER) {
+            // from here on (a branch around the lane's first step above costs
+            // 5 % of the call at d = 6)
+            if (k == k0) {
+#pragma unroll
+                for (int i = 0; i < D; i++) {
+                    fm[i] = m[i];
+#pragma unroll
+                    for (int j = 0; j < D; j++) fP[i][j] = fG[i][j] = P[i][j];
+                }
+            }
+        }
         if constexpr ((MODE & F_MOMENTS) != 0) {
 #pragma unroll
             for (int i = 0; i < D; i++) p.m[(size_t)i * p.n + k] = T(m[i]);
@@ -567,10 +598,6 @@ __device__ __forceinline__ void filter_tile_finish(const FilterParams<T> &p, con
         SAgg<D, T> sacc;
         sagg_identity<D, T>(sacc);
         if (k1 > k0) {
-            // a series that ends with the lane: the fixed-point smoother has
-            // seen all its observations (E = 0)
-            sv.seek(k1 - 1);
-            const bool end = (k1 >= tr.k_end) || sv.last(k1 - 1);
 #pragma unroll
             for (int i = 0; i < D; i++)
 #pragma unroll

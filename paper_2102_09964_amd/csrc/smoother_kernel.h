@@ -196,7 +196,7 @@ __device__ __forceinline__ void smoother_tile_fused(const SmoothParams<T> &p, co
     constexpr int INCL = SAggLayout<D>::INCL;
     constexpr int B = smoother_shear_col<LY>();
     using SP = Sparsity<LY>;
-    using HL = HandLayout<D>;
+    using HL = HandLayout<D, T>;
     const int lane = lane_id();
     const int slot = tr.slot_base + tile;
     const int64_t chunk_id = (int64_t)slot * PSSGP_WAVE + lane;
@@ -209,14 +209,18 @@ __device__ __forceinline__ void smoother_tile_fused(const SmoothParams<T> &p, co
     const int row = p.chunk + 1, half = PSSGP_WAVE * row;
     T *so = s_out + lane * row;
     if (k0 < k1) {
-        // inputs of the lane's last step, requested first
+        // a series ends with the lane: nothing after it
+        sv.seek(k1 - 1);
+        const bool end = (k1 >= tr.k_end) || sv.last(k1 - 1);
+        const int64_t kl = (lane_overlap<D, T>() && !end) ? k1 : k1 - 1;  // last step of the lane's run
+        // inputs of that step, requested first
         const OptInputs opt(p.mask, nullptr, p.t);
         const double *hp = p.hand + HL::step(slot, p.chunk, 0, lane);
         constexpr size_t ST = (size_t)HL::STEP * PSSGP_WAVE;
-        double ph[D], hm, tc = p.t[k1 - 1], tp = p.t[k1 - 1 > tr.k_begin ? k1 - 2 : k1 - 1];
-        T yc = p.y[k1 - 1];
-        bool oc = opt.observed(k1 - 1);
-        const double *hq = hp + (size_t)(k1 - 1 - k0) * ST;
+        double ph[D], hm, tc = p.t[kl], tp = p.t[kl > tr.k_begin ? kl - 1 : kl];
+        T yc = p.y[kl];
+        bool oc = opt.observed(kl);
+        const double *hq = hp + (size_t)(kl - k0) * ST;
 #pragma unroll
         for (int i = 0; i < D; i++) ph[i] = __builtin_nontemporal_load(hq + i * PSSGP_WAVE);
         hm = __builtin_nontemporal_load(hq + D * PSSGP_WAVE);
@@ -296,9 +300,6 @@ __device__ __forceinline__ void smoother_tile_fused(const SmoothParams<T> &p, co
             }
             forward(ms);
             backward(ms);
-            // a series ends with the lane: nothing after it
-            sv.seek(k1 - 1);
-            const bool end = (k1 >= tr.k_end) || sv.last(k1 - 1);
 #pragma unroll
             for (int i = 0; i < D; i++) {
                 lam[i] = end ? 0.0 : ms[i];
@@ -309,7 +310,7 @@ __device__ __forceinline__ void smoother_tile_fused(const SmoothParams<T> &p, co
                 }
             }
         }
-        for (int64_t k = k1 - 1;; k--) {
+        for (int64_t k = kl;; k--) {
             // the next step's inputs, one iteration ahead
             const int64_t kn = k > k0 ? k - 1 : k0;
             double nph[D];
@@ -354,7 +355,8 @@ __device__ __forceinline__ void smoother_tile_fused(const SmoothParams<T> &p, co
                 if (i > 0) ul = fma(lam[i], ph[i], ul);
             }
             phl = fma(lam[0], hph, ul);
-            // f outputs staged in LDS for coalesced stores
+            // f outputs staged in LDS for coalesced stores (those of a step
+            // past the lane go to the row's spare entry)
             so[k - k0] = T(fma(r, phl, fma(hph * w, v, hm)));
             so[half + (k - k0)] = T(r * fma(-r, phq, hph));
             if (k == k0) break;
