@@ -896,6 +896,7 @@ int pssgp_predict(const pssgp_model *model, const double *t, const void *y, cons
     sm.f_var = f_var;
     sm.hand = a.hand;
     sm.bound = a.bound;
+    sm.loglik = loglik;
     sm.slane = b + p.off_slane;
     sm.ws = sw;
     return check_launch(launch_smoother(dm, b0, b1, dtype == PSSGP_F64, sm, s), "smoother launch");
@@ -943,8 +944,6 @@ static int run_loglik_grad(const pssgp_model *model, const double *t, const void
     rc = check_launch(launch_filter(dm, b0, b1, dtype == PSSGP_F64, a, s), "filter launch");
     if (rc) return rc;
     ScanWs sw2 = scan_ws(ws, p, true);
-    rc = launch_ws_init(sw2.ctl, nullptr, 0, s, /*keep_status=*/true);
-    if ((rc = hip_err((hipError_t)rc, "workspace init"))) return rc;
     GradLaunch g{};
     g.t = t;
     g.y = y;
@@ -954,6 +953,8 @@ static int run_loglik_grad(const pssgp_model *model, const double *t, const void
     g.ntiles = p.ntiles;
     g.rec = b + p.off_rec;
     g.grad = grad;
+    g.loglik = loglik;
+    g.ll_partials = sw.partials;
     g.noise_fixed = noise_k != nullptr;
     g.ws = sw2;
     return check_launch(launch_grad(dm, b0, b1, dtype == PSSGP_F64, g, s), "adjoint launch");

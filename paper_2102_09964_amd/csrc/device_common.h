@@ -1110,6 +1110,35 @@ __device__ __forceinline__ T *lane_rec(T *base, int64_t slot, int size, int lane
 
 __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & (PSSGP_WAVE - 1)); }
 
+// Sum of one value per tile, np values apart, by one wave in a fixed order.
+__device__ __forceinline__ double sum_over_tiles(const double *partials, int ntiles, int np)
+{
+    double s = 0.0;
+#pragma unroll 8
+    for (int i = lane_id(); i < ntiles; i += PSSGP_WAVE) s += partials[(size_t)i * np];
+    return wave_sum(s);
+}
+
+// Sum over the tiles in the kernel that writes the tiles' partials, by the last
+// tile to finish (no waiting involved). True for that tile, whose partials are
+// then visible. Every tile's release writes back its L2 and its acquire
+// invalidates it, on top of one atomic at a time on the counter: about 20 ns a
+// tile, so that 977 tiles of a filter at d = 2 took 40 instead of 20 us (1e6
+// steps). Calls of more than LAST_TILES tiles sum in a kernel of their own (or
+// in one that runs later in the call anyway), which costs less than a launch.
+constexpr int LAST_TILES = 64;
+
+__device__ __forceinline__ bool last_tile(WsCtl *ctl, int ntiles)
+{
+    uint32_t prev = 0;
+    if (lane_id() == 0) prev = __hip_atomic_fetch_add(&ctl->done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+    prev = __shfl(prev, 0, PSSGP_WAVE);
+    if (prev != (uint32_t)(ntiles - 1)) return false;
+    __threadfence();
+    if (lane_id() == 0) ctl->done = 0u;  // for the next kernel of the call
+    return true;
+}
+
 // The model constants (up to ~3.5 KB, mostly the expansion matrices of the
 // transition) are copied from the kernel arguments into LDS once per
 // workgroup. Loops over steps start with a compiler barrier so that the

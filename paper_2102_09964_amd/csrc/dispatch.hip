@@ -4,12 +4,20 @@
 
 namespace {
 
-__global__ void ws_init_kernel(WsCtl *ctl, double *zero_out, int nzero, int keep_status)
+__global__ void ws_init_kernel(WsCtl *ctl, double *zero_out, int nzero)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i == 0) ctl->done = 0u;
-    if (i == 1 && !keep_status) ctl->status = 0u;
+    if (i == 1) ctl->status = 0u;
     if (zero_out && i < nzero) zero_out[i] = 0.0;
+}
+
+__global__ __launch_bounds__(64) void tile_sums_kernel(const double *ll, double *ll_out, const double *part, double *out,
+                                                       int np, int ntiles)
+{
+    const int q = (int)blockIdx.x - 1;
+    const double s = q < 0 ? sum_over_tiles(ll, ntiles, 1) : sum_over_tiles(part + q, ntiles, np);
+    if (lane_id() == 0) *(q < 0 ? ll_out : out + q) = s;
 }
 
 }  // namespace
@@ -72,11 +80,17 @@ int launch_plain(const DevModel &mdl, int b0, int b1, const PlainLaunch &a, hipS
     return -1;
 }
 
-int launch_ws_init(WsCtl *ctl, double *zero_out, int nzero, hipStream_t s, bool keep_status)
+int launch_tile_sums(const double *ll, double *ll_out, const double *part, double *out, int np, int ntiles, hipStream_t s)
+{
+    hipLaunchKernelGGL(tile_sums_kernel, dim3(1 + np), dim3(PSSGP_WAVE), 0, s, ll, ll_out, part, out, np, ntiles);
+    return (int)hipGetLastError();
+}
+
+int launch_ws_init(WsCtl *ctl, double *zero_out, int nzero, hipStream_t s)
 {
     int64_t cnt = nzero > 2 ? nzero : 2;
     if (nzero > cnt) cnt = nzero;
     const dim3 grid((unsigned)((cnt + 255) / 256)), block(256);
-    hipLaunchKernelGGL(ws_init_kernel, grid, block, 0, s, ctl, zero_out, nzero, keep_status ? 1 : 0);
+    hipLaunchKernelGGL(ws_init_kernel, grid, block, 0, s, ctl, zero_out, nzero);
     return (int)hipGetLastError();
 }

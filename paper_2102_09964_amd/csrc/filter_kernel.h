@@ -663,22 +663,16 @@ __global__ __launch_bounds__(PSSGP_WAVE, (finish_waves<LY::D, T>())) void filter
     double ll = 0.0;
     filter_tile_finish<LY, T, CT, MODE, OneSeries>(p, mdl, (cdouble *)p.cst, sv, tr, tile, ll);
 
-    // log-likelihood: deterministic wave sum, tile partial, the last tile to
-    // finish reduces the partials in a fixed order (no waiting involved)
+    // log-likelihood: deterministic wave sum, tile partial; the partials are
+    // summed in a fixed order here, by the smoother of the same call (F_SMOOTH)
+    // or by launch_tile_sums
     const double tot = wave_sum(ll);
-    uint32_t prev = 0;
-    if (lane == 0) {
-        p.partials[tile] = tot;
-        prev = __hip_atomic_fetch_add(&p.ctl->done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    prev = __shfl(prev, 0, PSSGP_WAVE);
-    if (prev == (uint32_t)(p.ntiles - 1)) {
-        __threadfence();
-        double s = 0.0;
-        for (int i = lane; i < p.ntiles; i += PSSGP_WAVE)
-            s += __hip_atomic_load(&p.partials[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        s = wave_sum(s);
-        if (lane == 0) *p.loglik = s;
+    if (lane == 0) p.partials[tile] = tot;
+    if constexpr (!(MODE & F_SMOOTH)) {
+        if (p.ntiles <= LAST_TILES && last_tile(p.ctl, p.ntiles)) {
+            const double s = sum_over_tiles(p.partials, p.ntiles, 1);
+            if (lane == 0) *p.loglik = s;
+        }
     }
 }
 
@@ -768,6 +762,9 @@ int launch_filter_t(const DevModel &mdl, const FilterLaunch &a, hipStream_t s)
             hipLaunchKernelGGL((filter_finish_kernel<LY, T, double, 0>), grid, block, 0, s, p, mdl);
     }
     rc = (int)hipGetLastError();
+    if (rc) return rc;
+    // (the gradient call sums both its passes after the second)
+    if (!a.hand && !a.rec && a.ntiles > LAST_TILES) rc = launch_tile_sums(a.ws.partials, a.loglik, nullptr, nullptr, 0, a.ntiles, s);
     pass_event(a.ev, 3, s);
     return rc;
 }

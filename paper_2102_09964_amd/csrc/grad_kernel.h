@@ -416,25 +416,19 @@ __global__ __launch_bounds__(PSSGP_WAVE) void grad_finish_kernel(GradParams<T> p
     }
     if (bad) status_or(&p.ctl->status, bad);
 
-    // deterministic reduction: wave sums, tile partials, last tile reduces
+    // deterministic reduction: wave sums, tile partials, summed here or by
+    // launch_tile_sums
     double tot[NP];
 #pragma unroll
     for (int q = 0; q < NP; q++) tot[q] = wave_sum(gacc[q]);
-    uint32_t prev = 0;
     if (lane == 0) {
 #pragma unroll
         for (int q = 0; q < NP; q++) p.partials[(size_t)tile * NP + q] = tot[q];
-        prev = __hip_atomic_fetch_add(&p.ctl->done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
     }
-    prev = __shfl(prev, 0, PSSGP_WAVE);
-    if (prev == (uint32_t)(p.ntiles - 1)) {
-        __threadfence();
+    if (p.ntiles <= LAST_TILES && last_tile(p.ctl, p.ntiles)) {
 #pragma unroll
         for (int q = 0; q < NP; q++) {
-            double s = 0.0;
-            for (int i = lane; i < p.ntiles; i += PSSGP_WAVE)
-                s += __hip_atomic_load(&p.partials[(size_t)i * NP + q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            s = wave_sum(s);
+            const double s = sum_over_tiles(p.partials + q, p.ntiles, NP);
             if (lane == 0) p.grad[q] = s;
         }
     }
@@ -466,7 +460,9 @@ int launch_grad_t(const DevModel &mdl, const GradLaunch &a, hipStream_t s)
     rc = launch_tile_scan<AdjointScanOps<LY::D, T>>(a.ws.aggp, 0, a.ntiles, true, a.ws.inclp, a.ws.gagg, a.ws.gcarry, s);
     if (rc) return rc;
     hipLaunchKernelGGL((grad_finish_kernel<LY, T>), grid, block, 0, s, p, mdl);
-    return (int)hipGetLastError();
+    rc = (int)hipGetLastError();
+    if (rc || a.ntiles <= LAST_TILES) return rc;
+    return launch_tile_sums(a.ll_partials, a.loglik, a.ws.partials, a.grad, 2 * LY::NB + 1, a.ntiles, s);
 }
 
 template <int B0, int B1>

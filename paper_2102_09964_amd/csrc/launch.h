@@ -8,7 +8,7 @@
 
 // Control block at the start of every workspace.
 struct WsCtl {
-    uint32_t done;     // tiles finished (last-block reduction)
+    uint32_t done;     // tiles finished (last_tile)
     uint32_t status;   // PSSGP_STATUS_* bits
     uint32_t pad[62];
 };
@@ -71,6 +71,7 @@ struct SmoothLaunch {
     const double *hand;   // nullable: fused call, what the filter's finish wrote (m, P unused)
     const double *bound;
     void *slane;
+    double *loglik;       // hand: receives the sum of the filter's partials
     ScanWs ws;
 };
 
@@ -84,6 +85,8 @@ struct GradLaunch {
     const void *rec;    // per-step records written by the forward filter
     int noise_fixed;    // per-step noise variances given: the noise-variance derivative is 0
     double *grad;       // device [2 n_comp + 1]
+    const double *ll_partials;  // the filter's log-likelihood by tiles
+    double *loglik;
     ScanWs ws;
 };
 
@@ -184,10 +187,11 @@ inline void pass_event(void *const *ev, int i, hipStream_t s)
     if (ev && ev[i]) (void)hipEventRecord((hipEvent_t)ev[i], s);
 }
 
-// Zeroes the control block (keep_status: only the tile counter, so that a
-// second pass of the same call keeps the first one's status bits) and
-// zero_out[0, nzero).
-int launch_ws_init(WsCtl *ctl, double *zero_out, int nzero, hipStream_t s, bool keep_status = false);
+// Sums of the tiles' partials: ll_out from ll (one value per tile) and out[q]
+// from part (np values per tile).
+int launch_tile_sums(const double *ll, double *ll_out, const double *part, double *out, int np, int ntiles, hipStream_t s);
+// Zeroes the control block and zero_out[0, nzero).
+int launch_ws_init(WsCtl *ctl, double *zero_out, int nzero, hipStream_t s);
 bool layout_supported(int b0, int b1);
 
 // Merge of sorted test times into the sorted training grid (merge.hip).

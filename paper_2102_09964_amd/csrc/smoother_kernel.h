@@ -45,6 +45,8 @@ struct SmoothParams {
     const double *cst;  // model constants of the transition
     const T *y;             // fused call: the filter's inputs
     const uint8_t *mask;
+    const double *partials; // fused call: the filter's log-likelihood by tiles, and its sum
+    double *loglik;
     const double *hand;     // fused call: the filter's handover (HandLayout)
     const double *bound;
 };
@@ -475,6 +477,12 @@ template <class LY, typename T>
 __global__ __launch_bounds__(PSSGP_WAVE, (fused_waves<LY::D>())) void smoother_fused_kernel(SmoothParams<T> p,
                                                                                           DevModel mdl_arg)
 {
+    // one block more than tiles: the filter's log-likelihood
+    if ((int)blockIdx.x == p.ntiles) {
+        const double s = sum_over_tiles(p.partials, p.ntiles, 1);
+        if (lane_id() == 0) *p.loglik = s;
+        return;
+    }
     __shared__ DevModel mdl;
     model_to_lds(mdl_arg, mdl);
     OneSeries sv;
@@ -508,6 +516,8 @@ int launch_smoother_t(const DevModel &mdl, const SmoothLaunch &a, hipStream_t s)
     p.mask = a.mask;
     p.hand = a.hand;
     p.bound = a.bound;
+    p.partials = a.ws.partials;
+    p.loglik = a.loglik;
     const dim3 grid(a.ntiles), block(PSSGP_WAVE);
     pass_event(a.ev, 0, s);
     if (a.hand) {
@@ -532,7 +542,7 @@ int launch_smoother_t(const DevModel &mdl, const SmoothLaunch &a, hipStream_t s)
     pass_event(a.ev, 2, s);
     const size_t smem = (size_t)2 * PSSGP_WAVE * (a.hand ? a.chunk + 1 : a.chunk) * sizeof(T);
     if (a.hand)
-        hipLaunchKernelGGL((smoother_fused_kernel<LY, T>), grid, block, smem, s, p, mdl);
+        hipLaunchKernelGGL((smoother_fused_kernel<LY, T>), dim3(a.ntiles + 1), block, smem, s, p, mdl);
     else if (a.ms && a.Ps)
         hipLaunchKernelGGL((smoother_finish_kernel<LY, T, true>), grid, block, smem, s, p, mdl);
     else
