@@ -105,9 +105,9 @@ __global__ __launch_bounds__(PSSGP_WAVE) void batched_filter_kernel(FilterParams
             filter_tile_finish<LB, T, double, MODE, ManySeries>(p, mdl, cst, sv, tr, tile, ll);
     } else {
         if (gi == 0)
-            filter_tile_fold<LA, T, T, ManySeries>(p, mdl, cst, sv, tr, tile);
+            filter_tile_fold<LA, T, T, false, ManySeries>(p, mdl, cst, sv, tr, tile);
         else
-            filter_tile_fold<LB, T, T, ManySeries>(p, mdl, cst, sv, tr, tile);
+            filter_tile_fold<LB, T, T, false, ManySeries>(p, mdl, cst, sv, tr, tile);
     }
 }
 

@@ -40,8 +40,8 @@ struct Plan {
 // leaves SIMDs idle while every lane runs its 16 steps one after the other;
 // with fewer steps per lane the chain is shorter on the same number of
 // launches. Measured (FP64, us with 16 / with this rule): filter + smoother,
-// 1 536 steps at d = 2 59 / 39, 131 101 steps at d = 8 1 139 / 955, 300 007
-// steps at d = 6 639 / 524; loglik + gradient, 2 000 steps at d = 6 698 / 531.
+// 1 536 steps at d = 2 59 / 38, 131 101 steps at d = 8 735 / 589, 300 007 steps
+// at d = 6 536 / 455; loglik + gradient, 2 000 steps at d = 6 505 / 303.
 // Below 4 the lane scan and the passes' starts dominate (1, 2 and 4 are within
 // 10 % of each other). In FP32 fewer steps per lane round the lane-start
 // moments more often in FP32, and a default that moved with n would move the
@@ -49,14 +49,28 @@ struct Plan {
 // (or the tuner's). At d = 8 in FP64 the lane records are 76 KB a tile: three
 // quarters of the tiles, so that the calls on the 64 MiB of static scratch
 // fit as they do with 16.
+// At d >= 6 the lane scan has one or two workgroups of d / 2 waves on a CU
+// (LDS), so that its tiles run in rounds of 256 or 512: the chunk is the least
+// that needs no more rounds than 16 steps would (131 101 steps at d = 8: 512
+// tiles of 4 steps a lane 759 us, 257 of 8 703, 228 of 9 in one round 589 us).
 constexpr int kMinDefaultChunk = 4;
 
 int64_t fill_tiles(int d, bool f64) { return (f64 && d >= 8) ? 768 : 1024; }
+int64_t round_tiles(int d) { return d >= 8 ? 256 : (d >= 6 ? 512 : 1024); }
+
+// Tiles that a default-chunk FP64 call of n steps has at most (it has fewer
+// where kMinDefaultChunk steps per lane give fewer, more beyond fill_tiles).
+int64_t most_tiles(int64_t n, int d)
+{
+    const int64_t one = round_tiles(d), rounds = (n + 64 * kDefaultChunk * one - 1) / (64 * kDefaultChunk * one);
+    const int64_t most = one * (rounds > 1 ? rounds : 1), fill = fill_tiles(d, true);
+    return most < fill ? most : fill;
+}
 
 int default_chunk(int64_t n, int d, bool f64)
 {
     if (!f64) return kDefaultChunk;
-    const int64_t lanes = 64 * fill_tiles(d, f64);
+    const int64_t lanes = 64 * most_tiles(n, d);
     const int64_t c = (n + lanes - 1) / lanes;
     return (int)(c < kMinDefaultChunk ? kMinDefaultChunk : (c > kDefaultChunk ? kDefaultChunk : c));
 }
@@ -72,7 +86,7 @@ int chunk_of(const pssgp_options *o, int64_t n, int d, bool f64)
 int64_t alloc_tiles(int64_t ntiles, int64_t n, int d, bool f64, const pssgp_options *o)
 {
     if (!f64 || (o && o->chunk)) return ntiles;
-    const int64_t small = (n + 64 * kMinDefaultChunk - 1) / (64 * kMinDefaultChunk), full = fill_tiles(d, f64);
+    const int64_t small = (n + 64 * kMinDefaultChunk - 1) / (64 * kMinDefaultChunk), full = most_tiles(n, d);
     const int64_t most = small < full ? small : full;
     return ntiles > most ? ntiles : most;
 }

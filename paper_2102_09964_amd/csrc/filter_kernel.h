@@ -24,6 +24,7 @@
 #pragma once
 #include "device_common.h"
 #include "filter_ops.h"
+#include "lane_scan.h"
 #include "launch.h"
 #include "smoother_ops.h"
 #include "tile_scan.h"
@@ -283,10 +284,26 @@ __device__ __forceinline__ void fixed_point_update(const double (&K)[D], double 
     }
 }
 
+// Whether the fold leaves the lane scan to lane_scan_kernel: at d >= 6 in FP64
+// (filter and smoother: 2 000 steps at d = 6 357 -> 272 us, at d = 8 634 -> 379;
+// 131 101 steps at d = 8 890 -> 589 with the chunk chosen for it); in FP32 at
+// d = 8 up to two workgroups a CU (1 000 steps 551 -> 469, 320 000 steps 679 ->
+// 618 us; 2^20 steps 778 -> 821 to 900). There, and at d = 6 in FP32 at any size
+// (1 000 steps 249 -> 264), the workgroup of tile 0 with its FP64 conditioning
+// takes longest, and every wave forming the factors costs more than it saves
+// once the SIMDs are full.
+template <int D, typename T>
+constexpr bool may_split() { return D >= 6 && (sizeof(T) == 8 || D >= 8); }
+template <int D, typename T>
+__host__ __device__ constexpr bool split_lane_scan(int ntiles)
+{
+    return may_split<D, T>() && (sizeof(T) == 8 || ntiles <= 512);
+}
+
 // Fold pass of one tile: each lane folds its chunk into an aggregate, the
 // wave scans the 64 chunk aggregates (inclusive, time order) and stores them
 // at lanep; lane 63 then holds the tile aggregate.
-template <class LY, typename T, typename CT, class SV>
+template <class LY, typename T, typename CT, bool SPLIT, class SV>
 __device__ __forceinline__ void filter_tile_fold(const FilterParams<T> &p, const DevModel &mdl, cdouble *cst,
                                                  SV &sv, const TileRange &tr, int tile)
 {
@@ -328,21 +345,8 @@ __device__ __forceinline__ void filter_tile_fold(const FilterParams<T> &p, const
         in.yc = yn;
         in.oc = on;
     }
-    if constexpr (sizeof(T) == 8 && D >= 6) {
-        // FP64 at d >= 6: the operator reads the predecessor's entries by
-        // shuffles where it uses them (agg_combine_lane); a shuffled copy of
-        // the whole aggregate spilled 3.3 KB per lane at d = 8 and 0.6 KB at
-        // d = 6 (there 272 -> 260 us of the fold at 300 000 steps). (In FP32
-        // the d = 8 scan does not spill that way; there the first tile's FP64
-        // combinations of a series-start prefix made this form slower.)
-        for (int o = 1; o < PSSGP_WAVE; o <<= 1) {
-            const bool other_from_start = __shfl_up((int)from_start, o, PSSGP_WAVE) != 0;
-            const bool on = lane >= o;
-            agg_combine_lane<D, T, double>(agg, o, on);
-            from_start = from_start || (on && other_from_start);
-        }
+    if constexpr (SPLIT) {
         agg_store<D, T>(lane_rec(p.lanep, slot, AGG, lane), agg, PSSGP_WAVE);
-        if (lane == PSSGP_WAVE - 1) agg_store<D, T>(p.aggp + (size_t)slot * AGG, agg);  // tile aggregate
         return;
     }
     for (int o = 1; o < PSSGP_WAVE; o <<= 1) {
@@ -636,8 +640,10 @@ __device__ __forceinline__ void filter_tile_finish(const FilterParams<T> &p, con
     ll_out = ll;
 }
 
-// CT: arithmetic type of the lane scan's combinations
-template <class LY, typename T, typename CT>
+// CT: arithmetic type of the lane scan's combinations. SPLIT: lane_scan_kernel
+// does the lane scan (a template argument: with both in one kernel the fold of
+// 2^20 steps at d = 8 took 150 us more)
+template <class LY, typename T, typename CT, bool SPLIT>
 __global__ __launch_bounds__(PSSGP_WAVE, (fold_waves<LY::D, T>())) void filter_fold_kernel(FilterParams<T> p,
                                                                                         DevModel mdl_arg)
 {
@@ -646,7 +652,7 @@ __global__ __launch_bounds__(PSSGP_WAVE, (fold_waves<LY::D, T>())) void filter_f
     OneSeries sv;
     sv.init(mdl, p.n);
     TileRange tr{0, p.n, p.ntiles, 0};
-    filter_tile_fold<LY, T, CT, OneSeries>(p, mdl, (cdouble *)p.cst, sv, tr, (int)blockIdx.x);
+    filter_tile_fold<LY, T, CT, SPLIT, OneSeries>(p, mdl, (cdouble *)p.cst, sv, tr, (int)blockIdx.x);
 }
 
 template <class LY, typename T, typename CT, int MODE>
@@ -733,7 +739,16 @@ int launch_filter_t(const DevModel &mdl, const FilterLaunch &a, hipStream_t s)
     const dim3 grid(a.ntiles), block(PSSGP_WAVE);
     pass_event(a.ev, 0, s);
     launch_consts<LY, T>(mdl, a.ws.cst, s);
-    hipLaunchKernelGGL((filter_fold_kernel<LY, T, T>), grid, block, 0, s, p, mdl);
+    if constexpr (may_split<LY::D, T>()) {
+        if (split_lane_scan<LY::D, T>(a.ntiles)) {
+            hipLaunchKernelGGL((filter_fold_kernel<LY, T, T, true>), grid, block, 0, s, p, mdl);
+            hipLaunchKernelGGL((lane_scan_kernel<LY::D, T>), grid, dim3(PSSGP_WAVE * LY::D / 2), 0, s, p.lanep, p.aggp);
+        }
+    }
+    if constexpr (!split_lane_scan<LY::D, T>(1 << 30)) {
+        if (!split_lane_scan<LY::D, T>(a.ntiles))
+            hipLaunchKernelGGL((filter_fold_kernel<LY, T, T, false>), grid, block, 0, s, p, mdl);
+    }
     int rc = (int)hipGetLastError();
     if (rc) return rc;
     pass_event(a.ev, 1, s);
