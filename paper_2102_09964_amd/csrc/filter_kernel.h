@@ -601,6 +601,23 @@ __device__ __forceinline__ void filter_tile_finish(const FilterParams<T> &p, con
         // its end moments, the covariance as its Cholesky factor
         SAgg<D, T> sacc;
         sagg_identity<D, T>(sacc);
+        // FP32 up to d = 3: the mean that the next lane enters with (for the
+        // last lane, the next tile's) in place of the lane's own end mean, so
+        // that the lanes meet in the same value. Apart by the rounding of the
+        // FP32 carry, they left f_mean of dense series up to 1.6 times as far
+        // from FP64 as an element per step does; now a fifth of that (merge of
+        // 3e5 steps: 1.0e-6, 1.6e-6, 3.0e-7). The covariance stays the lane's
+        // own: the entering one, in FP32, need not be positive definite in FP64
+        if constexpr (sizeof(T) == 4 && !OVER) {
+            T mn[D];
+#pragma unroll
+            for (int i = 0; i < D; i++) mn[i] = shfl_down_t(m0[i], 1);
+            if (k1 > k0 && !end) {
+                const T *ip = p.inclp + (size_t)(slot + 1) * INCL;
+#pragma unroll
+                for (int i = 0; i < D; i++) m[i] = (double)(lane == PSSGP_WAVE - 1 ? ip[i] : mn[i]);
+            }
+        }
         if (k1 > k0) {
 #pragma unroll
             for (int i = 0; i < D; i++)
