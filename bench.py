@@ -60,6 +60,11 @@ def pass_costs(d, tsize, chunk):
     vector operations count alike, since with packed FP32 disabled both run
     at the same vector rate).
 
+    The costs are those of the scans with a smoother element per step. The
+    fused call forms one element per lane of steps and hands over P h and h m
+    instead (d + 1 FP64 values), so its passes after the fold do less than
+    this and its smoother finish is bound by arithmetic, not by bytes.
+
     Bytes are each kernel's own inputs and outputs: the step inputs
     (t, y, mask), the smoother element of every step that the filter's
     finish pass hands to the smoother (E, g, packed L: d^2 + d + d(d+1)/2
@@ -135,7 +140,7 @@ def algorithmic_bytes(tsize, n):
 
 
 MERGE_SOURCES = ("merge.hip", "launch.h")
-SCAN_SOURCES = ("device_common.h", "filter_kernel.h", "filter_ops.h", "smoother_kernel.h", "smoother_ops.h",
+SCAN_SOURCES = ("device_common.h", "filter_kernel.h", "filter_ops.h", "lane_scan.h", "smoother_kernel.h", "smoother_ops.h",
                 "tile_scan.h", "tile_scan_team.h", "qp_ops.h", "qp_team.h", "launch.h", "model.h", "inst_filter.hip",
                 "inst_smoother.hip")
 GRAD_SOURCES = SCAN_SOURCES + ("grad_kernel.h", "inst_grad.hip")

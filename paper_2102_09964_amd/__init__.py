@@ -702,7 +702,7 @@ class BatchedPipeline:
     kinds: per-series Matern kind (sorted by state size, at most two kinds);
     offsets: int64 [n_series + 1]; params: float64 [n_series, 3] with
     (lengthscale, variance, noise_var) per series. fused=True runs both scans
-    in one pssgp_batched_predict call (smoother elements handed over in the
+    in one pssgp_batched_predict call (the handover in the
     workspace, no filter moments in memory); fused=False runs
     pssgp_batched_filter, keeps m and P, then pssgp_batched_smooth.
     """

@@ -14,10 +14,11 @@
 //           which gives the filter moments just before its chunk, then
 //           re-runs its steps as a plain Kalman filter (prediction and
 //           conditioning in FP64), writing (m, P), the adjoint's records or
-//           the smoother elements, and summing the log-likelihood terms in
+//           the smoother's handover, and summing the log-likelihood terms in
 //           FP64 per lane.
-// One series: the last tile to finish reduces the per-tile log-likelihood
-// partials in a fixed order. Batched: the fold and finish grids cover up to
+// One series: the per-tile log-likelihood partials are summed in a fixed order
+// (last_tile, launch_tile_sums). At d >= 6 the fold's lane scan may be a launch
+// of its own (split_lane_scan). Batched: the fold and finish grids cover up to
 // two groups of series with different state layouts (one carry scan per
 // group) and write one log-likelihood partial per series segment of a lane
 // (at the segment's first step) that a second kernel sums per series.
