@@ -77,8 +77,8 @@ __device__ __forceinline__ int group_of(const BatchLaunch &a, int slot)
 }
 
 // FMODE: what the finish pass writes besides the log-likelihood terms:
-// F_MOMENTS (filter moments), F_SMOOTH (the smoother's handover) or 0
-// (nothing)
+// F_MOMENTS (filter moments), F_ELEMS (smoother elements to the handover at
+// p.elem) or 0 (nothing)
 template <class LA, class LB, typename T, bool FINISH, int FMODE>
 __global__ __launch_bounds__(PSSGP_WAVE) void batched_filter_kernel(FilterParams<T> p, BatchLaunch a)
 {
@@ -111,9 +111,9 @@ __global__ __launch_bounds__(PSSGP_WAVE) void batched_filter_kernel(FilterParams
     }
 }
 
-// FUSED: the finish works from the handover written by the filter of the
-// same call, which has done the fold pass too
-template <class LA, class LB, typename T, bool FINISH, bool FUSED>
+// ELEMS: the smoother elements come from the handover (p.elem) written by the
+// filter of the same call, which has done the fold pass too
+template <class LA, class LB, typename T, bool FINISH, bool ELEMS>
 __global__ __launch_bounds__(PSSGP_WAVE) void batched_smoother_kernel(SmoothParams<T> p, BatchLaunch a)
 {
     __shared__ DevModel mdl;
@@ -133,20 +133,15 @@ __global__ __launch_bounds__(PSSGP_WAVE) void batched_smoother_kernel(SmoothPara
     if constexpr (FINISH) {
         extern __shared__ __align__(16) unsigned char pssgp_dyn_smem[];
         T *s_out = reinterpret_cast<T *>(pssgp_dyn_smem);
-        if constexpr (FUSED) {
-            if (gi == 0)
-                smoother_tile_fused<LA, T, ManySeries>(p, mdl, cst, sv, tr, tile, s_out);
-            else
-                smoother_tile_fused<LB, T, ManySeries>(p, mdl, cst, sv, tr, tile, s_out);
-        } else if (gi == 0)
-            smoother_tile_finish<LA, T, false, ManySeries>(p, mdl, cst, sv, tr, tile, s_out);
+        if (gi == 0)
+            smoother_tile_finish<LA, T, false, ELEMS, ManySeries>(p, mdl, cst, sv, tr, tile, s_out);
         else
-            smoother_tile_finish<LB, T, false, ManySeries>(p, mdl, cst, sv, tr, tile, s_out);
+            smoother_tile_finish<LB, T, false, ELEMS, ManySeries>(p, mdl, cst, sv, tr, tile, s_out);
     } else {
         if (gi == 0)
-            smoother_tile_fold<LA, T, ManySeries>(p, mdl, cst, sv, tr, tile);
+            smoother_tile_fold<LA, T, ELEMS, ManySeries>(p, mdl, cst, sv, tr, tile);
         else
-            smoother_tile_fold<LB, T, ManySeries>(p, mdl, cst, sv, tr, tile);
+            smoother_tile_fold<LB, T, ELEMS, ManySeries>(p, mdl, cst, sv, tr, tile);
     }
 }
 
@@ -204,8 +199,7 @@ int launch_bf(const BatchLaunch &a, hipStream_t s)
     p.aggp = (T *)a.ws.aggp;
     p.lanep = (T *)a.ws.lanep;
     p.partials = a.ws.partials;
-    p.hand = a.hand;
-    p.bound = a.bound;
+    p.elem = (T *)a.elem;
     p.slane = (T *)a.slane;
     const dim3 grid(a.total_tiles), block(PSSGP_WAVE);
     pass_event(a.ev, 0, s);
@@ -234,7 +228,7 @@ int launch_bf(const BatchLaunch &a, hipStream_t s)
     return rc;
 }
 
-template <class LA, class LB, typename T, bool FUSED>
+template <class LA, class LB, typename T, bool ELEMS>
 int launch_bs(const BatchLaunch &a, void *const *ev, hipStream_t s)
 {
     SmoothParams<T> p;
@@ -253,15 +247,15 @@ int launch_bs(const BatchLaunch &a, void *const *ev, hipStream_t s)
     p.aggp = (T *)a.ws.aggp;
     p.lanep = (T *)a.ws.lanep;
     p.cst = a.ws.cst;
-    p.y = (const T *)a.y;
-    p.mask = a.mask;
-    p.hand = a.hand;
-    p.bound = a.bound;
+    p.elem = (const T *)a.elem;
     const dim3 grid(a.total_tiles), block(PSSGP_WAVE);
     pass_event(ev, 0, s);
-    if constexpr (sizeof(T) == 4 && !FUSED)
+    if constexpr (sizeof(T) == 4 && !ELEMS)
         hipLaunchKernelGGL((batched_consts_kernel<LA, LB>), dim3(a.ngroups), dim3(256), 0, s, a);
-    if constexpr (FUSED) {
+    if constexpr (ELEMS) {
+        static_assert(lane_aggregate_handover<LA::D>() && lane_aggregate_handover<LB::D>() &&
+                          !lane_handover(LA::D, sizeof(T) == 8) && !lane_handover(LB::D, sizeof(T) == 8),
+                      "the batched form hands over an element per step and the lanes' aggregates");
         // the filter's finish pass of the same call did the fold pass (lane
         // records at slane, tile aggregates at aggp)
         p.lanep = (T *)a.slane;
@@ -280,8 +274,8 @@ int launch_bs(const BatchLaunch &a, void *const *ev, hipStream_t s)
         if (rc) return rc;
     }
     pass_event(ev, 2, s);
-    const size_t smem = (size_t)2 * PSSGP_WAVE * (FUSED ? a.chunk + 1 : a.chunk) * sizeof(T);
-    hipLaunchKernelGGL((batched_smoother_kernel<LA, LB, T, true, FUSED>), grid, block, smem, s, p, a);
+    const size_t smem = (size_t)2 * PSSGP_WAVE * a.chunk * sizeof(T);
+    hipLaunchKernelGGL((batched_smoother_kernel<LA, LB, T, true, ELEMS>), grid, block, smem, s, p, a);
     rc = (int)hipGetLastError();
     pass_event(ev, 3, s);
     return rc;
@@ -290,7 +284,7 @@ int launch_bs(const BatchLaunch &a, void *const *ev, hipStream_t s)
 template <class LA, class LB, typename T>
 int launch_bp(const BatchLaunch &a, hipStream_t s)
 {
-    int rc = launch_bf<LA, LB, T, F_SMOOTH>(a, s);
+    int rc = launch_bf<LA, LB, T, F_ELEMS>(a, s);
     if (rc) return rc;
     return launch_bs<LA, LB, T, true>(a, a.ev ? a.ev + 4 : nullptr, s);
 }

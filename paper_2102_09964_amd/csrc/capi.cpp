@@ -27,7 +27,7 @@ struct Plan {
     size_t off_incl2 = 0, off_lane2 = 0, off_part2 = 0, off_agg2 = 0;
     size_t off_x = 0, off_xraw = 0;  // plain baseline element arrays
     size_t off_gagg = 0, off_gcarry = 0;  // carry pass group scratch
-    size_t off_hand = 0, off_bound = 0;  // predict: filter-to-smoother handover (steps, lane ends)
+    size_t off_elem = 0, off_hand = 0, off_bound = 0;  // predict: filter-to-smoother handover (lane_handover)
     size_t off_fagg2 = 0;            // second buffer of filter tile aggregates (team carry)
     size_t off_slane = 0;            // predict: the smoother's lane records
     size_t total = 0;
@@ -147,15 +147,20 @@ Plan make_plan(int d, int ncomp, int64_t n, pssgp_dtype dtype, int op, const pss
     }
     if (op == PSSGP_OP_PREDICT) {
         // filter then smoother on one stream: the scans share their regions
-        // (the filter's are the larger); the handover is FP64 whatever the
-        // scan type (HandLayout; d > 3 in FP32: lane_overlap)
+        // (the filter's are the larger); the handover holds the smoother
+        // elements of every step in the tile layout (elem_index), or FP64
+        // values per step and lane (HandLayout, chunk + 1 steps a lane)
         p.off_incl = take(nt * filter_incl_elems(d) * p.tsize);
         p.off_agg = take(nt * filter_agg_elems(d) * p.tsize);
         p.off_fagg2 = take(nt * filter_agg_elems(d) * p.tsize);
         p.off_lane = take(nt * 64 * filter_agg_elems(d) * p.tsize);
         p.off_part = take(nt * sizeof(double) * n_params(ncomp));
-        p.off_hand = take((steps + (p.tsize == 4 && d > 3 ? nt * 64 : 0)) * (d + 1) * sizeof(double));
-        p.off_bound = take(nt * 64 * (size_t)smooth_incl_elems(d) * sizeof(double));
+        if (lane_handover(d, f64)) {
+            p.off_hand = take((steps + nt * 64) * (d + 1) * sizeof(double));
+            p.off_bound = take(nt * 64 * (size_t)smooth_incl_elems(d) * sizeof(double));
+        } else {
+            p.off_elem = take(steps * smooth_agg_elems(d) * p.tsize);
+        }
         p.off_slane = take(nt * 64 * (size_t)smooth_agg_elems(d) * p.tsize);
         p.total = off;
         return p;
@@ -319,7 +324,7 @@ struct BatchPlan {
     BatchGroup g[2];
     BatchModel bm[2];
     size_t off_incl = 0, off_lane = 0, off_part = 0, off_terms = 0, off_cst = 0, off_agg = 0, total = 0;
-    size_t off_gagg = 0, off_gcarry = 0, off_hand = 0, off_bound = 0, off_slane = 0;
+    size_t off_gagg = 0, off_gcarry = 0, off_elem = 0, off_slane = 0;
 };
 
 int make_batch_plan(const pssgp_batch_group *groups, int ngroups, int64_t n_series, const int64_t *off,
@@ -425,11 +430,10 @@ int make_batch_plan(const pssgp_batch_group *groups, int ngroups, int64_t n_seri
     bp.off_cst = take(2 * PSSGP_CONST_DOUBLES * sizeof(double));
     if (op != PSSGP_OP_SMOOTH) bp.off_terms = take((size_t)(n > 0 ? n : 1) * sizeof(double));
     if (op == PSSGP_OP_PREDICT) {
-        // the handover (HandLayout); the slots of the second group (larger
-        // state) start past the first group's values because the groups
-        // ascend in state size
-        bp.off_hand = take(steps * (d + 1) * sizeof(double));
-        bp.off_bound = take(nt * 64 * (size_t)smooth_incl_elems(d) * sizeof(double));
+        // smoother elements of every step in the tile layout; the slots of
+        // the second group (larger state) start past the first group's
+        // elements because the groups ascend in state size
+        bp.off_elem = take(steps * smooth_agg_elems(d) * bp.tsize);
         bp.off_slane = take(nt * 64 * (size_t)smooth_agg_elems(d) * bp.tsize);
     }
     bp.total = o;
@@ -499,8 +503,7 @@ int run_batched(const pssgp_batch_group *groups, int ngroups, int64_t n_series, 
     a.ws.cst = (double *)(b + bp.off_cst);
     a.ws.agg2 = nullptr;
     if (op == PSSGP_OP_PREDICT) {
-        a.hand = (double *)(b + bp.off_hand);
-        a.bound = (double *)(b + bp.off_bound);
+        a.elem = b + bp.off_elem;
         a.slane = b + bp.off_slane;
     }
     const bool zero_ll = (op != PSSGP_OP_SMOOTH && a.n == 0);
@@ -892,6 +895,8 @@ int pssgp_predict(const pssgp_model *model, const double *t, const void *y, cons
     a.P = nullptr;
     a.loglik = loglik;
     a.rec = nullptr;
+    a.fused = 1;
+    a.elem = b + p.off_elem;
     a.hand = (double *)(b + p.off_hand);
     a.bound = (double *)(b + p.off_bound);
     a.slane = b + p.off_slane;
@@ -901,15 +906,17 @@ int pssgp_predict(const pssgp_model *model, const double *t, const void *y, cons
     SmoothLaunch sm{};
     sm.ev = opts ? opts->pass_events + 4 : nullptr;
     sm.t = t;
-    sm.y = y;
-    sm.mask = mask;
+    sm.fused = 1;
     sm.n = n;
     sm.chunk = p.chunk;
     sm.ntiles = p.ntiles;
     sm.f_mean = f_mean;
     sm.f_var = f_var;
+    sm.elem = a.elem;
     sm.hand = a.hand;
     sm.bound = a.bound;
+    sm.y = y;
+    sm.mask = mask;
     sm.loglik = loglik;
     sm.slane = b + p.off_slane;
     sm.ws = sw;

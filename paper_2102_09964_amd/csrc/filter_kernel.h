@@ -33,9 +33,12 @@
 
 // Finish-pass outputs: filter moments in the [entry][n] layout, per-step
 // records for the adjoint (RecLayout, tile layout), or what the smoother of
-// the same call needs (HandLayout: per-step predicted P h and h m, the lanes'
-// end moments and smoother elements).
-enum : int { F_MOMENTS = 1, F_RECS = 2, F_SMOOTH = 4 };
+// the same call needs: its elements step by step (elem_index), or per-step
+// predicted P h and h m, the lanes' end moments and smoother elements
+// (HandLayout).
+enum : int { F_MOMENTS = 1, F_RECS = 2, F_ELEMS = 4, F_LANES = 8 };
+template <int D, typename T>
+constexpr int fused_mode() { return lane_handover(D, sizeof(T) == 8) ? F_LANES : F_ELEMS; }
 
 template <typename T>
 struct FilterParams {
@@ -57,9 +60,10 @@ struct FilterParams {
     T *inclp;
     T *lanep;
     double *partials;
-    double *hand;   // F_SMOOTH: per-step handover to the smoother (HandLayout)
-    double *bound;  // F_SMOOTH: end moments of the lanes (HandLayout)
-    T *slane;       // F_SMOOTH: the smoother's lane records
+    T *elem;        // F_ELEMS: smoother element of every step (elem_index)
+    double *hand;   // F_LANES: per-step handover to the smoother (HandLayout)
+    double *bound;  // F_LANES: end moments of the lanes (HandLayout)
+    T *slane;       // F_ELEMS (lane_aggregate_handover), F_LANES: the smoother's lane records
 };
 
 // Tile geometry: steps [k_begin, k_end) split into ntiles tiles; workspace
@@ -115,6 +119,96 @@ struct StepInputs {
         }
     }
 };
+
+// Smoother element of step k (supplement, Proposition 2), built by the
+// filter right after predicting step k + 1, from what that prediction
+// already holds: the filtered moments (m, P) of step k and, in FP64,
+// Y = F P, mp = F m and Pp = F P F^T + Q of step k + 1:
+//   Pp = C C^T (Cholesky), Y = C^-1 F P, L = P - Y^T Y,
+//   E = (C^-T Y)^T = P F^T Pp^-1, g = m - E mp.
+// At the last step of a series the caller passes the prior transition
+// (F = 0, Q = Pinf), for which these give exactly the element (0, m, P).
+// e receives the element rounded to T, in the smoother's coordinates
+// z' = S z, S = I + e_0 e_B^T (smoother_shear_col; B = 0: identity).
+// (m, P) come in U (the filter carries them in FP64).
+template <int D, int B, typename T, typename U = T>
+__device__ __forceinline__ void smoother_element_from_prediction(const U (&m)[D], const U (&P)[D][D],
+                                                                 double (&Y)[D][D], const double (&mp)[D],
+                                                                 const double (&Pp)[D][D], SAgg<D, T> &e,
+                                                                 uint32_t &bad)
+{
+    // Y holds F P on entry and is overwritten
+    double C[D][D];
+#pragma unroll
+    for (int i = 0; i < D; i++)
+#pragma unroll
+        for (int j = 0; j <= i; j++) C[i][j] = Pp[i][j];
+    double rd[D];  // reciprocals of the Cholesky diagonal
+    if (!cholesky<D, double>(C, rd)) bad |= PSSGP_STATUS_CHOLESKY;
+#pragma unroll
+    for (int j = 0; j < D; j++)
+#pragma unroll
+        for (int i = 0; i < D; i++) {
+            double acc = Y[i][j];
+#pragma unroll
+            for (int q = 0; q < i; q++) acc = fma(-C[i][q], Y[q][j], acc);
+            Y[i][j] = acc * rd[i];
+        }
+    // L' = S P S^T - (Y S^T)^T (Y S^T); Y S^T is column 0 plus column B
+    if constexpr (B > 0) {
+#pragma unroll
+        for (int q = 0; q < D; q++) Y[q][0] += Y[q][B];
+    }
+#pragma unroll
+    for (int i = 0; i < D; i++)
+#pragma unroll
+        for (int j = i; j < D; j++) {
+            double acc = (double)P[i][j];
+            if constexpr (B > 0) {
+                if (i == 0) acc += (double)P[B][j] + (j == 0 ? (double)P[0][B] + (double)P[B][B] : 0.0);
+            }
+#pragma unroll
+            for (int q = 0; q < D; q++) acc = fma(-Y[q][i], Y[q][j], acc);
+            e.L[i][j] = T(acc);
+            e.L[j][i] = e.L[i][j];
+        }
+#pragma unroll
+    for (int j = 0; j < D; j++)
+#pragma unroll
+        for (int i = D - 1; i >= 0; i--) {
+            double acc = Y[i][j];
+#pragma unroll
+            for (int q = i + 1; q < D; q++) acc = fma(-C[q][i], Y[q][j], acc);
+            Y[i][j] = acc * rd[i];
+        }
+    // Y = (S E)^T: g' = S m - (S E) mp, E' = (S E) S^-1 (column B minus column 0)
+#pragma unroll
+    for (int i = 0; i < D; i++) {
+        double acc = (double)m[i];
+        if constexpr (B > 0) {
+            if (i == 0) acc += (double)m[B];
+        }
+#pragma unroll
+        for (int q = 0; q < D; q++) acc = fma(-Y[q][i], mp[q], acc);
+        e.g[i] = T(acc);
+#pragma unroll
+        for (int j = 0; j < D; j++) e.E[i][j] = T((B > 0 && j == B) ? Y[B][i] - Y[0][i] : Y[j][i]);
+    }
+}
+
+// The smoother element of a step is handed over (stored in the tile layout
+// with non-temporal stores: it is read back only after the whole filter, and
+// with ordinary stores the caches fetched every line before writing it,
+// which doubled the pass's HBM traffic) and, where the smoother takes lane
+// aggregates from the filter
+// (lane_aggregate_handover), also appended to the lane's running smoother
+// aggregate: acc <- acc (x) e (acc covers the lane's earlier steps).
+template <int D, typename T, bool LANEAGG>
+__device__ __forceinline__ void hand_over_element(const SAgg<D, T> &e, T *out, SAgg<D, T> &acc)
+{
+    sagg_store_nt<D, T>(out, e, PSSGP_WAVE);
+    if constexpr (LANEAGG) sagg_combine<D, T>(acc, e, acc);
+}
 
 // Smoother element of a lane: the map from the smoothed moments of the lane's
 // last step to those of the step before its first one (supplement,
@@ -401,9 +495,12 @@ __device__ __forceinline__ void filter_tile_finish(const FilterParams<T> &p, con
     for (int i = 0; i < D; i++) h[i] = T(LY::hobs(i));
     uint32_t bad = 0;
 
-    constexpr bool SMOOTH = (MODE & F_SMOOTH) != 0;
-    constexpr bool OVER = SMOOTH && lane_overlap<D, T>() > 0;
-    using HL = HandLayout<D, T>;
+    constexpr bool ELEMS = (MODE & F_ELEMS) != 0, LANES = (MODE & F_LANES) != 0;
+    using HL = HandLayout<D>;
+    // smoother lane aggregate accumulated from the handed-over elements
+    constexpr bool LANEAGG = ELEMS && lane_aggregate_handover<D>();
+    SAgg<D, T> sacc;
+    if constexpr (LANEAGG || LANES) sagg_identity<D, T>(sacc);
 
     T m0[D], P0[D][D];
     moments_load<D, T>(p.inclp + (size_t)slot * INCL, m0, P0);
@@ -426,10 +523,10 @@ __device__ __forceinline__ void filter_tile_finish(const FilterParams<T> &p, con
 #pragma unroll
         for (int j = 0; j < D; j++) P[i][j] = (double)P0[i][j];
     }
-    // fixed-point smoother of the state before the lane (of its first step with
-    // OVER; lane_smoother_element)
+    // fixed-point smoother of the lane's first step (lane_smoother_element),
+    // set at the end of that step
     double fm[D], fP[D][D], fG[D][D];
-    if constexpr (SMOOTH) {
+    if constexpr (LANES) {
 #pragma unroll
         for (int i = 0; i < D; i++) {
             fm[i] = m[i];
@@ -451,17 +548,14 @@ __device__ __forceinline__ void filter_tile_finish(const FilterParams<T> &p, con
     const OptInputs opt(p.mask, p.noise_k, p.t);
     // a series that ends with the lane: the fixed-point smoother has seen all
     // its observations (E = 0), and there is no step after to end the run with
-    bool end = false;
-    if constexpr (SMOOTH) {
-        if (k1 > k0) {
-            SV se = sv;
-            se.seek(k1 - 1);
-            end = (k1 >= tr.k_end) || se.last(k1 - 1);
-        }
-    }
-    const int64_t ke = (OVER && k1 > k0 && !end) ? k1 + 1 : k1;
+    const bool end = k1 >= tr.k_end;
+    static_assert(!LANES || !SEG, "a run over series starts");
+    const int64_t ke = (LANES && k1 > k0 && !end) ? k1 + 1 : k1;
     for (int64_t k = k0; k < ke; k++) {
-        const int64_t kn = (k + 1 < ke) ? k + 1 : k;
+        // (F_ELEMS: the last step of the lane loads the time of the next lane's
+        // first step, which its smoother element needs after the loop: no load
+        // after the loop waits behind the element stores)
+        const int64_t kn = (k + 1 < (ELEMS ? tr.k_end : ke)) ? k + 1 : k;
         const double tn = p.t[kn];
         const T yn = p.y[kn];
         const bool on = opt.observed(kn);
@@ -485,17 +579,25 @@ __device__ __forceinline__ void filter_tile_finish(const FilterParams<T> &p, con
         // predict in FP64 (mp = F m, Y = F P, Pp = F P F^T + Q)
         double mp[D], Y[D][D], Pp[D][D];
         predict_step<D, double, Sparsity<LY>>(m, P, Dl, Q, mp, Y, Pp);
-        // (with OVER, the fixed-point smoother of the lane's first step is
-        // overwritten below; a branch around it costs 5 % of the call at d = 6
-        // and gains 2 % at d = 8)
-        const bool fixed = !(OVER && D > 6) || k > k0;
-        if constexpr (SMOOTH) {
-            if (fixed) fixed_point_predict<D, Sparsity<LY>>(Dl, fG);
+        // (the fixed-point smoother of the lane's first step is overwritten
+        // below; a branch around it costs 5 % of the call at d = 6 and gains 2 %
+        // at d = 8)
+        if constexpr (LANES) {
+            if (D <= 6 || k > k0) fixed_point_predict<D, Sparsity<LY>>(Dl, fG);
         }
         // the loads of this iteration are waited for here, before the
         // handover stores: the wait counter is in order, so a wait after
         // the stores would also wait for all of them
         asm volatile("" ::"v"(tn), "v"(yn), "v"((int)on), "v"(Rk));
+        if constexpr (ELEMS) {
+            // smoother element of the previous step of this lane
+            if (k > k0) {
+                SAgg<D, T> e;
+                smoother_element_from_prediction<D, smoother_shear_col<LY>(), T, double>(m, P, Y, mp, Pp, e, bad);
+                hand_over_element<D, T, LANEAGG>(e, p.elem + elem_index<D>(slot, p.chunk, (int)(k - 1 - k0), lane),
+                                                 sacc);
+            }
+        }
         // conditioning on y_k in FP64 (symmetric form): the subtraction
         // that cancels when the noise is small against the predicted
         // variance is done in FP64
@@ -525,7 +627,7 @@ __device__ __forceinline__ void filter_tile_finish(const FilterParams<T> &p, con
             lg = (double)__builtin_amdgcn_logf((float)(6.283185307179586 * S)) * 0.6931471805599453;
         else
             lg = log(6.283185307179586 * S);
-        const double term = (obs && (!OVER || k < k1)) ? -0.5 * (lg + v * v * w) : 0.0;
+        const double term = (obs && (!LANES || k < k1)) ? -0.5 * (lg + v * v * w) : 0.0;
         if constexpr (SEG) {
             if (first && k > k0) {
                 if (p.ll_terms) p.ll_terms[seg_k] = seg;
@@ -534,13 +636,13 @@ __device__ __forceinline__ void filter_tile_finish(const FilterParams<T> &p, con
             }
             seg += term;
         } else {
-            if (p.ll_terms && (!OVER || k < k1)) p.ll_terms[k] = term;
+            if (p.ll_terms && (!LANES || k < k1)) p.ll_terms[k] = term;
         }
         ll += term;
         double K[D];
 #pragma unroll
         for (int i = 0; i < D; i++) K[i] = Ph[i] * w;
-        if constexpr (SMOOTH) {
+        if constexpr (LANES) {
             // non-temporal: read back by the smoother after all of it is written
             double *hp = p.hand + HL::step(slot, p.chunk, (int)(k - k0), lane);
 #pragma unroll
@@ -576,9 +678,8 @@ __device__ __forceinline__ void filter_tile_finish(const FilterParams<T> &p, con
                 P[i][j] = c;
                 P[j][i] = c;
             }
-        if constexpr (OVER) {
-            // from here on (a branch around the lane's first step above costs
-            // 5 % of the call at d = 6)
+        if constexpr (LANES) {
+            // from here on
             if (k == k0) {
 #pragma unroll
                 for (int i = 0; i < D; i++) {
@@ -597,28 +698,26 @@ __device__ __forceinline__ void filter_tile_finish(const FilterParams<T> &p, con
                 for (int j = i; j < D; j++) p.P[(size_t)sidx<D>(i, j) * p.n + k] = T(P[i][j]);
         }
     }
-    if constexpr (SMOOTH) {
+    if constexpr (ELEMS) {
+        // element of the lane's last step: predict the next step (the first of
+        // the next lane), or take the prior transition at a series end
+        if (k1 > k0) {
+            sv.seek(k1 - 1);
+            const bool last = end || sv.last(k1 - 1);
+            const double dt = last ? 0.0 : in.tc - in.tp;  // t[k1] - t[k1 - 1]
+            cdouble *c = cst;
+            PSSGP_LAUNDER(c);
+            double Dl[D][D], Q[D][D], mp[D], Y[D][D], Pp[D][D];
+            step_transition<LY, double, T>(mdl, c, sv.sc, dt, last, Dl, Q);
+            predict_step<D, double, Sparsity<LY>>(m, P, Dl, Q, mp, Y, Pp);
+            SAgg<D, T> e;
+            smoother_element_from_prediction<D, smoother_shear_col<LY>(), T, double>(m, P, Y, mp, Pp, e, bad);
+            hand_over_element<D, T, LANEAGG>(e, p.elem + elem_index<D>(slot, p.chunk, (int)(k1 - 1 - k0), lane), sacc);
+        }
+    }
+    if constexpr (LANES) {
         // the lane's smoother element (identity for a lane without steps) and
         // its end moments, the covariance as its Cholesky factor
-        SAgg<D, T> sacc;
-        sagg_identity<D, T>(sacc);
-        // FP32 up to d = 3: the mean that the next lane enters with (for the
-        // last lane, the next tile's) in place of the lane's own end mean, so
-        // that the lanes meet in the same value. Apart by the rounding of the
-        // FP32 carry, they left f_mean of dense series up to 1.6 times as far
-        // from FP64 as an element per step does; now a fifth of that (merge of
-        // 3e5 steps: 1.0e-6, 1.6e-6, 3.0e-7). The covariance stays the lane's
-        // own: the entering one, in FP32, need not be positive definite in FP64
-        if constexpr (sizeof(T) == 4 && !OVER) {
-            T mn[D];
-#pragma unroll
-            for (int i = 0; i < D; i++) mn[i] = shfl_down_t(m0[i], 1);
-            if (k1 > k0 && !end) {
-                const T *ip = p.inclp + (size_t)(slot + 1) * INCL;
-#pragma unroll
-                for (int i = 0; i < D; i++) m[i] = (double)(lane == PSSGP_WAVE - 1 ? ip[i] : mn[i]);
-            }
-        }
         if (k1 > k0) {
 #pragma unroll
             for (int i = 0; i < D; i++)
@@ -635,21 +734,21 @@ __device__ __forceinline__ void filter_tile_finish(const FilterParams<T> &p, con
                     bp[(D + sidx<D>(j, i)) * PSSGP_WAVE] = (i == j) ? rd[i] : C[i][j];
             }
         }
-        // the smoother's fold pass over this tile: the wave scans the lanes'
-        // elements as suffixes (inclusive, reverse time order) into the lane
-        // records at slane, and lane 0 stores the tile aggregate in the scan
-        // region the two scans share (the filter's carry has consumed it);
-        // with smoother_by_rows a launch of its own does that scan
+    }
+    if constexpr (LANEAGG || LANES) {
+        // the smoother's fold pass over this tile, done here: the wave scans
+        // the lanes' smoother aggregates (identity for a lane without steps)
+        // as suffixes (inclusive, reverse time order) into the lane records
+        // at slane, and lane 0 stores the tile aggregate in the scan region
+        // the two scans share (the filter's carry has consumed it)
         constexpr int SAGG = SAggLayout<D>::SIZE;
-        if constexpr (!smoother_by_rows<D, T>()) {
-            for (int o = 1; o < PSSGP_WAVE; o <<= 1) {
-                SAgg<D, T> other;
-                sagg_shfl_down<D, T>(sacc, other, o);
-                if (lane + o < PSSGP_WAVE) sagg_combine<D, T>(sacc, other, sacc);
-            }
-            if (lane == 0) sagg_store<D, T>(p.aggp + (size_t)slot * SAGG, sacc);
+        for (int o = 1; o < PSSGP_WAVE; o <<= 1) {
+            SAgg<D, T> other;
+            sagg_shfl_down<D, T>(sacc, other, o);
+            if (lane + o < PSSGP_WAVE) sagg_combine<D, T>(sacc, other, sacc);
         }
         sagg_store<D, T>(lane_rec(p.slane, slot, SAGG, lane), sacc, PSSGP_WAVE);
+        if (lane == 0) sagg_store<D, T>(p.aggp + (size_t)slot * SAGG, sacc);
     }
     if constexpr (SEG) {
         if (p.ll_terms && k1 > k0) p.ll_terms[seg_k] = seg;
@@ -688,11 +787,11 @@ __global__ __launch_bounds__(PSSGP_WAVE, (finish_waves<LY::D, T>())) void filter
     filter_tile_finish<LY, T, CT, MODE, OneSeries>(p, mdl, (cdouble *)p.cst, sv, tr, tile, ll);
 
     // log-likelihood: deterministic wave sum, tile partial; the partials are
-    // summed in a fixed order here, by the smoother of the same call (F_SMOOTH)
-    // or by launch_tile_sums
+    // summed in a fixed order here, by the smoother of the same call or by
+    // launch_tile_sums
     const double tot = wave_sum(ll);
     if (lane == 0) p.partials[tile] = tot;
-    if constexpr (!(MODE & F_SMOOTH)) {
+    if constexpr (!(MODE & (F_ELEMS | F_LANES))) {
         if (p.ntiles <= LAST_TILES && last_tile(p.ctl, p.ntiles)) {
             const double s = sum_over_tiles(p.partials, p.ntiles, 1);
             if (lane == 0) *p.loglik = s;
@@ -744,6 +843,7 @@ FilterParams<T> filter_params(const FilterLaunch &a)
     p.aggp = (T *)a.ws.aggp;
     p.lanep = (T *)a.ws.lanep;
     p.partials = a.ws.partials;
+    p.elem = (T *)a.elem;
     p.hand = a.hand;
     p.bound = a.bound;
     p.slane = (T *)a.slane;
@@ -787,8 +887,8 @@ int launch_filter_t(const DevModel &mdl, const FilterLaunch &a, hipStream_t s)
         pass_event(a.ev, 2, s);
         // lane-start moments (the lane's exclusive prefix applied to the
         // tile's carry, once per lane) in FP64
-        if (a.hand)
-            hipLaunchKernelGGL((filter_finish_kernel<LY, T, double, F_SMOOTH>), grid, block, 0, s, p, mdl);
+        if (a.fused)
+            hipLaunchKernelGGL((filter_finish_kernel<LY, T, double, fused_mode<LY::D, T>()>), grid, block, 0, s, p, mdl);
         else if (a.m)
             hipLaunchKernelGGL((filter_finish_kernel<LY, T, double, F_MOMENTS>), grid, block, 0, s, p, mdl);
         else
@@ -797,7 +897,7 @@ int launch_filter_t(const DevModel &mdl, const FilterLaunch &a, hipStream_t s)
     rc = (int)hipGetLastError();
     if (rc) return rc;
     // (the gradient call sums both its passes after the second)
-    if (!a.hand && !a.rec && a.ntiles > LAST_TILES) rc = launch_tile_sums(a.ws.partials, a.loglik, nullptr, nullptr, 0, a.ntiles, s);
+    if (!a.fused && !a.rec && a.ntiles > LAST_TILES) rc = launch_tile_sums(a.ws.partials, a.loglik, nullptr, nullptr, 0, a.ntiles, s);
     pass_event(a.ev, 3, s);
     return rc;
 }

@@ -18,6 +18,22 @@ struct WsCtl {
 #define PSSGP_LAYOUTS(X) X(1, 0) X(2, 0) X(3, 0) X(4, 0) X(6, 0) X(2, 6) X(1, 2)
 #endif
 
+// What the filter of a fused call hands to its smoother: an element per lane
+// and, per step, P h and h m (true), or a smoother element per step. The first
+// moves less and takes fewer instructions (FP32, 2^22 steps at d = 6: filter
+// finish + smoother 473 + 167 us with an element per step, 313 + 185 us), but
+// inside a lane it carries the smoothed moments as P^-1 (P - P^s) P^-1, whose
+// rounding is that of its largest entry: where the filtered covariance falls
+// far below the one at another step of the lane, or is nearly singular along f,
+// f_var loses digits that the covariance itself has. In FP64 those are the
+// digits that the type is chosen for (Matern-3/2 + RBF-6, gaps of a
+// length-scale, noise variance 1e-12: 2e-9 against 8e-15), so FP64 takes an
+// element per step. So does FP32 up to d = 3, where the lanes, joined by FP32
+// moments, lost more than that (Matern-1/2 + Matern-3/2, noise variance 1e-6:
+// 2e-2 against 1e-7) and the gain of the filter was the smoother's loss (4 096
+// series: finish 1.17 -> 0.91, smoother 0.56 -> 0.81 ms).
+constexpr bool lane_handover(int d, bool f64) { return !f64 && d > 3; }
+
 // Room for the constants of the transition of one model in the
 // workspace, in doubles (8 KB).
 #define PSSGP_CONST_DOUBLES 1024
@@ -48,9 +64,11 @@ struct FilterLaunch {
     void *P;         // nullable
     double *loglik;  // nullable
     void *rec;       // nullable: per-step records of the adjoint (tile layout)
-    double *hand;    // nullable: fused call, per-step handover to the smoother (HandLayout; m, P unused)
-    double *bound;   // hand: the lanes' end moments
-    void *slane;     // hand: the smoother's lane records
+    int fused;       // hand over to the smoother of the same call (m, P unused): by lane_handover,
+    void *elem;      //   an element per step (tile layout), or
+    double *hand;    //   the per-step handover (HandLayout) and
+    double *bound;   //   the lanes' end moments
+    void *slane;     // fused: the smoother's lane records
     ScanWs ws;
 };
 
@@ -66,12 +84,14 @@ struct SmoothLaunch {
     void *f_var;
     void *ms;  // nullable
     void *Ps;  // nullable
+    int fused;            // what the filter's finish wrote (m, P unused)
+    const void *elem;
+    const double *hand;
+    const double *bound;
     const void *y;        // hand: the filter's observations
     const uint8_t *mask;  // hand: their mask (nullable)
-    const double *hand;   // nullable: fused call, what the filter's finish wrote (m, P unused)
-    const double *bound;
     void *slane;
-    double *loglik;       // hand: receives the sum of the filter's partials
+    double *loglik;       // fused: receives the sum of the filter's partials
     ScanWs ws;
 };
 
@@ -130,9 +150,8 @@ struct BatchLaunch {
     void *f_var;
     double *loglik;           // device [n_series]
     void *ll_terms;           // workspace [n]: log-likelihood partials at segment starts
-    double *hand;             // nullable: filter then smoother in one call, the handover (HandLayout)
-    double *bound;
-    void *slane;              // hand: the smoother's lane records (written by the filter's finish)
+    void *elem;               // nullable: filter then smoother in one call, an element per step (tile layout)
+    void *slane;              // elem: the smoother's lane records (written by the filter's finish)
     ScanWs ws;
 };
 
@@ -140,7 +159,7 @@ int launch_batched_filter(const BatchLaunch &a, bool f64, hipStream_t s);
 // the filter without moment outputs (log-likelihood only)
 int launch_batched_loglik(const BatchLaunch &a, bool f64, hipStream_t s);
 int launch_batched_smooth(const BatchLaunch &a, bool f64, hipStream_t s);
-// filter writing the handover, then the smoother reading it (a.hand;
+// filter writing the handover, then the smoother reading it (a.elem;
 // a.ev, when set, holds 8 events: filter passes, then smoother passes)
 int launch_batched_predict(const BatchLaunch &a, bool f64, hipStream_t s);
 

@@ -43,12 +43,13 @@ struct SmoothParams {
     T *inclp;
     T *lanep;
     const double *cst;  // model constants of the transition
-    const T *y;             // fused call: the filter's inputs
-    const uint8_t *mask;
-    const double *partials; // fused call: the filter's log-likelihood by tiles, and its sum
+    const double *partials;  // fused call: the filter's log-likelihood by tiles, and its sum
     double *loglik;
-    const double *hand;     // fused call: the filter's handover (HandLayout)
+    const T *elem;           // fused call, an element per step (elem_index)
+    const double *hand;      // fused call, an element per lane (HandLayout) and
     const double *bound;
+    const T *y;              //   the filter's inputs
+    const uint8_t *mask;
 };
 
 struct STileRange {
@@ -61,7 +62,7 @@ struct STileRange {
 // right, the wave scans the 64 chunk aggregates as suffixes (inclusive,
 // reverse time order) and stores them at lanep; lane 0 then holds the tile
 // aggregate.
-template <class LY, typename T, class SV>
+template <class LY, typename T, bool ELEMS, class SV>
 __device__ __forceinline__ void smoother_tile_fold(const SmoothParams<T> &p, const DevModel &mdl,
                                                    cdouble *cst, SV &sv, const STileRange &tr, int tile)
 {
@@ -75,14 +76,19 @@ __device__ __forceinline__ void smoother_tile_fold(const SmoothParams<T> &p, con
     uint32_t bad = 0;  // reported by the finish pass
     SAgg<D, T> agg;
     sagg_identity<D, T>(agg);
-    // (a fused call has its fold pass done by the filter's finish pass)
+    // (a fused call with lane aggregates has its fold pass done by the
+    // filter's finish pass and does not launch this one)
     for (int64_t k = k1 - 1; k >= k0; k--) {
         if constexpr (reload_constants<D>()) PSSGP_RELOAD_CONSTANTS();
         sv.seek(k);
         SAgg<D, T> e;
-        cdouble *c = cst;
-        if constexpr (reload_constants<D>()) PSSGP_LAUNDER(c);
-        smoother_element<LY, T, SV>(mdl, c, sv, p.t, p.m + k, p.P + k, (size_t)p.n, k, e, bad);
+        if constexpr (ELEMS) {
+            sagg_load_nt<D, T>(p.elem + elem_index<D>(slot, p.chunk, (int)(k - k0), lane), e, PSSGP_WAVE);
+        } else {
+            cdouble *c = cst;
+            if constexpr (reload_constants<D>()) PSSGP_LAUNDER(c);
+            smoother_element<LY, T, SV>(mdl, c, sv, p.t, p.m + k, p.P + k, (size_t)p.n, k, e, bad);
+        }
         sagg_combine<D, T>(e, agg, agg);
     }
     if constexpr (smoother_by_rows<D, T>()) {
@@ -102,7 +108,15 @@ __device__ __forceinline__ void smoother_tile_fold(const SmoothParams<T> &p, con
 // Finish pass of one tile: each lane takes the smoothed moments entering
 // the tile from the right (carry pass), applies its exclusive lane suffix
 // and runs the backward RTS recursion over its chunk.
-template <class LY, typename T, bool FULL, class SV>
+// Steps whose handed-over elements it loads ahead of their use, per group
+// (small states only: their per-step work is short against a load's latency).
+template <int D>
+constexpr int smoother_prefetch_group()
+{
+    return D <= 2 ? 4 : (D == 3 ? 2 : 1);
+}
+
+template <class LY, typename T, bool FULL, bool ELEMS, class SV>
 __device__ __forceinline__ void smoother_tile_finish(const SmoothParams<T> &p, const DevModel &mdl,
                                                      cdouble *cst, SV &sv, const STileRange &tr, int tile,
                                                      T *s_out)
@@ -130,13 +144,8 @@ __device__ __forceinline__ void smoother_tile_finish(const SmoothParams<T> &p, c
         sagg_load<D, T>(lane_rec(p.lanep, slot, AGG, lane + 1), excl, PSSGP_WAVE);
         sagg_apply<D, T>(excl, ms, Ps, ms, Ps);
     }
-    for (int64_t k = k1 - 1; k >= k0; k--) {
-        if constexpr (reload_constants<D>()) PSSGP_RELOAD_CONSTANTS();
-        sv.seek(k);
-        SAgg<D, T> e;
-        cdouble *c = cst;
-        if constexpr (reload_constants<D>()) PSSGP_LAUNDER(c);
-        smoother_element<LY, T, SV>(mdl, c, sv, p.t, p.m + k, p.P + k, (size_t)p.n, k, e, bad);
+    // one step of the backward recursion from its element
+    auto step_out = [&](const SAgg<D, T> &e, int64_t k) {
         sagg_apply<D, T>(e, ms, Ps, ms, Ps);
         T Ph[D];
         mat_vec<D, T>(Ps, h, Ph);
@@ -153,6 +162,50 @@ __device__ __forceinline__ void smoother_tile_finish(const SmoothParams<T> &p, c
 #pragma unroll
                 for (int j = i; j < D; j++) p.Ps[(size_t)sidx<D>(i, j) * p.n + k] = Po[i][j];
         }
+    };
+    // (single series only: in the batched form, chunk 16 over series of
+    // uneven lengths, the grouping measured 5 % slower)
+    constexpr int G = std::is_same<SV, OneSeries>::value ? smoother_prefetch_group<D>() : 1;
+    if constexpr (ELEMS && G > 1) {
+        // small states: the elements of the next G steps are loaded while
+        // the current G are processed (a lane's recursion is otherwise one
+        // dependent load per step); indices below k0 are clamped to k0, so
+        // every load is in the tile's region and none sits in a branch
+        auto load = [&](int64_t k, SAgg<D, T> &e) {
+            const int j = k >= k0 ? (int)(k - k0) : 0;
+            sagg_load_nt<D, T>(p.elem + elem_index<D>(slot, p.chunk, j, lane), e, PSSGP_WAVE);
+        };
+        SAgg<D, T> cur[G], nxt[G];
+#pragma unroll
+        for (int g = 0; g < G; g++) load(k1 - 1 - g, cur[g]);
+        for (int64_t kb = k1 - 1; kb >= k0; kb -= G) {
+#pragma unroll
+            for (int g = 0; g < G; g++) load(kb - G - g, nxt[g]);
+#pragma unroll
+            for (int g = 0; g < G; g++) {
+                const int64_t k = kb - g;
+                if (k >= k0) {
+                    sv.seek(k);
+                    step_out(cur[g], k);
+                }
+            }
+#pragma unroll
+            for (int g = 0; g < G; g++) cur[g] = nxt[g];
+        }
+    } else {
+        for (int64_t k = k1 - 1; k >= k0; k--) {
+            if constexpr (reload_constants<D>()) PSSGP_RELOAD_CONSTANTS();
+            sv.seek(k);
+            SAgg<D, T> e;
+            if constexpr (ELEMS) {
+                sagg_load_nt<D, T>(p.elem + elem_index<D>(slot, p.chunk, (int)(k - k0), lane), e, PSSGP_WAVE);
+            } else {
+                cdouble *c = cst;
+                if constexpr (reload_constants<D>()) PSSGP_LAUNDER(c);
+                smoother_element<LY, T, SV>(mdl, c, sv, p.t, p.m + k, p.P + k, (size_t)p.n, k, e, bad);
+            }
+            step_out(e, k);
+        }
     }
     __syncthreads();
     for (int i = lane; i < tile_len; i += PSSGP_WAVE) {
@@ -165,7 +218,7 @@ __device__ __forceinline__ void smoother_tile_finish(const SmoothParams<T> &p, c
     if (bad) status_or(&p.ctl->status, bad);
 }
 
-// Smoother pass of a fused call: one tile. Up to the lane's last step it is
+// Smoother pass of a fused call with an element per lane: one tile. Up to the lane's last step it is
 // the RTS smoother (the smoothed moments there come from the carry and the
 // lane's exclusive suffix); inside the lane the same recursion runs in the
 // form of Bryson and Frazier, on the pair (lambda, Lambda) with
@@ -182,9 +235,11 @@ __device__ __forceinline__ void smoother_tile_finish(const SmoothParams<T> &p, c
 // and forms no element per step. With r = R / S (1 at a missing step) the
 // filtered P h is r times the predicted one, f_var = r h P h^T - r^2 (P h)^T
 // Lambda (P h) and f_mean = h m + h P h^T v / S + r (P h)^T lambda.
-// f_var is a difference, which FP64 carries: against RTS in extended
-// precision its error is that of RTS in FP64 (3e-15 to 4e-13 over gaps from
-// 1e-3 to 3 length-scales and noise variances down to 1e-6).
+// f_var is a difference, and Lambda is rounded relative to its largest entry:
+// FP64 carries that for the results of an FP32 scan (gaps of 1e-3 to 100
+// length-scales, noise variances of 1e-2 to 1e-14, d = 4, 6 and 8: no further
+// from extended precision than an element per step in FP32), and for no other
+// (lane_handover).
 // Handover and elements together: filter finish + smoother of 2^22 steps at
 // d = 6 (FP32, chunk 64) 473 + 167 us with an element per step (63 values; a
 // Cholesky factor, two solves and a composition), 313 + 185 us in this form,
@@ -198,7 +253,7 @@ __device__ __forceinline__ void smoother_tile_fused(const SmoothParams<T> &p, co
     constexpr int INCL = SAggLayout<D>::INCL;
     constexpr int B = smoother_shear_col<LY>();
     using SP = Sparsity<LY>;
-    using HL = HandLayout<D, T>;
+    using HL = HandLayout<D>;
     const int lane = lane_id();
     const int slot = tr.slot_base + tile;
     const int64_t chunk_id = (int64_t)slot * PSSGP_WAVE + lane;
@@ -211,10 +266,8 @@ __device__ __forceinline__ void smoother_tile_fused(const SmoothParams<T> &p, co
     const int row = p.chunk + 1, half = PSSGP_WAVE * row;
     T *so = s_out + lane * row;
     if (k0 < k1) {
-        // a series ends with the lane: nothing after it
-        sv.seek(k1 - 1);
-        const bool end = (k1 >= tr.k_end) || sv.last(k1 - 1);
-        const int64_t kl = (lane_overlap<D, T>() && !end) ? k1 : k1 - 1;  // last step of the lane's run
+            const bool end = k1 >= tr.k_end;
+        const int64_t kl = end ? k1 - 1 : k1;  // last step of the lane's run
         // inputs of that step, requested first
         const OptInputs opt(p.mask, nullptr, p.t);
         const double *hp = p.hand + HL::step(slot, p.chunk, 0, lane);
@@ -385,10 +438,7 @@ __device__ __forceinline__ void smoother_tile_fused(const SmoothParams<T> &p, co
             if constexpr (reload_constants<D>()) PSSGP_LAUNDER(cc);
             const bool first = sv.first(k);
             double F[D][D];
-            if constexpr (sizeof(T) == 8)
-                transition<LY, true>(mdl, cc, sv.sc, first ? 0.0 : tc - tp, first, F);
-            else
-                transition_plain<LY>(mdl, cc, sv.sc, first ? 0.0 : tc - tp, first, F);
+            transition_plain<LY>(mdl, cc, sv.sc, first ? 0.0 : tc - tp, first, F);
             double X[D][D], nl[D];
 #pragma unroll
             for (int i = 0; i < D; i++) {
@@ -447,7 +497,9 @@ __device__ __forceinline__ void smoother_tile_fused(const SmoothParams<T> &p, co
     }
 }
 
-template <class LY, typename T>
+// ELEMS: the smoother elements come from the filter of the same call instead
+// of being built from the filter moments.
+template <class LY, typename T, bool ELEMS>
 __global__ __launch_bounds__(PSSGP_WAVE, (smoother_waves<LY::D, T>())) void smoother_fold_kernel(SmoothParams<T> p,
                                                                                            DevModel mdl_arg)
 {
@@ -456,20 +508,34 @@ __global__ __launch_bounds__(PSSGP_WAVE, (smoother_waves<LY::D, T>())) void smoo
     OneSeries sv;
     sv.init(mdl, p.n);
     STileRange tr{0, p.n, p.ntiles, 0};
-    smoother_tile_fold<LY, T, OneSeries>(p, mdl, (cdouble *)p.cst, sv, tr, (int)blockIdx.x);
+    smoother_tile_fold<LY, T, ELEMS, OneSeries>(p, mdl, (cdouble *)p.cst, sv, tr, (int)blockIdx.x);
 }
 
-template <class LY, typename T, bool FULL>
+// The last block of a fused call's smoother, one more than there are tiles,
+// sums the filter's log-likelihood.
+template <typename T>
+__device__ __forceinline__ bool loglik_block(const SmoothParams<T> &p)
+{
+    if ((int)blockIdx.x != p.ntiles) return false;
+    const double s = sum_over_tiles(p.partials, p.ntiles, 1);
+    if (lane_id() == 0) *p.loglik = s;
+    return true;
+}
+
+template <class LY, typename T, bool FULL, bool ELEMS>
 __global__ __launch_bounds__(PSSGP_WAVE, (smoother_waves<LY::D, T>())) void smoother_finish_kernel(SmoothParams<T> p,
                                                                                              DevModel mdl_arg)
 {
+    if constexpr (ELEMS) {
+        if (loglik_block(p)) return;
+    }
     __shared__ DevModel mdl;
     model_to_lds(mdl_arg, mdl);
     OneSeries sv;
     sv.init(mdl, p.n);
     STileRange tr{0, p.n, p.ntiles, 0};
     extern __shared__ __align__(16) unsigned char pssgp_dyn_smem[];
-    smoother_tile_finish<LY, T, FULL, OneSeries>(p, mdl, (cdouble *)p.cst, sv, tr, (int)blockIdx.x,
+    smoother_tile_finish<LY, T, FULL, ELEMS, OneSeries>(p, mdl, (cdouble *)p.cst, sv, tr, (int)blockIdx.x,
                                                  reinterpret_cast<T *>(pssgp_dyn_smem));
 }
 
@@ -477,12 +543,7 @@ template <class LY, typename T>
 __global__ __launch_bounds__(PSSGP_WAVE, (fused_waves<LY::D>())) void smoother_fused_kernel(SmoothParams<T> p,
                                                                                           DevModel mdl_arg)
 {
-    // one block more than tiles: the filter's log-likelihood
-    if ((int)blockIdx.x == p.ntiles) {
-        const double s = sum_over_tiles(p.partials, p.ntiles, 1);
-        if (lane_id() == 0) *p.loglik = s;
-        return;
-    }
+    if (loglik_block(p)) return;
     __shared__ DevModel mdl;
     model_to_lds(mdl_arg, mdl);
     OneSeries sv;
@@ -512,24 +573,31 @@ int launch_smoother_t(const DevModel &mdl, const SmoothLaunch &a, hipStream_t s)
     p.aggp = (T *)a.ws.aggp;
     p.lanep = (T *)a.ws.lanep;
     p.cst = a.ws.cst;
-    p.y = (const T *)a.y;
-    p.mask = a.mask;
-    p.hand = a.hand;
-    p.bound = a.bound;
     p.partials = a.ws.partials;
     p.loglik = a.loglik;
+    p.elem = (const T *)a.elem;
+    p.hand = a.hand;
+    p.bound = a.bound;
+    p.y = (const T *)a.y;
+    p.mask = a.mask;
     const dim3 grid(a.ntiles), block(PSSGP_WAVE);
     pass_event(a.ev, 0, s);
-    if (a.hand) {
+    constexpr bool LANES = lane_handover(LY::D, sizeof(T) == 8);
+    constexpr bool FOLDED = LANES || lane_aggregate_handover<LY::D>();
+    if (a.fused && FOLDED) {
         // the filter's finish pass of the same call did this pass (lane
         // records at slane, tile aggregates at aggp)
         p.lanep = (T *)a.slane;
     } else {
-        launch_consts<LY, T>(mdl, a.ws.cst, s);
-        hipLaunchKernelGGL((smoother_fold_kernel<LY, T>), grid, block, 0, s, p, mdl);
+        if (!a.fused) {
+            launch_consts<LY, T>(mdl, a.ws.cst, s);
+            hipLaunchKernelGGL((smoother_fold_kernel<LY, T, false>), grid, block, 0, s, p, mdl);
+        } else if constexpr (!FOLDED) {
+            hipLaunchKernelGGL((smoother_fold_kernel<LY, T, true>), grid, block, 0, s, p, mdl);
+        }
+        if constexpr (smoother_by_rows<LY::D, T>())
+            hipLaunchKernelGGL((rows_lane_scan<LY::D, T>), grid, dim3(PSSGP_WAVE * LY::D), 0, s, p.lanep, p.aggp, 0);
     }
-    if constexpr (smoother_by_rows<LY::D, T>())
-        hipLaunchKernelGGL((rows_lane_scan<LY::D, T>), grid, dim3(PSSGP_WAVE * LY::D), 0, s, p.lanep, p.aggp, 0);
     int rc = (int)hipGetLastError();
     if (rc) return rc;
     pass_event(a.ev, 1, s);
@@ -540,13 +608,18 @@ int launch_smoother_t(const DevModel &mdl, const SmoothLaunch &a, hipStream_t s)
                                                          a.ws.gcarry, s);
     if (rc) return rc;
     pass_event(a.ev, 2, s);
-    const size_t smem = (size_t)2 * PSSGP_WAVE * (a.hand ? a.chunk + 1 : a.chunk) * sizeof(T);
-    if (a.hand)
-        hipLaunchKernelGGL((smoother_fused_kernel<LY, T>), dim3(a.ntiles + 1), block, smem, s, p, mdl);
-    else if (a.ms && a.Ps)
-        hipLaunchKernelGGL((smoother_finish_kernel<LY, T, true>), grid, block, smem, s, p, mdl);
+    const bool rows = a.fused && LANES;
+    const size_t smem = (size_t)2 * PSSGP_WAVE * (rows ? a.chunk + 1 : a.chunk) * sizeof(T);
+    const dim3 fgrid(a.ntiles + (a.fused ? 1 : 0));
+    if (a.fused) {
+        if constexpr (LANES)
+            hipLaunchKernelGGL((smoother_fused_kernel<LY, T>), fgrid, block, smem, s, p, mdl);
+        else
+            hipLaunchKernelGGL((smoother_finish_kernel<LY, T, false, true>), fgrid, block, smem, s, p, mdl);
+    } else if (a.ms && a.Ps)
+        hipLaunchKernelGGL((smoother_finish_kernel<LY, T, true, false>), grid, block, smem, s, p, mdl);
     else
-        hipLaunchKernelGGL((smoother_finish_kernel<LY, T, false>), grid, block, smem, s, p, mdl);
+        hipLaunchKernelGGL((smoother_finish_kernel<LY, T, false, false>), grid, block, smem, s, p, mdl);
     rc = (int)hipGetLastError();
     pass_event(a.ev, 3, s);
     return rc;

@@ -105,6 +105,23 @@ __device__ __forceinline__ void sagg_store(T *p, const SAgg<D, T> &a, size_t st 
         for (int j = i; j < D; j++) p[(size_t)(D * D + D + sidx<D>(i, j)) * st] = a.L[i][j];
 }
 
+// sagg_store with non-temporal stores: for the per-step handover, which is
+// read back only after far more data than the caches hold has been written
+template <int D, typename T>
+__device__ __forceinline__ void sagg_store_nt(T *p, const SAgg<D, T> &a, size_t st)
+{
+#pragma unroll
+    for (int i = 0; i < D; i++)
+#pragma unroll
+        for (int j = 0; j < D; j++) __builtin_nontemporal_store(a.E[i][j], p + (size_t)(i * D + j) * st);
+#pragma unroll
+    for (int i = 0; i < D; i++) __builtin_nontemporal_store(a.g[i], p + (size_t)(D * D + i) * st);
+#pragma unroll
+    for (int i = 0; i < D; i++)
+#pragma unroll
+        for (int j = i; j < D; j++) __builtin_nontemporal_store(a.L[i][j], p + (size_t)(D * D + D + sidx<D>(i, j)) * st);
+}
+
 template <int D, typename T>
 __device__ __forceinline__ void sagg_load(const T *p, SAgg<D, T> &a, size_t st = 1)
 {
@@ -118,6 +135,25 @@ __device__ __forceinline__ void sagg_load(const T *p, SAgg<D, T> &a, size_t st =
     for (int i = 0; i < D; i++)
 #pragma unroll
         for (int j = i; j < D; j++) { a.L[i][j] = p[(size_t)(D * D + D + sidx<D>(i, j)) * st]; a.L[j][i] = a.L[i][j]; }
+}
+
+// sagg_load with non-temporal loads: for the per-step handover, read once
+template <int D, typename T>
+__device__ __forceinline__ void sagg_load_nt(const T *p, SAgg<D, T> &a, size_t st)
+{
+#pragma unroll
+    for (int i = 0; i < D; i++)
+#pragma unroll
+        for (int j = 0; j < D; j++) a.E[i][j] = __builtin_nontemporal_load(p + (size_t)(i * D + j) * st);
+#pragma unroll
+    for (int i = 0; i < D; i++) a.g[i] = __builtin_nontemporal_load(p + (size_t)(D * D + i) * st);
+#pragma unroll
+    for (int i = 0; i < D; i++)
+#pragma unroll
+        for (int j = i; j < D; j++) {
+            a.L[i][j] = __builtin_nontemporal_load(p + (size_t)(D * D + D + sidx<D>(i, j)) * st);
+            a.L[j][i] = a.L[i][j];
+        }
 }
 
 template <int D, typename T>
@@ -142,41 +178,52 @@ __device__ __forceinline__ void gl_load(const T *p, T (&g)[D], T (&L)[D][D], siz
         for (int j = i; j < D; j++) { L[i][j] = p[(size_t)(D + sidx<D>(i, j)) * st]; L[j][i] = L[i][j]; }
 }
 
-// Handover from the filter to the smoother when both scans run in one call,
-// in FP64 whatever the scan type (the smoothed variance is the filtered one
-// minus a quadratic form of these values, smoother_tile_fused):
+// Handover from the filter to the smoother when both scans run in one call, of
+// one of two kinds (lane_handover). An element per step: the smoother elements
+// of step k0 + j of lane l of tile slot s are stored at
+// base[((s * chunk + j) * SIZE + field) * 64 + l] (SIZE = D^2 + D + NS fields:
+// E row-major, g, packed L), so that every access of a wave covers 64
+// consecutive elements.
+template <int D>
+__device__ __forceinline__ size_t elem_index(int slot, int chunk, int j, int lane)
+{
+    return ((size_t)slot * chunk + j) * (D * D + D + D * (D + 1) / 2) * 64 + lane;
+}
+
+// Whether the filter also composes, per lane, the smoother aggregate of the
+// lane's elements while it builds them, and then does the smoother's fold pass
+// itself (the wave's suffix scan of those aggregates): the smoother reads no
+// element before its finish pass, and its fold launch disappears. It costs the
+// filter one smoother combination per step and a working set of SIZE more
+// values per lane, which the register budget allows up to d = 6.
+#ifndef PSSGP_LANEAGG_MAXD
+#define PSSGP_LANEAGG_MAXD 6
+#endif
+template <int D>
+constexpr bool lane_aggregate_handover() { return D <= PSSGP_LANEAGG_MAXD; }
+
+// An element per lane, in FP64 (the smoothed variance is the filtered one minus
+// a quadratic form of these values, smoother_tile_fused):
 //  * per step, the predicted moments against the observation row, P h (D
 //    values) and h m;
 //  * per lane, the filter mean of its last step (D values) and the Cholesky
 //    factor of its covariance (packed by columns, the diagonal's reciprocals
 //    in its place).
-// The step k0 + j of lane l of tile slot s is stored at
-// [((s * run + j) * STEP + field) * 64 + l], run = chunk + lane_overlap, and a lane's record at
-// [(s * LANE + field) * 64 + l], so that every access of a wave covers 64
-// consecutive values.
-// FP32 scans: a lane's run for the smoother ends with the first step of the
-// lane after it, so that run has chunk + 1 steps. The two lanes' moments
-// differ there by the rounding of the FP32 carry, which the conditioning on
-// that step's observation has then reduced (in FP64 there is no such
-// difference to speak of). Joined at the last step of the lane instead, f_var
-// was up to 2.8 times as far from FP64 (sum of two kernels, 4046 steps with
-// gaps of half a length-scale: 8.5e-7 against 2.4e-6). Up to d = 3 the step
-// changed nothing that can be told from the rounding of the elements (1e5 to
-// 4e6 steps: 0.7 to 1.4 times the error of an element per step with it and
-// without) and cost 4 % (4 096 series, chunk 16: 2.50 against 2.59 ms).
-template <int D, typename T>
-__host__ __device__ constexpr int lane_overlap()
-{
-    return (sizeof(T) == 4 && D > 3) ? 1 : 0;
-}
-
-template <int D, typename T>
+// A lane's run for the smoother ends with the first step of the lane after it,
+// so that it has chunk + 1 steps: step k0 + j of lane l of tile slot s is
+// stored at [((s * (chunk + 1) + j) * STEP + field) * 64 + l], a lane's record
+// at [(s * LANE + field) * 64 + l]. The two lanes' moments differ there by the
+// rounding of the FP32 carry, which the conditioning on that step's
+// observation has then reduced. Joined at the last step of the lane instead,
+// f_var was up to 2.8 times as far from FP64 (sum of two kernels, 4046 steps
+// with gaps of half a length-scale: 8.5e-7 against 2.4e-6).
+template <int D>
 struct HandLayout {
     static constexpr int STEP = D + 1;
     static constexpr int LANE = D + D * (D + 1) / 2;
     __device__ static __forceinline__ size_t step(int slot, int chunk, int j, int lane)
     {
-        return ((size_t)slot * (chunk + lane_overlap<D, T>()) + j) * (size_t)(STEP * 64) + lane;
+        return ((size_t)slot * (chunk + 1) + j) * (size_t)(STEP * 64) + lane;
     }
     __device__ static __forceinline__ size_t lane(int slot, int lane) { return (size_t)slot * (LANE * 64) + lane; }
 };

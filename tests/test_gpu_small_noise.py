@@ -1,0 +1,110 @@
+"""Posterior variances at observation noise far below the signal, where the
+smoothed covariance is orders of magnitude smaller than the covariances it is
+formed from: the bars of the library (tests.parity.TOL) against the oracle, and
+the fused call against the separate ones, which work from the same filter
+moments. The oracle's own rounding at a noise variance R is about 1e-16 / R of
+f_var where every step is observed, and of order 1e-13 where test points between
+the observations set the scale of f_var: the noise of each case leaves both a
+tenth of the bar or less."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from oracle.model import MATERN12, MATERN32, MATERN52, RBF, OracleModel
+from tests.conftest import gpu_available
+from tests.parity import TOL, rel
+
+pytestmark = pytest.mark.gpu
+
+if not gpu_available():
+    pytest.skip("needs a HIP device", allow_module_level=True)
+
+import torch  # noqa: E402
+
+import paper_2102_09964_amd as P  # noqa: E402
+
+MODELS = {"m12": [(MATERN12, 0, 0.5, 1.0)], "m32": [(MATERN32, 0, 0.5, 1.0)], "m52": [(MATERN52, 0, 1.0, 1.0)],
+          "rbf6": [(RBF, 6, 1.0, 1.0)], "m12+m32": [(MATERN12, 0, 1.0, 0.5), (MATERN32, 0, 0.5, 0.5)],
+          "m32+rbf6": [(MATERN32, 0, 2.0, 0.5), (RBF, 6, 0.5, 0.5)]}
+
+
+def _series(n, gap, noise, missing, seed):
+    rng = np.random.default_rng(seed)
+    t = np.cumsum(gap * (0.5 + rng.random(n)))
+    y = np.sin(2 * t) + 0.3 * np.sin(5.1 * t + 1) + np.sqrt(noise) * rng.normal(size=n)
+    mask = (rng.random(n) >= missing).astype(np.uint8)
+    if missing:
+        mask[n // 4:n // 3] = 0
+    return t, y.astype(np.float32).astype(np.float64), mask
+
+
+def _run(name, noise, t, y, mask, dtype, chunk, fused=True):
+    pipe = P.Pipeline(P.make_model(MODELS[name], noise), len(t), dtype, options=P.make_options(chunk=chunk), fused=fused)
+    fm, fv, _ = pipe.run(torch.as_tensor(t, device="cuda"), torch.as_tensor(y, device="cuda", dtype=getattr(torch, dtype)),
+                         torch.as_tensor(mask, device="cuda"))
+    assert P.status(pipe.ws_s) == 0 and P.status(pipe.ws_f) == 0
+    return fm.double().cpu().numpy(), fv.double().cpu().numpy()
+
+
+@pytest.mark.parametrize("chunk", [4, 16])
+@pytest.mark.parametrize("noise", [1e-12, 1e-14])
+@pytest.mark.parametrize("name", ["m12+m32", "m32+rbf6"])
+def test_sum_between_observations(name, noise, chunk):
+    """FP64, gaps of a length-scale, a third of the steps test points: the sum is
+    known at an observation, its terms are not, so that the filtered covariance
+    is all but singular there."""
+    t, y, mask = _series(525, 1.0, noise, 0.3, 11)
+    fm, fv = _run(name, noise, t, y, mask, "float64", chunk)
+    o = oracle.run(OracleModel(MODELS[name], noise), t, y, mask)
+    e = rel(fm, o["f_mean"]), rel(fv, o["f_var"])
+    print(name, noise, chunk, "%.1e %.1e" % e, flush=True)
+    assert e[0] <= TOL["float64"]["mean"] and e[1] <= TOL["float64"]["var"]
+
+
+@pytest.mark.parametrize("chunk", [4, 16])
+@pytest.mark.parametrize("noise", [1e-4, 1e-6])
+@pytest.mark.parametrize("name", ["m32", "m52", "rbf6", "m12+m32", "m32+rbf6"])
+def test_every_step_observed_fp32(name, noise, chunk):
+    """FP32, every step observed, f_var of the size of the noise: where lanes meet,
+    the rounding of their FP32 moments is far larger than that."""
+    t, y, mask = _series(2100, 1.0, noise, 0.0, 12)
+    fm, fv = _run(name, noise, t, y, mask, "float32", chunk)
+    o = oracle.run(OracleModel(MODELS[name], noise), t, y, mask)
+    e = rel(fm, o["f_mean"]), rel(fv, o["f_var"])
+    print(name, noise, chunk, "%.1e %.1e" % e, flush=True)
+    assert e[0] <= TOL["float32"]["mean"] and e[1] <= TOL["float32"]["var"]
+
+
+@pytest.mark.parametrize("gap,noise", [(1e-3, 1e-3), (1e-3, 1e-6), (1e-4, 1e-6), (1e-4, 1e-4)])
+@pytest.mark.parametrize("name", ["m12", "m32", "m52", "rbf6"])
+def test_fused_equals_separate_fp64(name, gap, noise):
+    """FP64: a dense series starts at the prior and is known well a few steps later.
+    The two calls share the filter moments, so they differ by the rounding of the
+    smoother alone: a tenth of the bar of either against the oracle."""
+    t, y, mask = _series(3000, gap, noise, 0.0, 13)
+    for chunk in (4, 64):
+        a = _run(name, noise, t, y, mask, "float64", chunk)
+        b = _run(name, noise, t, y, mask, "float64", chunk, fused=False)
+        e = rel(a[0], b[0]), rel(a[1], b[1])
+        print(name, gap, noise, chunk, "%.1e %.1e" % e, flush=True)
+        assert e[0] <= 0.1 * TOL["float64"]["mean"] and e[1] <= 0.1 * TOL["float64"]["var"]
+
+
+@pytest.mark.parametrize("chunk", [16, 32])
+@pytest.mark.parametrize("name", ["m32", "m52", "m12+m32", "rbf6"])
+def test_dense_fp32(name, chunk):
+    """FP32 against FP64 on the same observations where the lanes' joins matter
+    most: 3e5 steps a thousandth of a unit apart. Measured 8e-7 to 2.4e-6 (f_mean)
+    and 4e-7 to 2e-6 (f_var; 1.0e-5 for the sum, 8e-6 for RBF-6); the bars are
+    twice the largest."""
+    rng = np.random.default_rng(14)
+    n = 300007
+    t = np.cumsum(1e-3 * rng.exponential(size=n)) * (10.0 if name == "rbf6" else 1.0)
+    y = (np.sin(2 * np.pi * t) + 0.1 * rng.normal(size=n)).astype(np.float32).astype(np.float64)
+    mask = (rng.random(n) >= 0.3).astype(np.uint8)
+    r = _run(name, 0.01, t, y, mask, "float64", 16)
+    a = _run(name, 0.01, t, y, mask, "float32", chunk)
+    e = rel(a[0], r[0]), rel(a[1], r[1])
+    print(name, chunk, "%.1e %.1e" % e, flush=True)
+    assert e[0] <= {"rbf6": 1.2e-5}.get(name, 5e-6) and e[1] <= {"m12+m32": 2e-5, "rbf6": 2e-5}.get(name, 4e-6)
