@@ -156,7 +156,7 @@ Plan make_plan(int d, int ncomp, int64_t n, pssgp_dtype dtype, int op, const pss
         p.off_lane = take(nt * 64 * filter_agg_elems(d) * p.tsize);
         p.off_part = take(nt * sizeof(double) * n_params(ncomp));
         if (lane_handover(d, f64)) {
-            p.off_hand = take((steps + nt * 64) * (d + 1) * sizeof(double));
+            p.off_hand = take((steps + nt * 64) * (d + 3) * sizeof(double));
             p.off_bound = take(nt * 64 * (size_t)smooth_incl_elems(d) * sizeof(double));
         } else {
             p.off_elem = take(steps * smooth_agg_elems(d) * p.tsize);
@@ -915,8 +915,6 @@ int pssgp_predict(const pssgp_model *model, const double *t, const void *y, cons
     sm.elem = a.elem;
     sm.hand = a.hand;
     sm.bound = a.bound;
-    sm.y = y;
-    sm.mask = mask;
     sm.loglik = loglik;
     sm.slane = b + p.off_slane;
     sm.ws = sw;

@@ -648,6 +648,8 @@ __device__ __forceinline__ void filter_tile_finish(const FilterParams<T> &p, con
 #pragma unroll
             for (int i = 0; i < D; i++) __builtin_nontemporal_store(Ph[i], hp + i * PSSGP_WAVE);
             __builtin_nontemporal_store(hm, hp + D * PSSGP_WAVE);
+            __builtin_nontemporal_store(obs ? v : 0.0, hp + (D + 1) * PSSGP_WAVE);
+            __builtin_nontemporal_store(__builtin_copysign(dt, obs ? 1.0 : -1.0), hp + (D + 2) * PSSGP_WAVE);
             fixed_point_update<D, smoother_shear_col<LY>(), Sparsity<LY>>(K, v, w, obs ? (double)R * w : 1.0, fm, fP, fG);
         }
         if constexpr ((MODE & F_RECS) != 0) {

@@ -88,8 +88,6 @@ struct SmoothLaunch {
     const void *elem;
     const double *hand;
     const double *bound;
-    const void *y;        // hand: the filter's observations
-    const uint8_t *mask;  // hand: their mask (nullable)
     void *slane;
     double *loglik;       // fused: receives the sum of the filter's partials
     ScanWs ws;

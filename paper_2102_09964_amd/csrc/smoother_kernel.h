@@ -48,8 +48,6 @@ struct SmoothParams {
     const T *elem;           // fused call, an element per step (elem_index)
     const double *hand;      // fused call, an element per lane (HandLayout) and
     const double *bound;
-    const T *y;              //   the filter's inputs
-    const uint8_t *mask;
 };
 
 struct STileRange {
@@ -230,8 +228,8 @@ __device__ __forceinline__ void smoother_tile_finish(const SmoothParams<T> &p, c
 //     Lambda <- (I - K h)^T Lambda (I - K h) + h^T h / S
 //     lambda <- (I - K h)^T lambda + h^T v / S
 //   and over the transition before it, Lambda <- F^T Lambda F, lambda <- F^T lambda.
-// f needs only P h and h m of the step, so that the filter hands over D + 1
-// values per step instead of the D^2 + D + D (D + 1) / 2 of a smoother element
+// f needs only P h and h m of the step, so that the filter hands over D + 3
+// values per step (HandLayout) instead of the D^2 + D + D (D + 1) / 2 of a smoother element
 // and forms no element per step. With r = R / S (1 at a missing step) the
 // filtered P h is r times the predicted one, f_var = r h P h^T - r^2 (P h)^T
 // Lambda (P h) and f_mean = h m + h P h^T v / S + r (P h)^T lambda.
@@ -269,16 +267,16 @@ __device__ __forceinline__ void smoother_tile_fused(const SmoothParams<T> &p, co
             const bool end = k1 >= tr.k_end;
         const int64_t kl = end ? k1 - 1 : k1;  // last step of the lane's run
         // inputs of that step, requested first
-        const OptInputs opt(p.mask, nullptr, p.t);
-        const double *hp = p.hand + HL::step(slot, p.chunk, 0, lane);
         constexpr size_t ST = (size_t)HL::STEP * PSSGP_WAVE;
-        double ph[D], hm, tc = p.t[kl], tp = p.t[kl > tr.k_begin ? kl - 1 : kl];
-        T yc = p.y[kl];
-        bool oc = opt.observed(kl);
-        const double *hq = hp + (size_t)(kl - k0) * ST;
+        const double *hq = p.hand + HL::step(slot, p.chunk, (int)(kl - k0), lane);
+        double ph[D], in[3];  // P h; h m, innovation, length and mask of the step
+        auto load = [&](const double *q, double (&x)[D], double (&z)[3]) {
 #pragma unroll
-        for (int i = 0; i < D; i++) ph[i] = __builtin_nontemporal_load(hq + i * PSSGP_WAVE);
-        hm = __builtin_nontemporal_load(hq + D * PSSGP_WAVE);
+            for (int i = 0; i < D; i++) x[i] = __builtin_nontemporal_load(q + i * PSSGP_WAVE);
+#pragma unroll
+            for (int i = 0; i < 3; i++) z[i] = __builtin_nontemporal_load(q + (D + i) * PSSGP_WAVE);
+        };
+        load(hq, ph, in);
         double lam[D], Lam[D][D];
         {
             T msT[D], PsT[D][D];
@@ -367,19 +365,12 @@ __device__ __forceinline__ void smoother_tile_fused(const SmoothParams<T> &p, co
         }
         for (int64_t k = kl;; k--) {
             // the next step's inputs, one iteration ahead
-            const int64_t kn = k > k0 ? k - 1 : k0;
-            double nph[D];
-            const double *q = k > k0 ? hq - ST : hq;
-            hq = q;
-#pragma unroll
-            for (int i = 0; i < D; i++) nph[i] = __builtin_nontemporal_load(q + i * PSSGP_WAVE);
-            const double nhm = __builtin_nontemporal_load(q + D * PSSGP_WAVE);
-            const double tn = p.t[kn > tr.k_begin ? kn - 1 : kn];
-            const T yn = p.y[kn];
-            const bool on = opt.observed(kn);
-            if constexpr (reload_constants<D>()) PSSGP_RELOAD_CONSTANTS();
-            sv.seek(k);
-            const double R = (double)T(sv.R);
+            double nph[D], nin[3];
+            hq = k > k0 ? hq - ST : hq;
+            load(hq, nph, nin);
+            PSSGP_RELOAD_CONSTANTS();
+            const double R = (double)T(sv.R), hm = in[0], v = in[1], dt = __builtin_fabs(in[2]);
+            const bool oc = !__builtin_signbit(in[2]);
             // in the coordinates z' = S z (identity for one component) the
             // observation row is the first unit vector: P h is summed into
             // its first entry, Lambda' = S^-T Lambda S^-1, lambda' = S^-T lambda
@@ -394,7 +385,6 @@ __device__ __forceinline__ void smoother_tile_fused(const SmoothParams<T> &p, co
             const double hph = ph[0];
             const double S = R + hph;
             const double w = oc ? rcp64(S) : 0.0;
-            const double v = oc ? (double)yc - hm : 0.0;
             const double r = oc ? R * w : 1.0;
             // q = Lambda P h and s = Lambda (I - K h) e_0, whose first factor
             // 1 - K_0 is r: formed as a difference it would lose log10(S / R)
@@ -433,12 +423,12 @@ __device__ __forceinline__ void smoother_tile_fused(const SmoothParams<T> &p, co
 #pragma unroll
                 for (int j = 0; j < D; j++) Lam[j][B] = (j == B) ? Lam[B][B] + Lam[B][0] : Lam[B][j];
             }
-            // over the transition into step k (F = 0 at a series start)
+            // over the transition into step k (past the lane's first step, so
+            // never the series' first)
             cdouble *cc = cst;
-            if constexpr (reload_constants<D>()) PSSGP_LAUNDER(cc);
-            const bool first = sv.first(k);
+            PSSGP_LAUNDER(cc);
             double F[D][D];
-            transition_plain<LY>(mdl, cc, sv.sc, first ? 0.0 : tc - tp, first, F);
+            transition_plain<LY>(mdl, cc, sv.sc, dt, false, F);
             double X[D][D], nl[D];
 #pragma unroll
             for (int i = 0; i < D; i++) {
@@ -471,11 +461,8 @@ __device__ __forceinline__ void smoother_tile_fused(const SmoothParams<T> &p, co
             }
 #pragma unroll
             for (int i = 0; i < D; i++) ph[i] = nph[i];
-            hm = nhm;
-            tc = tp;
-            tp = tn;
-            yc = yn;
-            oc = on;
+#pragma unroll
+            for (int i = 0; i < 3; i++) in[i] = nin[i];
         }
     }
     __syncthreads();
@@ -578,8 +565,6 @@ int launch_smoother_t(const DevModel &mdl, const SmoothLaunch &a, hipStream_t s)
     p.elem = (const T *)a.elem;
     p.hand = a.hand;
     p.bound = a.bound;
-    p.y = (const T *)a.y;
-    p.mask = a.mask;
     const dim3 grid(a.ntiles), block(PSSGP_WAVE);
     pass_event(a.ev, 0, s);
     constexpr bool LANES = lane_handover(LY::D, sizeof(T) == 8);

@@ -205,7 +205,10 @@ constexpr bool lane_aggregate_handover() { return D <= PSSGP_LANEAGG_MAXD; }
 // An element per lane, in FP64 (the smoothed variance is the filtered one minus
 // a quadratic form of these values, smoother_tile_fused):
 //  * per step, the predicted moments against the observation row, P h (D
-//    values) and h m;
+//    values) and h m, the innovation (0 at a missing step) and the step's
+//    length, its sign bit set at a missing step. With these the smoother reads
+//    nothing but the workspace, so that its outputs may overlap the call's
+//    inputs, as with an element per step;
 //  * per lane, the filter mean of its last step (D values) and the Cholesky
 //    factor of its covariance (packed by columns, the diagonal's reciprocals
 //    in its place).
@@ -219,7 +222,7 @@ constexpr bool lane_aggregate_handover() { return D <= PSSGP_LANEAGG_MAXD; }
 // with gaps of half a length-scale: 8.5e-7 against 2.4e-6).
 template <int D>
 struct HandLayout {
-    static constexpr int STEP = D + 1;
+    static constexpr int STEP = D + 3;
     static constexpr int LANE = D + D * (D + 1) / 2;
     __device__ static __forceinline__ size_t step(int slot, int chunk, int j, int lane)
     {
