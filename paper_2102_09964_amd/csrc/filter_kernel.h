@@ -221,23 +221,45 @@ __device__ __forceinline__ void hand_over_element(const SAgg<D, T> &e, T *out, S
 // the filter moments of the last step and P = C C^T,
 //   Z = C^-1 G, L = P0 - Z^T Z, E = (C^-T Z)^T = G^T P^-1, g = m0 - E m.
 // This is what composing the steps' elements gives, without forming one per
-// step (no Cholesky factor, solves and three matrix products per step). A
-// series start inside the lane has F = 0, so G = 0 and E = 0 from there on.
-// e receives the element rounded to T, in the smoother's coordinates
-// z' = S z, S = I + e_0 e_B^T (smoother_shear_col; B = 0: identity); C the
-// factor with the reciprocals rd of its diagonal.
+// step (no Cholesky factor, solves and three matrix products per step).
+// All in the smoother's coordinates z' = S z, S = I + e_0 e_B^T
+// (smoother_shear_col; B = 0: identity), whose first state is f, and with the
+// first row of S P S^T taken as r P h, r = R / S (1 at a missing step), from the
+// last conditioning (ph): formed as a difference it keeps no digit of a
+// filtered variance of f below 1e-16 of the predicted one, and for a sum of two
+// components P is then not positive definite. (h G, which is as small, may be a
+// sum of its two rows: the factor's first column, of the size of its root, takes
+// their rounding into nothing larger than that.) G comes in the filter's coordinates and is overwritten; m, C and rd
+// receive S m, the factor and the reciprocals of its diagonal. In a lane that
+// ends the series (end) E = 0, and the factor, which nothing uses, is not
+// judged.
 template <int D, int B, typename T>
 __device__ __forceinline__ void lane_smoother_element(const double (&m0)[D], double (&P0)[D][D], double (&G)[D][D],
-                                                      const double (&m)[D], const double (&P)[D][D],
-                                                      double (&C)[D][D], double (&rd)[D], SAgg<D, T> &e,
+                                                      double (&m)[D], const double (&P)[D][D], double fm,
+                                                      const double (&ph)[D], double r,
+                                                      bool end, double (&C)[D][D], double (&rd)[D], SAgg<D, T> &e,
                                                       uint32_t &bad)
 {
-    // G is overwritten
+    m[0] = fm;
+    double hph = ph[0];
+    if constexpr (B > 0) hph += ph[B];
+#pragma unroll
+    for (int i = 0; i < D; i++) {
+        C[i][0] = r * (i == 0 ? hph : ph[i]);
+#pragma unroll
+        for (int j = 1; j <= i; j++) C[i][j] = P[i][j];
+    }
+    if (!cholesky<D, double>(C, rd) && !end) bad |= PSSGP_STATUS_CHOLESKY;
 #pragma unroll
     for (int i = 0; i < D; i++)
 #pragma unroll
-        for (int j = 0; j <= i; j++) C[i][j] = P[i][j];
-    if (!cholesky<D, double>(C, rd)) bad |= PSSGP_STATUS_CHOLESKY;
+        for (int j = 0; j < D; j++) G[i][j] = end ? 0.0 : G[i][j];
+    if constexpr (B > 0) {
+#pragma unroll
+        for (int c = 0; c < D; c++) G[0][c] += G[B][c];
+#pragma unroll
+        for (int q = 0; q < D; q++) G[q][0] += G[q][B];
+    }
 #pragma unroll
     for (int j = 0; j < D; j++)
 #pragma unroll
@@ -247,11 +269,7 @@ __device__ __forceinline__ void lane_smoother_element(const double (&m0)[D], dou
             for (int q = 0; q < i; q++) acc = fma(-C[i][q], G[q][j], acc);
             G[i][j] = acc * rd[i];
         }
-    // L' = S P0 S^T - (Z S^T)^T (Z S^T); Z S^T is column 0 plus column B
-    if constexpr (B > 0) {
-#pragma unroll
-        for (int q = 0; q < D; q++) G[q][0] += G[q][B];
-    }
+    // L = S P0 S^T - Z^T Z
 #pragma unroll
     for (int i = 0; i < D; i++)
 #pragma unroll
@@ -274,7 +292,7 @@ __device__ __forceinline__ void lane_smoother_element(const double (&m0)[D], dou
             for (int q = i + 1; q < D; q++) acc = fma(-C[q][i], G[q][j], acc);
             G[i][j] = acc * rd[i];
         }
-    // G = (S E)^T: g' = S m0 - (S E) m, E' = (S E) S^-1 (column B minus column 0)
+    // G = E^T: g = S m0 - E S m
 #pragma unroll
     for (int i = 0; i < D; i++) {
         double acc = m0[i];
@@ -285,7 +303,7 @@ __device__ __forceinline__ void lane_smoother_element(const double (&m0)[D], dou
         for (int q = 0; q < D; q++) acc = fma(-G[q][i], m[q], acc);
         e.g[i] = T(acc);
 #pragma unroll
-        for (int j = 0; j < D; j++) e.E[i][j] = T((B > 0 && j == B) ? G[B][i] - G[0][i] : G[j][i]);
+        for (int j = 0; j < D; j++) e.E[i][j] = T(G[j][i]);
     }
 }
 
@@ -650,7 +668,8 @@ __device__ __forceinline__ void filter_tile_finish(const FilterParams<T> &p, con
             __builtin_nontemporal_store(hm, hp + D * PSSGP_WAVE);
             __builtin_nontemporal_store(obs ? v : 0.0, hp + (D + 1) * PSSGP_WAVE);
             __builtin_nontemporal_store(__builtin_copysign(dt, obs ? 1.0 : -1.0), hp + (D + 2) * PSSGP_WAVE);
-            fixed_point_update<D, smoother_shear_col<LY>(), Sparsity<LY>>(K, v, w, obs ? (double)R * w : 1.0, fm, fP, fG);
+            const double r = obs ? (double)R * w : 1.0;
+            fixed_point_update<D, smoother_shear_col<LY>(), Sparsity<LY>>(K, v, w, r, fm, fP, fG);
         }
         if constexpr ((MODE & F_RECS) != 0) {
             constexpr int NS = RecLayout<D>::NS;
@@ -721,12 +740,18 @@ __device__ __forceinline__ void filter_tile_finish(const FilterParams<T> &p, con
         // the lane's smoother element (identity for a lane without steps) and
         // its end moments, the covariance as its Cholesky factor
         if (k1 > k0) {
+            // (the last conditioning from the handover: kept in registers over
+            // the loop it cost 5 % of the call at d = 8)
+            constexpr int B = smoother_shear_col<LY>();
+            const double *hp = p.hand + HL::step(slot, p.chunk, (int)(ke - 1 - k0), lane);
+            double C[D][D], rd[D], ph[D];
 #pragma unroll
-            for (int i = 0; i < D; i++)
-#pragma unroll
-                for (int j = 0; j < D; j++) fG[i][j] = end ? 0.0 : fG[i][j];
-            double C[D][D], rd[D];
-            lane_smoother_element<D, smoother_shear_col<LY>(), T>(fm, fP, fG, m, P, C, rd, sacc, bad);
+            for (int i = 0; i < D; i++) ph[i] = hp[i * PSSGP_WAVE];
+            const double hph = B > 0 ? ph[0] + ph[B] : ph[0], R = (double)T(sv.R);
+            const bool obs = !__builtin_signbit(hp[(D + 2) * PSSGP_WAVE]);
+            const double w = obs ? rcp64(R + hph) : 0.0;
+            const double f = fma(hph * w, hp[(D + 1) * PSSGP_WAVE], hp[D * PSSGP_WAVE]);
+            lane_smoother_element<D, B, T>(fm, fP, fG, m, P, f, ph, obs ? R * w : 1.0, end, C, rd, sacc, bad);
             double *bp = p.bound + HL::lane(slot, lane);
 #pragma unroll
             for (int i = 0; i < D; i++) {

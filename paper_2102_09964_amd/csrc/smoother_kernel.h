@@ -286,14 +286,13 @@ __device__ __forceinline__ void smoother_tile_fused(const SmoothParams<T> &p, co
                 sagg_load<D, T>(lane_rec(p.lanep, slot, AGG, lane + 1), excl, PSSGP_WAVE);
                 sagg_apply<D, T>(excl, msT, PsT, msT, PsT);
             }
-            double msd[D], Psd[D][D], ms[D], Ps[D][D];
+            double ms[D], Ps[D][D];
 #pragma unroll
             for (int i = 0; i < D; i++) {
-                msd[i] = (double)msT[i];
+                ms[i] = (double)msT[i];
 #pragma unroll
-                for (int j = 0; j < D; j++) Psd[i][j] = (double)PsT[i][j];
+                for (int j = 0; j < D; j++) Ps[i][j] = (double)PsT[i][j];
             }
-            from_smoother_coords<D, B, double>(msd, Psd, ms, Ps);
             const double *bp = p.bound + HL::lane(slot, lane);
             double C[D][D], rd[D];
 #pragma unroll
@@ -371,17 +370,10 @@ __device__ __forceinline__ void smoother_tile_fused(const SmoothParams<T> &p, co
             PSSGP_RELOAD_CONSTANTS();
             const double R = (double)T(sv.R), hm = in[0], v = in[1], dt = __builtin_fabs(in[2]);
             const bool oc = !__builtin_signbit(in[2]);
-            // in the coordinates z' = S z (identity for one component) the
-            // observation row is the first unit vector: P h is summed into
-            // its first entry, Lambda' = S^-T Lambda S^-1, lambda' = S^-T lambda
-            if constexpr (B > 0) {
-                ph[0] += ph[B];
-                lam[B] -= lam[0];
-#pragma unroll
-                for (int j = 0; j < D; j++) Lam[B][j] -= Lam[0][j];
-#pragma unroll
-                for (int j = 0; j < D; j++) Lam[j][B] = (j == B) ? Lam[B][B] - Lam[B][0] : Lam[B][j];
-            }
+            // here lambda and Lambda are in the coordinates z' = S z (identity
+            // for one component), where the observation row is the first unit
+            // vector: P h is summed into its first entry
+            if constexpr (B > 0) ph[0] += ph[B];
             const double hph = ph[0];
             const double S = R + hph;
             const double w = oc ? rcp64(S) : 0.0;
@@ -416,6 +408,8 @@ __device__ __forceinline__ void smoother_tile_fused(const SmoothParams<T> &p, co
                 Lam[0][0] = fma(-w, us, fma(r, su[0], w));
                 lam[0] = fma(w, v - ul, r * lam[0]);
             }
+            // in the filter's coordinates, S^T Lambda' S and S^T lambda', over the
+            // transition, whose blocks they keep apart
             if constexpr (B > 0) {
                 lam[B] += lam[0];
 #pragma unroll
@@ -458,6 +452,14 @@ __device__ __forceinline__ void smoother_tile_fused(const SmoothParams<T> &p, co
                     Lam[i][j] = x;
                     Lam[j][i] = x;
                 }
+            }
+            // back: S^-T Lambda S^-1, S^-T lambda
+            if constexpr (B > 0) {
+                lam[B] -= lam[0];
+#pragma unroll
+                for (int j = 0; j < D; j++) Lam[B][j] -= Lam[0][j];
+#pragma unroll
+                for (int j = 0; j < D; j++) Lam[j][B] = (j == B) ? Lam[B][B] - Lam[B][0] : Lam[B][j];
             }
 #pragma unroll
             for (int i = 0; i < D; i++) ph[i] = nph[i];

@@ -211,7 +211,7 @@ constexpr bool lane_aggregate_handover() { return D <= PSSGP_LANEAGG_MAXD; }
 //    inputs, as with an element per step;
 //  * per lane, the filter mean of its last step (D values) and the Cholesky
 //    factor of its covariance (packed by columns, the diagonal's reciprocals
-//    in its place).
+//    in its place), both in the smoother's coordinates.
 // A lane's run for the smoother ends with the first step of the lane after it,
 // so that it has chunk + 1 steps: step k0 + j of lane l of tile slot s is
 // stored at [((s * (chunk + 1) + j) * STEP + field) * 64 + l], a lane's record

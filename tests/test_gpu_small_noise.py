@@ -25,7 +25,7 @@ import torch  # noqa: E402
 import paper_2102_09964_amd as P  # noqa: E402
 
 MODELS = {"m12": [(MATERN12, 0, 0.5, 1.0)], "m32": [(MATERN32, 0, 0.5, 1.0)], "m52": [(MATERN52, 0, 1.0, 1.0)],
-          "rbf6": [(RBF, 6, 1.0, 1.0)], "m12+m32": [(MATERN12, 0, 1.0, 0.5), (MATERN32, 0, 0.5, 0.5)],
+          "rbf4": [(RBF, 4, 1.0, 1.0)], "rbf6": [(RBF, 6, 1.0, 1.0)], "m12+m32": [(MATERN12, 0, 1.0, 0.5), (MATERN32, 0, 0.5, 0.5)],
           "m32+rbf6": [(MATERN32, 0, 2.0, 0.5), (RBF, 6, 0.5, 0.5)]}
 
 
@@ -74,6 +74,22 @@ def test_every_step_observed_fp32(name, noise, chunk):
     e = rel(fm, o["f_mean"]), rel(fv, o["f_var"])
     print(name, noise, chunk, "%.1e %.1e" % e, flush=True)
     assert e[0] <= TOL["float32"]["mean"] and e[1] <= TOL["float32"]["var"]
+
+
+@pytest.mark.parametrize("dtype", ["float32", "float64"])
+@pytest.mark.parametrize("name", ["m12", "m52", "rbf4", "m12+m32", "m32+rbf6"])
+def test_noise_below_rounding(name, dtype):
+    """Noise below 1e-16 of the signal, which the interface accepts: the filtered
+    variance of f at an observation is then below the rounding of the predicted
+    one, test points between the observations set the scale, and no status bit is
+    raised (_run)."""
+    for chunk in (4, 16):
+        t, y, mask = _series(525, 3.0, 0.0, 0.3, 15)
+        fm, fv = _run(name, 1e-18, t, y, mask, dtype, chunk)
+        o = oracle.run(OracleModel(MODELS[name], 1e-18), t, y, mask)
+        e = rel(fm, o["f_mean"]), rel(fv, o["f_var"])
+        print(name, dtype, chunk, "%.1e %.1e" % e, flush=True)
+        assert e[0] <= TOL[dtype]["mean"] and e[1] <= TOL[dtype]["var"]
 
 
 @pytest.mark.parametrize("gap,noise", [(1e-3, 1e-3), (1e-3, 1e-6), (1e-4, 1e-6), (1e-4, 1e-4)])
