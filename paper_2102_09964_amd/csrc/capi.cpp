@@ -547,9 +547,10 @@ int qp_check_opts(const pssgp_options *opts)
 // every SIMD (4 096 teams) at 8 states and half of that at 12 and 16, where a
 // level of the scan costs more than the steps it saves, from qp_least to
 // kQPDefaultChunk steps. Measured (FP64, ms at chunk 16 / 32 / 64 / 128 / 256):
-// 8 states, 65 000 steps 0.43 / 0.41 / 0.53 / 0.83 / 1.44, 260 000 steps 1.52 /
-// 1.01 / 0.72 / 0.94 / 1.48; 16 states, 20 000 steps 3.4 / 2.6 / 2.1 / 2.6 / 3.8,
-// 260 000 steps 26 / 12.8 / 6.4 / 4.7 / 5.2.
+// 8 states, 65 000 steps 0.51 / 0.57 / 0.86 / 1.49 / 2.80, 262 107 steps 1.73 /
+// 1.21 / 1.07 / 1.66 / 2.94; 12 states, 20 000 steps 1.41 / 1.26 / 1.76 / 2.85 /
+// 5.10, 262 107 steps 8.99 / 5.07 / 3.25 / 3.78 / 5.51; 16 states, 20 000 steps
+// 3.7 / 3.2 / 3.3 / 5.0 / 8.5, 262 107 steps 28.6 / 14.8 / 8.2 / 7.6 / 10.2.
 int64_t qp_least(int d) { return d <= 10 ? 16 : 64; }
 int64_t qp_teams(int d) { return d <= 10 ? 4096 : 2048; }
 
@@ -595,11 +596,14 @@ QPPlan qp_plan(int d, int64_t n, pssgp_dtype dtype, bool elems, const pssgp_opti
     p.off_f[0] = take(G * nf_f * p.tsize);
     p.off_f[1] = take(G * nf_f * p.tsize);
     if (elems) {
-        p.off_elem = take(ns * nf_s * p.tsize);
+        const size_t steps = (size_t)(n > 0 ? n : 1);
+        p.off_elem = take((qp_sub_handover(f64) ? ns : steps) * nf_s * p.tsize);
         p.off_s[0] = take(G * nf_s * p.tsize);
         p.off_s[1] = take(G * nf_s * p.tsize);
-        p.off_hand = take((size_t)(n > 0 ? n : 1) * (d + 2) * sizeof(double));
-        p.off_bound = take(ns * d * (d + 2) * sizeof(double));
+        if (qp_sub_handover(f64)) {
+            p.off_hand = take(steps * (d + 2) * sizeof(double));
+            p.off_bound = take(ns * d * (d + 2) * sizeof(double));
+        }
     }
     p.off_part = take(G * sizeof(double));
     p.total = off;
@@ -658,8 +662,9 @@ int qp_run(const pssgp_model *model, const double *t, const void *y, const uint8
     q.elem = elems ? b + p.off_elem : nullptr;
     q.sub = p.sub;
     q.nsub = p.nsub;
-    q.hand = elems ? (double *)(b + p.off_hand) : nullptr;
-    q.bound = elems ? (double *)(b + p.off_bound) : nullptr;
+    const bool subs = elems && qp_sub_handover(dtype == PSSGP_F64);
+    q.hand = subs ? (double *)(b + p.off_hand) : nullptr;
+    q.bound = subs ? (double *)(b + p.off_bound) : nullptr;
     q.partials = (double *)(b + p.off_part);
     q.loglik = loglik;
     q.f_mean = f_mean;

@@ -12,17 +12,20 @@
 //                   A = 0, so the prefix of chunk g - 1 holds the filter
 //                   moments entering chunk g
 //   filter finish   each team re-runs its chunk from those moments as a
-//                   Kalman filter in FP64 and sums the log-likelihood terms;
-//                   next to it runs the fixed-point smoother of the state
-//                   before each sub-chunk of steps, which gives one smoother
-//                   element per sub-chunk (qp_element), and P h, h m of every
-//                   step go to the smoother
+//                   Kalman filter in FP64 and sums the log-likelihood terms.
+//                   FP64: it writes the smoother element of every step. FP32
+//                   (qp_sub_handover): next to it runs the fixed-point smoother
+//                   of the state before each sub-chunk of steps, which gives
+//                   one smoother element per sub-chunk (qp_element), and P h,
+//                   h m of every step go to the smoother
 //   loglik          one workgroup sums the per-chunk partials in chunk order
-//   smoother join   each team joins the elements of its chunk's sub-chunks
+//   smoother fold   each team composes its chunk's elements right to left, or
+//   smoother join   those of its chunk's sub-chunks
 //   smoother scan   suffix scan of the chunks' elements (Hillis-Steele)
-//   smoother finish each team runs the recursion of Bryson and Frazier
-//                   backwards over a sub-chunk, as the one-lane scans do
-//                   (smoother_tile_fused), and writes f_mean, f_var
+//   smoother finish FP64: each team applies the elements of its chunk backwards
+//                   (RTS) and writes f_mean, f_var. FP32: each team runs the
+//                   recursion of Bryson and Frazier backwards over a sub-chunk,
+//                   as the one-lane scans do (smoother_tile_fused)
 // What bounds these passes at the default chunk is the chain of steps of one
 // team (256 steps at 2^18 are one wave on every fourth SIMD), so the smoother,
 // which needs no further filter aggregate for it, works on sub-chunks.
@@ -58,10 +61,10 @@ struct QPArgs {
     int chunk;
     int G;          // chunks
     T *fagg[2];     // filter chunk aggregates / prefixes (ping-pong)
-    int sub;        // steps per sub-chunk of the smoother
-    int nsub;       // sub-chunks per chunk
-    T *elem;        // smoother elements of the sub-chunks
+    T *elem;        // smoother elements of the steps or of the sub-chunks
     T *sagg[2];     // smoother elements of the chunks / suffixes (ping-pong)
+    int sub;        // sub-chunks: steps per sub-chunk of the smoother
+    int nsub;       // sub-chunks per chunk
     double *hand;   // per step: P h (D values), h m, one unused
     double *bound;  // per sub-chunk, by rows: Cholesky factor of its end covariance, its diagonal's reciprocal, end mean
     double *partials;
@@ -172,10 +175,13 @@ __global__ __launch_bounds__(64) void qp_filter_level(const T *in, T *out, int G
 }
 
 // Filter finish: moments entering the chunk from the prefix of chunk g - 1,
-// then a Kalman filter in FP64 over the chunk. SMOOTH: the fixed-point smoother
-// of the state before every sub-chunk (G, m0, P0 as in lane_smoother_element)
-// and the handover.
-template <class L, typename T, bool SMOOTH>
+// then a Kalman filter in FP64 over the chunk. QP_ELEMS: the smoother element of
+// every step (iteration it builds the element of step k - 1 from the prediction
+// of step k; one extra iteration predicts past the chunk for the element of its
+// last step). QP_SUBS: the fixed-point smoother of the state before every
+// sub-chunk (G, m0, P0 as in lane_smoother_element) and the handover.
+enum : int { QP_ELEMS = 1, QP_SUBS = 2 };
+template <class L, typename T, int MODE>
 __global__ __launch_bounds__(64) void qp_filter_finish(QPArgs<T> a, QPDev m, const T *prefix)
 {
     extern __shared__ __align__(16) double qp_lds[];
@@ -201,10 +207,11 @@ __global__ __launch_bounds__(64) void qp_filter_finish(QPArgs<T> a, QPDev m, con
     constexpr int NFS = D * qsagg_fields<L>();
     double m0[R], P0[R][D], G[R][D];
     const double h0 = m.h[0];
+    constexpr bool ELEMS = (MODE & QP_ELEMS) != 0, SUBS = (MODE & QP_SUBS) != 0;
     QPInputs<T> in;
     in.start(a, k0);
-    for (int it = 0; it < a.chunk; it++) {
-        if constexpr (SMOOTH) {
+    for (int it = 0; it < a.chunk + (ELEMS ? 1 : 0); it++) {
+        if constexpr (SUBS) {
             if (it % a.sub == 0) {
 #pragma unroll
                 for (int s = 0; s < R; s++) {
@@ -220,19 +227,36 @@ __global__ __launch_bounds__(64) void qp_filter_finish(QPArgs<T> a, QPDev m, con
         T yn;
         uint8_t mn;
         in.fetch(k, tn, yn, mn);
-        const double dt = real ? in.dt(k) : 0.0;
+        const bool next = ELEMS && k == k1 && k1 > k0;  // element of the chunk's last step
+        const bool end = next && k1 >= a.n;             // past the series end: prior transition
+        const double dt = (real || (next && !end)) ? in.dt(k) : 0.0;
         if (real && !(dt >= 0.0)) bad |= (dt < 0.0) ? PSSGP_STATUS_UNSORTED : PSSGP_STATUS_NONFINITE;
         const bool obs = real && in.observed();
         const double yk = obs ? (double)in.yc : 0.0;
         in.advance(tn, yn, mn);
         QPStep<L::J> st;
-        qp_step<L::J>(m, dt, real && k == 0, !real, st);
+        qp_step<L::J>(m, dt, (real && k == 0) || end, !(real || next), st);
         // prediction in FP64: Y = F P, mp = F m, Pp = F P F^T + Q
         double Y[R][D], mp[R], Pp[R][D];
         qp_left_F<L, double, double>(st, P, Y, true);
         qp_left_F_vec<L, double, double>(st, mf, mp);
         qp_right_Ft_plus_Q<L, double>(st, Y, Pp);
-        if constexpr (SMOOTH) qp_left_F<L, double, double>(st, G, G, true);
+        if constexpr (SUBS) qp_left_F<L, double, double>(st, G, G, true);
+        if constexpr (ELEMS) {
+            // every team of the wave builds an element (the LDS transposes
+            // need uniform control flow); only those of steps k0..k1-1 are
+            // kept
+            const bool keep = k > k0 && (real || next);
+            QSAgg<L, T> e;
+            double Cl[R][D], rd[D];
+            uint32_t ebad = 0;
+            qp_element<L, T>(m, mf, P, Y, mp, Pp, Cl, rd, e, tbuf, ebad);
+            // the next step's loads are waited for before the element stores
+            // (the wait counter is in order)
+            asm volatile("" ::"v"(tn), "v"(yn), "v"((int)mn));
+            qsagg_store<L, T, T>(a.elem + (size_t)(keep ? k - 1 : 0) * NFS, e, keep);
+            bad |= keep ? ebad : 0u;
+        }
         // conditioning on y_k in FP64
         double c[D];
         qp_obs_combo<L, double>(m, Pp, c);
@@ -250,7 +274,7 @@ __global__ __launch_bounds__(64) void qp_filter_finish(QPArgs<T> a, QPDev m, con
         double K[D];
 #pragma unroll
         for (int j = 0; j < D; j++) K[j] = c[j] * w;
-        if constexpr (SMOOTH) {
+        if constexpr (SUBS) {
             // the next step's loads are waited for before the stores (the wait
             // counter is in order)
             asm volatile("" ::"v"(tn), "v"(yn), "v"((int)mn));
@@ -295,7 +319,7 @@ __global__ __launch_bounds__(64) void qp_filter_finish(QPArgs<T> a, QPDev m, con
                 for (int j = 0; j < D; j++) P[s][j] = fma(S * Kr, K[j], fma(-cr, K[j], fma(-Kr, c[j], Pp[s][j])));
             }
         }
-        if constexpr (SMOOTH) {
+        if constexpr (SUBS) {
             if ((it + 1) % a.sub == 0 || it + 1 == a.chunk) {
                 // the sub-chunk's element (every team of the wave builds one:
                 // the LDS transposes need uniform control flow) and end moments
@@ -349,6 +373,26 @@ __global__ __launch_bounds__(256) void qp_loglik_sum(const double *partials, int
     }
 }
 
+// The smoother element of each chunk from its steps'
+template <class L, typename T>
+__global__ __launch_bounds__(64) void qp_smoother_fold(QPArgs<T> a)
+{
+    const int g = team_id();
+    const int64_t k0 = (int64_t)g * a.chunk;
+    const int64_t k1 = min(k0 + (int64_t)a.chunk, a.n);
+    constexpr int NFS = L::D * qsagg_fields<L>();
+    QSAgg<L, T> acc;
+    qsagg_identity<L, T>(acc);
+    for (int it = 0; it < a.chunk; it++) {
+        const int64_t k = k0 + a.chunk - 1 - it;
+        const bool real = k < k1;
+        QSAgg<L, T> e;
+        qsagg_load<L, T, T>(a.elem + (size_t)(real ? k : 0) * NFS, e, real);
+        qsagg_combine<L, T>(e, acc, acc);
+    }
+    qsagg_store<L, T, T>(a.sagg[0] + (size_t)g * NFS, acc, g < a.G);
+}
+
 // The smoother element of each chunk from its sub-chunks' (the scan's levels
 // then run over the chunks: over the sub-chunks they took 100 instead of 41 us
 // each at 2^18 steps)
@@ -381,6 +425,44 @@ __global__ __launch_bounds__(64) void qp_smoother_level(const T *in, T *out, int
     qsagg_load<L, T, T>(in + (size_t)(has_y ? g + o : 0) * NFS, y, has_y);
     qsagg_combine<L, T>(x, y, x);
     qsagg_store<L, T, T>(out + (size_t)g * NFS, x, g < G);
+}
+
+// Smoother finish of one chunk from the elements of its steps: smoothed moments
+// after the chunk from the suffix of chunk g + 1 (none after the last chunk: the
+// last element has E = 0), then the RTS recursion backwards; f = h_0 z'_0 in the
+// smoother's coordinates.
+template <class L, typename T>
+__global__ __launch_bounds__(64) void qp_smoother_steps(QPArgs<T> a, QPDev m, const T *suffix)
+{
+    constexpr int D = L::D, R = L::RPL;
+    const int g = team_id();
+    const int64_t k0 = (int64_t)g * a.chunk;
+    const int64_t k1 = min(k0 + (int64_t)a.chunk, a.n);
+    constexpr int NFS = D * qsagg_fields<L>();
+    T ms[R], Ps[R][D];
+    {
+        QSAgg<L, T> suf;
+        const bool has = g + 1 < a.G;
+        qsagg_load<L, T, T>(suffix + (size_t)(has ? g + 1 : 0) * NFS, suf, has);
+#pragma unroll
+        for (int s = 0; s < R; s++) {
+            ms[s] = has ? suf.g[s] : T(0);
+#pragma unroll
+            for (int j = 0; j < D; j++) Ps[s][j] = has ? suf.L_[s][j] : T(0);
+        }
+    }
+    const double h0 = m.h[0];
+    for (int it = 0; it < a.chunk; it++) {
+        const int64_t k = k0 + a.chunk - 1 - it;
+        const bool real = k < k1;
+        QSAgg<L, T> e;
+        qsagg_load<L, T, T>(a.elem + (size_t)(real ? k : 0) * NFS, e, real);
+        qsagg_apply<L, T>(e, ms, Ps);
+        if (real && team_lane() == 0) {
+            a.f_mean[k] = T(h0 * (double)ms[0]);
+            a.f_var[k] = T(h0 * h0 * (double)Ps[0][0]);
+        }
+    }
 }
 
 // Smoother finish of one sub-chunk: the smoothed moments of its last step from
@@ -632,16 +714,21 @@ int qp_launch_t(const QPDev &m, const QPLaunch &q, hipStream_t s)
         src ^= 1;
     }
     if (q.ev && q.ev[2]) (void)hipEventRecord((hipEvent_t)q.ev[2], s);
-    if (q.hand)
-        hipLaunchKernelGGL((qp_filter_finish<L, T, true>), grid, block, lds_finish, s, a, m, (const T *)a.fagg[src]);
+    constexpr bool SUBS = qp_sub_handover(sizeof(T) == 8);
+    if (q.elem)
+        hipLaunchKernelGGL((qp_filter_finish<L, T, SUBS ? QP_SUBS : QP_ELEMS>), grid, block, lds_finish, s, a, m,
+                           (const T *)a.fagg[src]);
     else
-        hipLaunchKernelGGL((qp_filter_finish<L, T, false>), grid, block, lds_finish, s, a, m, (const T *)a.fagg[src]);
+        hipLaunchKernelGGL((qp_filter_finish<L, T, 0>), grid, block, lds_finish, s, a, m, (const T *)a.fagg[src]);
     hipLaunchKernelGGL(qp_loglik_sum, dim3(1), dim3(256), 0, s, (const double *)a.partials, q.G, q.loglik);
     if (q.ev && q.ev[3]) (void)hipEventRecord((hipEvent_t)q.ev[3], s);
     int rc = (int)hipGetLastError();
-    if (rc || !q.hand) return rc;
+    if (rc || !q.elem) return rc;
     if (q.ev && q.ev[4]) (void)hipEventRecord((hipEvent_t)q.ev[4], s);
-    hipLaunchKernelGGL((qp_smoother_join<L, T>), grid, block, 0, s, a);
+    if constexpr (SUBS)
+        hipLaunchKernelGGL((qp_smoother_join<L, T>), grid, block, 0, s, a);
+    else
+        hipLaunchKernelGGL((qp_smoother_fold<L, T>), grid, block, 0, s, a);
     if (q.ev && q.ev[5]) (void)hipEventRecord((hipEvent_t)q.ev[5], s);
     src = 0;
     for (int o = 1; o < q.G; o <<= 1) {
@@ -649,9 +736,13 @@ int qp_launch_t(const QPDev &m, const QPLaunch &q, hipStream_t s)
                            q.G, o);
         src ^= 1;
     }
-    const dim3 sgrid((unsigned)(((int64_t)q.G * q.nsub + TEAMS - 1) / TEAMS));
     if (q.ev && q.ev[6]) (void)hipEventRecord((hipEvent_t)q.ev[6], s);
-    hipLaunchKernelGGL((qp_smoother_finish<L, T>), sgrid, block, lds_finish, s, a, m, (const T *)a.sagg[src]);
+    if constexpr (SUBS) {
+        const dim3 sgrid((unsigned)(((int64_t)q.G * q.nsub + TEAMS - 1) / TEAMS));
+        hipLaunchKernelGGL((qp_smoother_finish<L, T>), sgrid, block, lds_finish, s, a, m, (const T *)a.sagg[src]);
+    } else {
+        hipLaunchKernelGGL((qp_smoother_steps<L, T>), grid, block, 0, s, a, m, (const T *)a.sagg[src]);
+    }
     if (q.ev && q.ev[7]) (void)hipEventRecord((hipEvent_t)q.ev[7], s);
     return (int)hipGetLastError();
 }

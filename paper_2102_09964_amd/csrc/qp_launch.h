@@ -8,6 +8,13 @@
 
 struct pssgp_model;
 
+// What the filter of a fused call hands to its smoother: a smoother element per
+// sub-chunk and two products per step (true), or an element per step. As with
+// the one-lane scans (lane_handover) the first costs f_var digits that FP64 is
+// chosen for: 10 states, gaps of 0.1, noise variance 1e-4, test points between
+// the observations 7e-11 against 1e-13; noise 1e-12 and denser, wrong.
+constexpr bool qp_sub_handover(bool f64) { return !f64; }
+
 struct QPLaunch {
     void *const *ev;  // nullable: 8 events (filter fold, scan, finish, end; smoother fold, scan, finish, end)
     const double *t;
@@ -17,11 +24,12 @@ struct QPLaunch {
     int chunk;
     int G;              // chunks of `chunk` steps
     void *fagg[2];      // G filter aggregates each (ping-pong)
-    int sub, nsub;      // smoother: steps per sub-chunk, sub-chunks per chunk
-    void *elem;         // G nsub smoother elements of the sub-chunks
+    void *elem;         // smoother elements: n of the steps or, with hand, G nsub of the sub-chunks;
+                        //   NULL: log-likelihood only
+    int sub, nsub;      // hand: steps per sub-chunk of the smoother, sub-chunks per chunk
     void *sagg[2];      // G smoother elements each (ping-pong)
-    double *hand;       // n (d + 2) values handed to the smoother; NULL: log-likelihood only
-    double *bound;      // G nsub d (d + 2): end moments of the sub-chunks
+    double *hand;       // nullable (qp_sub_handover): n (d + 2) values handed to the smoother
+    double *bound;      // hand: G nsub d (d + 2), end moments of the sub-chunks
     double *partials;   // G
     double *loglik;     // device double[1]
     void *f_mean;
