@@ -17,7 +17,8 @@
 //                   (qp_sub_handover): next to it runs the fixed-point smoother
 //                   of the state before each sub-chunk of steps, which gives
 //                   one smoother element per sub-chunk (qp_element), and P h,
-//                   h m of every step go to the smoother
+//                   h m, the innovation and the length of every step go to the
+//                   smoother, which reads no input
 //   loglik          one workgroup sums the per-chunk partials in chunk order
 //   smoother fold   each team composes its chunk's elements right to left, or
 //   smoother join   those of its chunk's sub-chunks
@@ -65,7 +66,8 @@ struct QPArgs {
     T *sagg[2];     // smoother elements of the chunks / suffixes (ping-pong)
     int sub;        // sub-chunks: steps per sub-chunk of the smoother
     int nsub;       // sub-chunks per chunk
-    double *hand;   // per step: P h (D values), h m, one unused
+    double *hand;   // per step: P h (D values), h m, innovation (0 at a missing step), length (sign bit set
+                    //   at a missing step)
     double *bound;  // per sub-chunk, by rows: Cholesky factor of its end covariance, its diagonal's reciprocal, end mean
     double *partials;
     double *loglik;
@@ -280,7 +282,7 @@ __global__ __launch_bounds__(64) void qp_filter_finish(QPArgs<T> a, QPDev m, con
             asm volatile("" ::"v"(tn), "v"(yn), "v"((int)mn));
             double wh[D];
             qp_obs_combo<L, double>(m, G, wh);  // G^T h
-            double *hp = a.hand + (size_t)(real ? k : 0) * (D + 2);
+            double *hp = a.hand + (size_t)(real ? k : 0) * (D + 3);
 #pragma unroll
             for (int s = 0; s < R; s++) {
                 const int row = team_lane() + QP_TEAM * s;
@@ -293,7 +295,11 @@ __global__ __launch_bounds__(64) void qp_filter_finish(QPArgs<T> a, QPDev m, con
                     G[s][j] = fma(-Kr, wh[j], G[s][j]);
                 }
             }
-            if (real && team_lane() == 0) hp[D] = hm;
+            if (real && team_lane() == 0) {
+                hp[D] = hm;
+                hp[D + 1] = v;
+                hp[D + 2] = __builtin_copysign(dt, obs ? 1.0 : -1.0);
+            }
             // row 0 of G from h G = r G^T h, r = R / S: as a difference it
             // would lose log10(S / R) digits
             const double rs = obs ? m.R * w : 1.0;
@@ -579,24 +585,19 @@ __global__ __launch_bounds__(64) void qp_smoother_finish(QPArgs<T> a, QPDev m, c
 #pragma unroll
         for (int j = 0; j < D; j++) Lam[0][j] = has && row < D ? Ps[0][j] : 0.0;
     }
-    // inputs of a step (clamped into the series): P h and h m, the times of
-    // the step and of the one before it, its observation and mask
+    // what the filter handed over of a step (clamped into the series): P h; h m,
+    // innovation, length and mask
     struct In {
-        double ph[D], hm, tc, tp;
-        T y;
-        uint8_t mk;
+        double ph[D], hm, v, dt;
     };
-    const uint8_t *mk = a.mask ? a.mask : (const uint8_t *)a.t;
     auto fetch = [&](int64_t k, In &x) {
         const int64_t c = k < 0 ? 0 : (k < a.n ? k : a.n - 1);
-        const double *hp = a.hand + (size_t)c * (D + 2);
+        const double *hp = a.hand + (size_t)c * (D + 3);
 #pragma unroll
         for (int j = 0; j < D; j++) x.ph[j] = hp[j];
         x.hm = hp[D];
-        x.tc = a.t[c];
-        x.tp = a.t[c > 0 ? c - 1 : 0];
-        x.y = a.y[c];
-        x.mk = mk[c];
+        x.v = hp[D + 1];
+        x.dt = hp[D + 2];
     };
     In x, nx;
     fetch(k0 + a.sub - 1, x);
@@ -604,7 +605,7 @@ __global__ __launch_bounds__(64) void qp_smoother_finish(QPArgs<T> a, QPDev m, c
         const int64_t k = k0 + a.sub - 1 - it;
         const bool real = any && k < k1;
         fetch(k - 1, nx);
-        const bool obs = real && (!a.mask || x.mk != 0);
+        const bool obs = real && !__builtin_signbit(x.dt);
         // Lambda' = S^-T Lambda S^-1, lambda' = S^-T lambda, P h in z'
         {
             double l0[D];
@@ -621,7 +622,7 @@ __global__ __launch_bounds__(64) void qp_smoother_finish(QPArgs<T> a, QPDev m, c
         }
         const double hph = h0 * x.ph[0], S = m.R + hph;
         const double w = obs ? 1.0 / S : 0.0;
-        const double v = obs ? (double)x.y - x.hm : 0.0;
+        const double v = obs ? x.v : 0.0;
         const double r = obs ? m.R * w : 1.0;
         const double hw = h0 * w;
         double tt = 0.0;
@@ -661,7 +662,7 @@ __global__ __launch_bounds__(64) void qp_smoother_finish(QPArgs<T> a, QPDev m, c
         // over the transition into the step (none past the end)
         if (it + 1 < a.sub) {
             QPStep<L::J> st;
-            qp_step<L::J>(m, real && k > 0 ? x.tc - x.tp : 0.0, real && k == 0, !real, st);
+            qp_step<L::J>(m, real ? __builtin_fabs(x.dt) : 0.0, real && k == 0, !real, st);
             qp_right_F<L>(st, Lam, Lam);
             qp_left_Ft<L>(st, Lam, lam);
         }

@@ -64,3 +64,12 @@ def test_batched(dtype):
     check_overlaps(lambda: P.BatchedPipeline(w["kinds"], w["offsets"], w["params"], dtype=dtype,
                                              options=P.make_options(chunk=4)),
                    t, torch.nan_to_num(y).to(getattr(torch, dtype)), mask.to(torch.uint8))
+
+
+@pytest.mark.parametrize("dtype", ["float32", "float64"])
+@pytest.mark.parametrize("chunk", [16, 100])
+def test_quasiperiodic(chunk, dtype):
+    n = 100 * 2100 + 7
+    t, y, mask = _inputs(n, dtype)
+    m = P.make_model(workloads.co2_like(2, J=1)["model"]["components"], 0.01)
+    check_overlaps(lambda: P.Pipeline(m, n, dtype, options=P.make_options(chunk=chunk)), t, y, mask)
