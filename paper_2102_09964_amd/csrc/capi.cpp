@@ -601,7 +601,7 @@ QPPlan qp_plan(int d, int64_t n, pssgp_dtype dtype, bool elems, const pssgp_opti
         p.off_s[0] = take(G * nf_s * p.tsize);
         p.off_s[1] = take(G * nf_s * p.tsize);
         if (qp_sub_handover(f64)) {
-            p.off_hand = take(steps * (d + 3) * sizeof(double));
+            p.off_hand = take((steps + G) * (d + 3) * sizeof(double));
             p.off_bound = take(ns * d * (d + 2) * sizeof(double));
         }
     }

@@ -15,10 +15,13 @@
 //                   Kalman filter in FP64 and sums the log-likelihood terms.
 //                   FP64: it writes the smoother element of every step. FP32
 //                   (qp_sub_handover): next to it runs the fixed-point smoother
-//                   of the state before each sub-chunk of steps, which gives
-//                   one smoother element per sub-chunk (qp_element), and P h,
-//                   h m, the innovation and the length of every step go to the
-//                   smoother, which reads no input
+//                   of the state that each sub-chunk of steps starts from,
+//                   which gives one smoother element per sub-chunk
+//                   (qp_sub_element), and P h, h m, the innovation and the
+//                   length of every step go to the smoother, which reads no
+//                   input. As the lanes of the one-lane scans, the chunks
+//                   overlap by a step: a chunk's first sub-chunk starts from
+//                   its first step and its last one ends with the next chunk's
 //   loglik          one workgroup sums the per-chunk partials in chunk order
 //   smoother fold   each team composes its chunk's elements right to left, or
 //   smoother join   those of its chunk's sub-chunks
@@ -66,9 +69,10 @@ struct QPArgs {
     T *sagg[2];     // smoother elements of the chunks / suffixes (ping-pong)
     int sub;        // sub-chunks: steps per sub-chunk of the smoother
     int nsub;       // sub-chunks per chunk
-    double *hand;   // per step: P h (D values), h m, innovation (0 at a missing step), length (sign bit set
-                    //   at a missing step)
-    double *bound;  // per sub-chunk, by rows: Cholesky factor of its end covariance, its diagonal's reciprocal, end mean
+    double *hand;   // per step, then per chunk for the step that it shares with the next: P h (D values),
+                    //   h m, innovation (0 at a missing step), length (sign bit set at a missing step)
+    double *bound;  // per sub-chunk, by rows, in the smoother's coordinates: Cholesky factor of its end
+                    //   covariance, its diagonal's reciprocal, end mean
     double *partials;
     double *loglik;
     T *f_mean;
@@ -180,8 +184,10 @@ __global__ __launch_bounds__(64) void qp_filter_level(const T *in, T *out, int G
 // then a Kalman filter in FP64 over the chunk. QP_ELEMS: the smoother element of
 // every step (iteration it builds the element of step k - 1 from the prediction
 // of step k; one extra iteration predicts past the chunk for the element of its
-// last step). QP_SUBS: the fixed-point smoother of the state before every
-// sub-chunk (G, m0, P0 as in lane_smoother_element) and the handover.
+// last step). QP_SUBS: the fixed-point smoother of the state that every sub-chunk
+// starts from (G, m0, P0 as in lane_smoother_element), which is the last step of
+// the sub-chunk before it or the chunk's first step, and the handover; one extra
+// iteration is the first step of the next chunk.
 enum : int { QP_ELEMS = 1, QP_SUBS = 2 };
 template <class L, typename T, int MODE>
 __global__ __launch_bounds__(64) void qp_filter_finish(QPArgs<T> a, QPDev m, const T *prefix)
@@ -208,21 +214,20 @@ __global__ __launch_bounds__(64) void qp_filter_finish(QPArgs<T> a, QPDev m, con
     double ll = 0.0;
     constexpr int NFS = D * qsagg_fields<L>();
     double m0[R], P0[R][D], G[R][D];
+    auto restart = [&]() {
+#pragma unroll
+        for (int s = 0; s < R; s++) {
+            m0[s] = mf[s];
+#pragma unroll
+            for (int j = 0; j < D; j++) P0[s][j] = G[s][j] = P[s][j];
+        }
+    };
     const double h0 = m.h[0];
     constexpr bool ELEMS = (MODE & QP_ELEMS) != 0, SUBS = (MODE & QP_SUBS) != 0;
     QPInputs<T> in;
     in.start(a, k0);
-    for (int it = 0; it < a.chunk + (ELEMS ? 1 : 0); it++) {
-        if constexpr (SUBS) {
-            if (it % a.sub == 0) {
-#pragma unroll
-                for (int s = 0; s < R; s++) {
-                    m0[s] = mf[s];
-#pragma unroll
-                    for (int j = 0; j < D; j++) P0[s][j] = G[s][j] = P[s][j];
-                }
-            }
-        }
+    if constexpr (SUBS) restart();
+    for (int it = 0; it < a.chunk + (MODE != 0 ? 1 : 0); it++) {
         const int64_t k = k0 + it;
         const bool real = k < k1;
         double tn;
@@ -231,13 +236,15 @@ __global__ __launch_bounds__(64) void qp_filter_finish(QPArgs<T> a, QPDev m, con
         in.fetch(k, tn, yn, mn);
         const bool next = ELEMS && k == k1 && k1 > k0;  // element of the chunk's last step
         const bool end = next && k1 >= a.n;             // past the series end: prior transition
-        const double dt = (real || (next && !end)) ? in.dt(k) : 0.0;
+        const bool over = SUBS && it == a.chunk && g < a.G && k < a.n;  // the step shared with the next chunk
+        const bool live = real || over;
+        const double dt = (live || (next && !end)) ? in.dt(k) : 0.0;
         if (real && !(dt >= 0.0)) bad |= (dt < 0.0) ? PSSGP_STATUS_UNSORTED : PSSGP_STATUS_NONFINITE;
-        const bool obs = real && in.observed();
+        const bool obs = live && in.observed();
         const double yk = obs ? (double)in.yc : 0.0;
         in.advance(tn, yn, mn);
         QPStep<L::J> st;
-        qp_step<L::J>(m, dt, (real && k == 0) || end, !(real || next), st);
+        qp_step<L::J>(m, dt, (real && k == 0) || end, !(live || next), st);
         // prediction in FP64: Y = F P, mp = F m, Pp = F P F^T + Q
         double Y[R][D], mp[R], Pp[R][D];
         qp_left_F<L, double, double>(st, P, Y, true);
@@ -272,22 +279,23 @@ __global__ __launch_bounds__(64) void qp_filter_finish(QPArgs<T> a, QPDev m, con
         if (obs && !isfinite(yk)) bad |= PSSGP_STATUS_NONFINITE;
         const double w = obs ? 1.0 / S : 0.0;
         const double v = obs ? yk - hm : 0.0;
-        ll += obs ? -0.5 * (log(6.283185307179586 * S) + v * v * w) : 0.0;
+        ll += (obs && real) ? -0.5 * (log(6.283185307179586 * S) + v * v * w) : 0.0;
         double K[D];
 #pragma unroll
         for (int j = 0; j < D; j++) K[j] = c[j] * w;
+        double gh[D];  // row 0 of S G after the conditioning: h G / h_0 = r G^T h / h_0
         if constexpr (SUBS) {
             // the next step's loads are waited for before the stores (the wait
             // counter is in order)
             asm volatile("" ::"v"(tn), "v"(yn), "v"((int)mn));
             double wh[D];
             qp_obs_combo<L, double>(m, G, wh);  // G^T h
-            double *hp = a.hand + (size_t)(real ? k : 0) * (D + 3);
+            double *hp = a.hand + (size_t)(real ? k : (over ? a.n + g : 0)) * (D + 3);
 #pragma unroll
             for (int s = 0; s < R; s++) {
                 const int row = team_lane() + QP_TEAM * s;
                 const double cr = qp_pick<D>(c, row), Kr = cr * w, whr = qp_pick<D>(wh, row);
-                if (real && row < D) hp[row] = cr;
+                if (live && row < D) hp[row] = cr;
                 m0[s] = fma(whr * w, v, m0[s]);
 #pragma unroll
                 for (int j = 0; j < D; j++) {
@@ -295,7 +303,7 @@ __global__ __launch_bounds__(64) void qp_filter_finish(QPArgs<T> a, QPDev m, con
                     G[s][j] = fma(-Kr, wh[j], G[s][j]);
                 }
             }
-            if (real && team_lane() == 0) {
+            if (live && team_lane() == 0) {
                 hp[D] = hm;
                 hp[D + 1] = v;
                 hp[D + 2] = __builtin_copysign(dt, obs ? 1.0 : -1.0);
@@ -305,7 +313,10 @@ __global__ __launch_bounds__(64) void qp_filter_finish(QPArgs<T> a, QPDev m, con
             const double rs = obs ? m.R * w : 1.0;
             double g0[D];
 #pragma unroll
-            for (int j = 0; j < D; j++) g0[j] = rs * wh[j];
+            for (int j = 0; j < D; j++) {
+                g0[j] = rs * wh[j];
+                gh[j] = g0[j] / h0;
+            }
             sfor<1, L::NO>([&](auto qc) {
                 constexpr int r = L::obs_row(decltype(qc)::value);
                 const double hr = m.h[r];
@@ -315,7 +326,7 @@ __global__ __launch_bounds__(64) void qp_filter_finish(QPArgs<T> a, QPDev m, con
 #pragma unroll
             for (int j = 0; j < D; j++) G[0][j] = (obs && team_lane() == 0) ? g0[j] / h0 : G[0][j];
         }
-        if (real) {
+        if (live) {
 #pragma unroll
             for (int s = 0; s < R; s++) {
                 const int row = team_lane() + QP_TEAM * s;
@@ -326,37 +337,51 @@ __global__ __launch_bounds__(64) void qp_filter_finish(QPArgs<T> a, QPDev m, con
             }
         }
         if constexpr (SUBS) {
-            if ((it + 1) % a.sub == 0 || it + 1 == a.chunk) {
+            if (it == 0) restart();
+            if (it == a.chunk || ((it + 1) % a.sub == 0 && it + 1 < a.chunk)) {
                 // the sub-chunk's element (every team of the wave builds one:
                 // the LDS transposes need uniform control flow) and end moments
-                const int q = it / a.sub;
+                const int q = it == a.chunk ? a.nsub - 1 : it / a.sub;
                 const int64_t s0 = k0 + (int64_t)q * a.sub;
-                const bool any = s0 < k1, end = k + 1 >= a.n;
+                const bool any = s0 < k1, end = it == a.chunk ? !over : k + 1 >= a.n;
                 const size_t es = (size_t)g * a.nsub + q;
-                if (end) {
+                // S P S^T, S m and the first row of S G from the conditioning:
+                // r P h / h_0, f / h_0 and r h G / h_0, r = R / S (1 at a missing
+                // step). At the chunk's first step G is the filtered P
+                const int row = team_lane();
+                const double r = obs ? m.R * w : 1.0, rh = r / h0;
+                double hph = 0.0;
+                sfor<0, L::NO>([&](auto qc) {
+                    constexpr int o = L::obs_row(decltype(qc)::value);
+                    hph = fma(m.h[o], c[o], hph);
+                });
+                double Cl[R][D], ms[R], Gs[R][D], rd[D];
 #pragma unroll
-                    for (int s = 0; s < R; s++)
-#pragma unroll
-                        for (int j = 0; j < D; j++) G[s][j] = 0.0;
+                for (int j = 0; j < D; j++) {
+                    Cl[0][j] = row == 0 ? rh * c[j] : P[0][j];
+                    const double g0 = it == 0 ? rh * c[j] : gh[j];
+                    Gs[0][j] = end ? 0.0 : (row == 0 ? g0 : G[0][j]);
                 }
+                Cl[0][0] = rh * (row == 0 ? hph / h0 : qp_pick<D>(c, row));
+                if (end) {  // E = 0, and P need not have a factor
+#pragma unroll
+                    for (int j = 0; j < D; j++) Cl[0][j] = row == j ? 1.0 : 0.0;
+                }
+                ms[0] = row == 0 ? fma(hph * w, v, hm) / h0 : mf[0];
                 QSAgg<L, T> e;
-                double Cl[R][D], rd[D];
                 uint32_t ebad = 0;
-                qp_element<L, T>(m, m0, P0, G, mf, P, Cl, rd, e, tbuf, ebad);
+                qp_sub_element<L, T>(m, m0, P0, Gs, ms, Cl, rd, e, tbuf, ebad);
                 bad |= any ? ebad : 0u;
                 if (!any) qsagg_identity<L, T>(e);
                 qsagg_store<L, T, T>(a.elem + es * NFS, e, g < a.G);
                 double *bp = a.bound + es * (size_t)(D * (D + 2));
+                if (any && row < D) {
 #pragma unroll
-                for (int s = 0; s < R; s++) {
-                    const int row = team_lane() + QP_TEAM * s;
-                    if (any && row < D) {
-#pragma unroll
-                        for (int j = 0; j < D; j++) bp[row * (D + 2) + j] = Cl[s][j];
-                        bp[row * (D + 2) + D] = qp_pick<D>(rd, row);
-                        bp[row * (D + 2) + D + 1] = mf[s];
-                    }
+                    for (int j = 0; j < D; j++) bp[row * (D + 2) + j] = Cl[0][j];
+                    bp[row * (D + 2) + D] = qp_pick<D>(rd, row);
+                    bp[row * (D + 2) + D + 1] = ms[0];
                 }
+                restart();
             }
         }
     }
@@ -471,11 +496,12 @@ __global__ __launch_bounds__(64) void qp_smoother_steps(QPArgs<T> a, QPDev m, co
     }
 }
 
-// Smoother finish of one sub-chunk: the smoothed moments of its last step from
-// the elements after it (none after the series' end), then the
-// recursion of (lambda, Lambda) backwards (smoother_tile_fused has the
-// formulas); row i of Lambda on team lane i, in FP64. In the coordinates
-// z' = S z the observation row is h_0 times the first unit vector.
+// Smoother finish of one sub-chunk: the smoothed moments of its last step (a
+// chunk's last sub-chunk: of the next chunk's first) from the elements after it
+// (none after the series' end), then the recursion of (lambda, Lambda) backwards
+// (smoother_tile_fused has the formulas); row i of Lambda on team lane i, in
+// FP64. In the coordinates z' = S z the observation row is h_0 times the first
+// unit vector.
 template <class L, typename T>
 __global__ __launch_bounds__(64) void qp_smoother_finish(QPArgs<T> a, QPDev m, const T *suffix)
 {
@@ -530,26 +556,6 @@ __global__ __launch_bounds__(64) void qp_smoother_finish(QPArgs<T> a, QPDev m, c
 #pragma unroll
             for (int j = 0; j < D; j++) Ps[0][j] = has ? (double)Lm[0][j] : 0.0;
         }
-        // back to the filter's coordinates: m = S^-1 m', P = S^-1 P' S^-T
-        {
-            double r0[D], rm = 0.0;
-#pragma unroll
-            for (int j = 0; j < D; j++) r0[j] = 0.0;
-            sfor<1, L::NO>([&](auto qc) {
-                constexpr int r = L::obs_row(decltype(qc)::value);
-#pragma unroll
-                for (int j = 0; j < D; j++) r0[j] = fma(u[r], team_get<r>(Ps[0][j]), r0[j]);
-                rm = fma(u[r], team_get<r>(ms[0]), rm);
-            });
-            ms[0] -= row == 0 ? rm : 0.0;
-            double c0 = 0.0;
-#pragma unroll
-            for (int j = 0; j < D; j++) {
-                Ps[0][j] -= row == 0 ? r0[j] : 0.0;
-                c0 = fma(u[j], Ps[0][j], c0);
-            }
-            Ps[0][0] -= c0;
-        }
         const double *bp = a.bound + (size_t)(any ? es : 0) * (D * (D + 2));
         double Cl[R][D], Ct[R][D], rdr[R], rd[D];
         const bool ok = any && row < D;
@@ -585,13 +591,15 @@ __global__ __launch_bounds__(64) void qp_smoother_finish(QPArgs<T> a, QPDev m, c
 #pragma unroll
         for (int j = 0; j < D; j++) Lam[0][j] = has && row < D ? Ps[0][j] : 0.0;
     }
-    // what the filter handed over of a step (clamped into the series): P h; h m,
-    // innovation, length and mask
+    // what the filter handed over of a step (clamped into the sub-chunk): P h;
+    // h m, innovation, length and mask
     struct In {
         double ph[D], hm, v, dt;
     };
+    const bool over = any && k1 == kc + a.chunk && k1 < a.n;
+    const int64_t kl = over ? k1 : k1 - 1;  // last step of the run
     auto fetch = [&](int64_t k, In &x) {
-        const int64_t c = k < 0 ? 0 : (k < a.n ? k : a.n - 1);
+        const int64_t c = !any ? 0 : (over && k == k1) ? a.n + g : (k > k0 ? k : k0);
         const double *hp = a.hand + (size_t)c * (D + 3);
 #pragma unroll
         for (int j = 0; j < D; j++) x.ph[j] = hp[j];
@@ -600,26 +608,16 @@ __global__ __launch_bounds__(64) void qp_smoother_finish(QPArgs<T> a, QPDev m, c
         x.dt = hp[D + 2];
     };
     In x, nx;
-    fetch(k0 + a.sub - 1, x);
-    for (int it = 0; it < a.sub; it++) {
-        const int64_t k = k0 + a.sub - 1 - it;
-        const bool real = any && k < k1;
+    fetch(kl, x);
+    for (int it = 0; it <= a.sub; it++) {
+        const int64_t k = kl - it;
+        const bool live = any && k >= k0;
         fetch(k - 1, nx);
-        const bool obs = real && !__builtin_signbit(x.dt);
-        // Lambda' = S^-T Lambda S^-1, lambda' = S^-T lambda, P h in z'
-        {
-            double l0[D];
-            qp_row<L, 0>(Lam, l0);
-            const double lm0 = team_get<0>(lam[0]);
-            lam[0] = fma(-ur, lm0, lam[0]);
-#pragma unroll
-            for (int j = 0; j < D; j++) Lam[0][j] = fma(-ur, l0[j], Lam[0][j]);
-            sfor<1, L::NO>([&](auto qc) {
-                constexpr int r = L::obs_row(decltype(qc)::value);
-                Lam[0][r] = fma(-u[r], Lam[0][0], Lam[0][r]);
-                x.ph[0] = fma(u[r], x.ph[r], x.ph[0]);
-            });
-        }
+        const bool obs = live && !__builtin_signbit(x.dt);
+        sfor<1, L::NO>([&](auto qc) {  // P h in z'
+            constexpr int r = L::obs_row(decltype(qc)::value);
+            x.ph[0] = fma(u[r], x.ph[r], x.ph[0]);
+        });
         const double hph = h0 * x.ph[0], S = m.R + hph;
         const double w = obs ? 1.0 / S : 0.0;
         const double v = obs ? x.v : 0.0;
@@ -635,11 +633,11 @@ __global__ __launch_bounds__(64) void qp_smoother_finish(QPArgs<T> a, QPDev m, c
         const double us = team_sum(rest * sr), ul = team_sum(rest * lam[0]);
         const double lam0 = team_get<0>(lam[0]), s0 = team_get<0>(sr);
         const double phl = fma(x.ph[0], lam0, ul);
-        if (real && row == 0) {
+        if (live && k < k1 && row == 0) {
             a.f_mean[k] = T(fma(r, phl, fma(hph * w, v, x.hm)));
             a.f_var[k] = T(r * fma(-r, phq, hph));
         }
-        // the observation's update; for a step past the end it is the identity
+        // the observation's update (the identity before the sub-chunk's first step)
         {
             const double l00 = fma(-hw, us, fma(r, s0, h0 * hw));
             double col[R], l0[D];
@@ -659,12 +657,23 @@ __global__ __launch_bounds__(64) void qp_smoother_finish(QPArgs<T> a, QPDev m, c
                 Lam[0][rr] = fma(u[rr], Lam[0][0], Lam[0][rr]);
             });
         }
-        // over the transition into the step (none past the end)
-        if (it + 1 < a.sub) {
+        // over the transition into the step
+        if (it < a.sub) {
             QPStep<L::J> st;
-            qp_step<L::J>(m, real ? __builtin_fabs(x.dt) : 0.0, real && k == 0, !real, st);
+            qp_step<L::J>(m, live ? __builtin_fabs(x.dt) : 0.0, false, !live, st);
             qp_right_F<L>(st, Lam, Lam);
             qp_left_Ft<L>(st, Lam, lam);
+            // back: Lambda' = S^-T Lambda S^-1, lambda' = S^-T lambda
+            double l0[D];
+            qp_row<L, 0>(Lam, l0);
+            const double lm0 = team_get<0>(lam[0]);
+            lam[0] = fma(-ur, lm0, lam[0]);
+#pragma unroll
+            for (int j = 0; j < D; j++) Lam[0][j] = fma(-ur, l0[j], Lam[0][j]);
+            sfor<1, L::NO>([&](auto qc) {
+                constexpr int r = L::obs_row(decltype(qc)::value);
+                Lam[0][r] = fma(-u[r], Lam[0][0], Lam[0][r]);
+            });
         }
         x = nx;
     }

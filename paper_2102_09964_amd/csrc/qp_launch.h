@@ -28,7 +28,7 @@ struct QPLaunch {
                         //   NULL: log-likelihood only
     int sub, nsub;      // hand: steps per sub-chunk of the smoother, sub-chunks per chunk
     void *sagg[2];      // G smoother elements each (ping-pong)
-    double *hand;       // nullable (qp_sub_handover): n (d + 3) values handed to the smoother
+    double *hand;       // nullable (qp_sub_handover): (n + G) (d + 3) values handed to the smoother
     double *bound;      // hand: G nsub d (d + 2), end moments of the sub-chunks
     double *partials;   // G
     double *loglik;     // device double[1]

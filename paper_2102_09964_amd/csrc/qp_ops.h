@@ -794,6 +794,35 @@ __device__ __forceinline__ void qp_backward(const double (&Ct)[L::RPL][L::D], co
     });
 }
 
+// Cl <- its Cholesky factor (lower triangle by rows), right-looking: column k,
+// then the trailing update; rd the reciprocals of its diagonal
+template <class L>
+__device__ __forceinline__ void qp_cholesky(double (&Cl)[L::RPL][L::D], double (&rd)[L::D], uint32_t &bad)
+{
+    constexpr int D = L::D, R = L::RPL;
+    sfor<0, D>([&](auto kc) {
+        constexpr int k = decltype(kc)::value;
+        const double dkk = team_get<k % QP_TEAM>(Cl[k / QP_TEAM][k]);
+        if (!(dkk > 0.0)) bad |= 8u;  // PSSGP_STATUS_CHOLESKY
+        const double dd = sqrt(dkk);
+        const double inv = 1.0 / dd;
+        rd[k] = inv;
+        double l[R];
+#pragma unroll
+        for (int s = 0; s < R; s++) {
+            const int row = team_lane() + QP_TEAM * s;
+            l[s] = row > k ? Cl[s][k] * inv : 0.0;
+            Cl[s][k] = row > k ? l[s] : (row == k ? dd : 0.0);
+        }
+        sfor<k + 1, D>([&](auto jc) {
+            constexpr int j = decltype(jc)::value;
+            const double lj = team_get<j % QP_TEAM>(l[j / QP_TEAM]);
+#pragma unroll
+            for (int s = 0; s < R; s++) Cl[s][j] = fma(-l[s], lj, Cl[s][j]);
+        });
+    });
+}
+
 // Smoother element of a run of steps (supplement, Proposition 2) in FP64: the
 // map from the smoothed moments of its last step to those of the step before
 // its first. From the fixed-point smoother of that earlier state, its moments
@@ -817,28 +846,7 @@ __device__ __forceinline__ void qp_element(const QPDev &m, const double (&mf)[L:
     for (int s = 0; s < R; s++)
 #pragma unroll
         for (int j = 0; j < D; j++) Cl[s][j] = Pp[s][j];
-    // Cholesky, right-looking: column k, then the trailing update
-    sfor<0, D>([&](auto kc) {
-        constexpr int k = decltype(kc)::value;
-        const double dkk = team_get<k % QP_TEAM>(Cl[k / QP_TEAM][k]);
-        if (!(dkk > 0.0)) bad |= 8u;  // PSSGP_STATUS_CHOLESKY
-        const double dd = sqrt(dkk);
-        const double inv = 1.0 / dd;
-        rd[k] = inv;
-        double l[R];
-#pragma unroll
-        for (int s = 0; s < R; s++) {
-            const int row = team_lane() + QP_TEAM * s;
-            l[s] = row > k ? Cl[s][k] * inv : 0.0;
-            Cl[s][k] = row > k ? l[s] : (row == k ? dd : 0.0);
-        }
-        sfor<k + 1, D>([&](auto jc) {
-            constexpr int j = decltype(jc)::value;
-            const double lj = team_get<j % QP_TEAM>(l[j / QP_TEAM]);
-#pragma unroll
-            for (int s = 0; s < R; s++) Cl[s][j] = fma(-l[s], lj, Cl[s][j]);
-        });
-    });
+    qp_cholesky<L>(Cl, rd, bad);
     qp_forward<L>(Cl, rd, Y);
     // L = P - Y^T Y
     {
@@ -909,5 +917,68 @@ __device__ __forceinline__ void qp_element(const QPDev &m, const double (&mf)[L:
             e.E[s][j] = T(E[s][j]);
             e.L_[s][j] = T(P[s][j]);
         }
+    }
+}
+
+// The same for a sub-chunk, in the smoother's coordinates throughout (as
+// lane_smoother_element): G with its first row already that of S G (h G / h_0),
+// mp = S m and Cl = S P S^T of the last step, whose first row and column come
+// from the last conditioning. Cl receives the factor.
+template <class L, typename T>
+__device__ __forceinline__ void qp_sub_element(const QPDev &m, double (&m0)[L::RPL], double (&P0)[L::RPL][L::D],
+                                               double (&G)[L::RPL][L::D], const double (&mp)[L::RPL],
+                                               double (&Cl)[L::RPL][L::D], double (&rd)[L::D], QSAgg<L, T> &e,
+                                               double *tbuf, uint32_t &bad)
+{
+    constexpr int D = L::D, R = L::RPL;
+    static_assert(R == 1, "one row per lane");
+    const bool r0 = team_lane() == 0;
+    qp_cholesky<L>(Cl, rd, bad);
+    // S P0 S^T, S m0, (S G) S^T
+    {
+        double add[D], addm = 0.0, cp = 0.0, cg = 0.0;
+#pragma unroll
+        for (int j = 0; j < D; j++) add[j] = 0.0;
+        sfor<1, L::NO>([&](auto qc) {
+            constexpr int r = L::obs_row(decltype(qc)::value);
+#pragma unroll
+            for (int j = 0; j < D; j++) add[j] = fma(m.u[r], team_get<r>(P0[0][j]), add[j]);
+            addm = fma(m.u[r], team_get<r>(m0[0]), addm);
+        });
+#pragma unroll
+        for (int j = 0; j < D; j++) P0[0][j] += r0 ? add[j] : 0.0;
+        m0[0] += r0 ? addm : 0.0;
+        sfor<1, L::NO>([&](auto qc) {
+            constexpr int r = L::obs_row(decltype(qc)::value);
+            cp = fma(P0[0][r], m.u[r], cp);
+            cg = fma(G[0][r], m.u[r], cg);
+        });
+        P0[0][0] += cp;
+        G[0][0] += cg;
+    }
+    qp_forward<L>(Cl, rd, G);
+    // L = S P0 S^T - Z^T Z
+    {
+        double ZT[R][D], ZZ[R][D];
+        qp_transpose<L, double>(G, ZT, tbuf);
+        qp_matmul<L, double, double>(ZT, G, ZZ);
+#pragma unroll
+        for (int j = 0; j < D; j++) P0[0][j] -= ZZ[0][j];
+        qp_symmetrize<L, double>(P0, tbuf);
+    }
+    double E[R][D], g[R], mpu[D];
+    {
+        double Ct[R][D];
+        qp_transpose<L, double>(Cl, Ct, tbuf);
+        qp_backward<L>(Ct, rd, G);
+    }
+    qp_transpose<L, double>(G, E, tbuf);
+    qp_gather<L, double, double>(mp, mpu);
+    qp_matvec<L, double, double>(E, mpu, g);
+    e.g[0] = T(m0[0] - g[0]);
+#pragma unroll
+    for (int j = 0; j < D; j++) {
+        e.E[0][j] = T(E[0][j]);
+        e.L_[0][j] = T(P0[0][j]);
     }
 }

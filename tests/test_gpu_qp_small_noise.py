@@ -44,3 +44,23 @@ def test_between_observations(J, noise, chunk):
     """FP64, gaps of a tenth of the longest length-scale, a third of the steps test
     points."""
     _check(J, 5.0, noise, 0.3, "float64", chunk)
+
+
+@pytest.mark.parametrize("chunk", [16, 64])
+@pytest.mark.parametrize("noise", [1e-2, 1e-10, 1e-18])
+@pytest.mark.parametrize("J", [1, 2, 3])
+def test_between_observations_fp32(J, noise, chunk):
+    """As above in FP32, whose chunks' moments differ by their rounding, and, at the
+    smallest noise, a filtered variance of f below the rounding of the predicted
+    one."""
+    _check(J, 5.0, noise, 0.3, "float32", chunk)
+
+
+@pytest.mark.parametrize("chunk", [16, 64])
+@pytest.mark.parametrize("J,gap,noise", [(J, 5.0, r) for J in (1, 2, 3) for r in (1e-2, 1e-3)] + [(2, 1.0, 1e-4)])
+def test_every_step_observed_fp32(J, gap, noise, chunk):
+    """Every step observed, f_var of the size of the noise. (At 1e-4 the rounding of
+    the chunks' FP32 moments puts 6e-5 to 1.0e-4 into f_var whatever the smoother
+    does; 12 states stay clear of the bar.)"""
+    _check(J, gap, noise, 0.0, "float32", chunk)
+
