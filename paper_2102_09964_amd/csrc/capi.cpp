@@ -35,15 +35,20 @@ struct Plan {
 
 // Default chunk of a scan over n steps. FP32: 16. FP64: as many tiles (one
 // wave each) as the chip has SIMDs (256 CUs x 4), or fewer where even
-// kMinDefaultChunk steps per lane do not give as many, and 16 at most. With a
+// min_default_chunk steps per lane do not give as many, and 16 at most. With a
 // fixed 16 a series of n steps is n / 1 024 waves, which below 2^20 steps
 // leaves SIMDs idle while every lane runs its 16 steps one after the other;
 // with fewer steps per lane the chain is shorter on the same number of
 // launches. Measured (FP64, us with 16 / with this rule): filter + smoother,
-// 1 536 steps at d = 2 59 / 38, 131 101 steps at d = 8 735 / 589, 300 007 steps
+// 1 536 steps at d = 2 59 / 38, 131 101 steps at d = 8 888 / 685, 300 007 steps
 // at d = 6 536 / 455; loglik + gradient, 2 000 steps at d = 6 505 / 303.
 // Below 4 the lane scan and the passes' starts dominate (1, 2 and 4 are within
-// 10 % of each other). In FP32 fewer steps per lane round the lane-start
+// 10 % of each other). At d = 8 the scan's rounding is larger than the filter's
+// and goes with the number of lanes, so that 8 is the least (Matern-3/2 + RBF-6,
+// 12 011 steps 0.01 apart, error of f_var with 4 / 8 / 16 steps a lane: noise
+// variance 0.003 8e-12 / 3e-12 / 2e-12, 1e-4 1e-9 / 5e-10 / 2e-10; over gaps of
+// 0.001 to 0.05 and noise of 1e-4 to 0.03 8 is as exact as 16, within the
+// scatter of one rounding against another; up to d = 6 4 is, too). In FP32 fewer steps per lane round the lane-start
 // moments more often in FP32, and a default that moved with n would move the
 // log-likelihood in its eighth digit: there the choice stays the caller's
 // (or the tuner's). At d = 8 in FP64 the lane records are 76 KB a tile: three
@@ -52,14 +57,14 @@ struct Plan {
 // At d >= 6 the lane scan has one or two workgroups of d / 2 waves on a CU
 // (LDS), so that its tiles run in rounds of 256 or 512: the chunk is the least
 // that needs no more rounds than 16 steps would (131 101 steps at d = 8: 512
-// tiles of 4 steps a lane 759 us, 257 of 8 703, 228 of 9 in one round 589 us).
-constexpr int kMinDefaultChunk = 4;
+// tiles of 4 steps a lane 858 us, 228 of 9 in one round 685 us).
+int min_default_chunk(int d) { return d >= 8 ? 8 : 4; }
 
 int64_t fill_tiles(int d, bool f64) { return (f64 && d >= 8) ? 768 : 1024; }
 int64_t round_tiles(int d) { return d >= 8 ? 256 : (d >= 6 ? 512 : 1024); }
 
 // Tiles that a default-chunk FP64 call of n steps has at most (it has fewer
-// where kMinDefaultChunk steps per lane give fewer, more beyond fill_tiles).
+// where min_default_chunk steps per lane give fewer, more beyond fill_tiles).
 int64_t most_tiles(int64_t n, int d)
 {
     const int64_t one = round_tiles(d), rounds = (n + 64 * kDefaultChunk * one - 1) / (64 * kDefaultChunk * one);
@@ -72,7 +77,8 @@ int default_chunk(int64_t n, int d, bool f64)
     if (!f64) return kDefaultChunk;
     const int64_t lanes = 64 * most_tiles(n, d);
     const int64_t c = (n + lanes - 1) / lanes;
-    return (int)(c < kMinDefaultChunk ? kMinDefaultChunk : (c > kDefaultChunk ? kDefaultChunk : c));
+    const int least = min_default_chunk(d);
+    return (int)(c < least ? least : (c > kDefaultChunk ? kDefaultChunk : c));
 }
 
 int chunk_of(const pssgp_options *o, int64_t n, int d, bool f64)
@@ -86,7 +92,7 @@ int chunk_of(const pssgp_options *o, int64_t n, int d, bool f64)
 int64_t alloc_tiles(int64_t ntiles, int64_t n, int d, bool f64, const pssgp_options *o)
 {
     if (!f64 || (o && o->chunk)) return ntiles;
-    const int64_t small = (n + 64 * kMinDefaultChunk - 1) / (64 * kMinDefaultChunk), full = most_tiles(n, d);
+    const int64_t least = 64 * min_default_chunk(d), small = (n + least - 1) / least, full = most_tiles(n, d);
     const int64_t most = small < full ? small : full;
     return ntiles > most ? ntiles : most;
 }
