@@ -56,14 +56,10 @@ PASSES = ("filter_fold", "filter_carry", "filter_finish", "smoother_fold", "smoo
 
 def pass_costs(d, tsize, chunk):
     """Algorithmic HBM bytes and flops per time step of every pass of the
-    fused filter + smoother call (2 flops per multiply-add; FP64 and FP32
-    vector operations count alike, since with packed FP32 disabled both run
-    at the same vector rate).
-
-    The costs are those of the scans with a smoother element per step. The
-    fused call forms one element per lane of steps and hands over P h and h m
-    instead (d + 1 FP64 values), so its passes after the fold do less than
-    this and its smoother finish is bound by arithmetic, not by bytes.
+    fused filter + smoother call with a smoother element per step (FP64, and
+    FP32 up to d = 3; fused_costs gives the costs of the form that a call
+    takes). 2 flops per multiply-add; FP64 and FP32 vector operations count
+    alike, since with packed FP32 disabled both run at the same vector rate.
 
     Bytes are each kernel's own inputs and outputs: the step inputs
     (t, y, mask), the smoother element of every step that the filter's
@@ -111,14 +107,44 @@ def pass_costs(d, tsize, chunk):
     }
 
 
+def fused_costs(d, tsize, chunk):
+    """Costs of the fused call's passes as built: pass_costs, or, in FP32 above
+    d = 3, those of an element per lane of steps. There the filter's finish
+    pass runs the fixed-point smoother of the lane's first step beside the
+    filter (F G, a rank-one update of G and of a symmetric matrix) over the
+    lane's steps and the first of the next lane, and hands over d + 3 FP64
+    values per step (P h, h m, the innovation, the step's length), the lane's
+    end moments (d + d(d+1)/2 FP64 values) and its smoother element; the
+    smoother's finish forms F alone and carries (lambda, Lambda) over it
+    (F^T Lambda F, a rank-one update)."""
+    costs = pass_costs(d, tsize, chunk)
+    if tsize != 4 or d <= 3:
+        return costs
+    ns = d * (d + 1) // 2
+    run = (chunk + 1) / chunk
+    fagg = tsize * (d * d + 2 * d + 2 * ns) / chunk
+    handed = 8 * (d + 3) * run + (8 * (d + ns) + tsize * (d * d + d + ns)) / chunk
+    trans = 25 * d + d * d + 2 * d * (d - 1)
+    disc = trans + 2 * d * d + 3 * d * (d - 1)
+    step = disc + d ** 3 + d * d + ns * d + ns + d * d + 3 * d + 3 * ns   # transition, prediction, conditioning
+    fixed = d ** 3 + 2 * d * d + ns + 2 * d
+    scomb = 2 * d ** 3 + ns * d + d * d
+    lane = 5 * d ** 3 + d ** 3 // 6 + d ** 3 + ns * d + 6 * scomb         # entering moments, element, lane scan
+    back = trans + d ** 3 + ns * d + d * d + 2 * d * d + 5 * d
+    costs["filter_finish"] = ((8 + tsize + 1) * run + fagg + handed, 2 * (run * (step + fixed) + lane / chunk))
+    costs["smoother_fold"] = (0.0, 0.0)
+    costs["smoother_finish"] = (handed + 2 * tsize, 2 * (run * back + (d ** 3 + ns * d + 2 * d ** 3) / chunk))
+    return costs
+
+
 def path_bytes_per_step(d, tsize):
     """Algorithmic HBM bytes per time step of the whole filter + smoother
     path: the inputs t (8 B), y and mask (1 B) read once, the filter moments
     (m, P) handed to the smoother (d(d+3)/2 values, written once and read
     once), t read again by the smoother, f_mean and f_var written once:
     29 + 4 d(d+3) bytes in FP32, 41 + 8 d(d+3) in FP64 (245 and 473 at
-    d = 6). The fused call hands over the smoother elements instead of the
-    moments; the figure is the method's, not this implementation's."""
+    d = 6). The fused call hands over other values in place of the moments
+    (fused_costs); the figure is the method's, not this implementation's."""
     return 8 + tsize + 1 + 2 * tsize * (d * (d + 3) // 2) + 8 + 2 * tsize
 
 
@@ -327,8 +353,8 @@ def roofline_of(m, workload=None, dtype=None, costs=None):
     arithmetic intensity puts it under. `traffic` is the kernel's measured
     HBM bytes per launch (FETCH_SIZE + WRITE_SIZE, calibrated on a copy),
     when a counter summary for these sources, workload and chunk exists.
-    costs: per-pass (bytes, flops) per step, default pass_costs of m."""
-    costs = costs or pass_costs(m["d"], m["tsize"], m["chunk"])
+    costs: per-pass (bytes, flops) per step, default fused_costs of m."""
+    costs = costs or fused_costs(m["d"], m["tsize"], m["chunk"])
     dom = max(m["pass_ms"], key=lambda k: m["pass_ms"][k])
     ms = m["pass_ms"][dom]
     bpstep, fpstep = costs[dom]
@@ -481,7 +507,7 @@ def measure_batched(steps, warmup, chunk=0, missing=0.0):
     for kind, dd in ((P.MATERN32, 2), (P.MATERN52, 3)):
         idx = np.nonzero(np.asarray(w["kinds"]) == kind)[0]
         frac = float(np.sum(off[idx + 1] - off[idx])) / n
-        for k, (b, f) in pass_costs(dd, 4, chunk).items():
+        for k, (b, f) in fused_costs(dd, 4, chunk).items():
             costs[k][0] += frac * b
             costs[k][1] += frac * f
     costs["filter_finish"][0] += 16.0 * (1.0 / chunk + len(w["kinds"]) / n)
