@@ -761,39 +761,8 @@ __device__ __forceinline__ void discretize_fast(const DevModel &mdl, cdouble *cs
     if constexpr (LY::NB > 1) disc_fast_block<LY, 1, T>(mdl, cst, sc, dt, first, Dl, Q);
 }
 
-// F alone in FP64 from the constants at cst (the expansion of the FP32
-// scans), with the special cases of discretize: F = 0 at a series start,
-// F = I exactly for a zero step.
-template <class LY>
-__device__ __forceinline__ void transition_fast(const DevModel &mdl, cdouble *cst, const StepScale &sc, double dt,
-                                                bool first, double (&F)[LY::D][LY::D])
-{
-    constexpr int D = LY::D;
-#pragma unroll
-    for (int i = 0; i < D; i++)
-#pragma unroll
-        for (int j = 0; j < D; j++) F[i][j] = 0.0;
-    const bool zero = (dt == 0.0);
-    auto block = [&](auto bc) {
-        constexpr int b = decltype(bc)::value;
-        constexpr int dc = LY::bdim(b);
-        constexpr int o = LY::boff(b);
-        double phi[dc];
-        block_phi<LY, b>(mdl, sc, dt, phi);
-        double dl[dc][dc];
-        dl_fast_block<LY, b>(cst, phi, first, zero, dl);
-#pragma unroll
-        for (int i = 0; i < dc; i++)
-#pragma unroll
-            for (int j = 0; j < dc; j++)
-                F[o + i][o + j] = first ? 0.0 : (zero ? ((i == j) ? 1.0 : 0.0) : dl[i][j] + (i == j ? 1.0 : 0.0));
-    };
-    block(std::integral_constant<int, 0>());
-    if constexpr (LY::NB > 1) block(std::integral_constant<int, 1>());
-}
-
-// The same without the selects: F = I + Dl, which at a series start is 0 and
-// at a zero step I exactly, as dl_fast_block's first row is then.
+// F = I + Dl in FP64 from the constants at cst (the expansion of the FP32
+// scans), past a series start.
 template <class LY>
 __device__ __forceinline__ void transition_plain(const DevModel &mdl, cdouble *cst, const StepScale &sc, double dt,
                                                  bool first, double (&F)[LY::D][LY::D])
@@ -812,6 +781,25 @@ __device__ __forceinline__ void transition_plain(const DevModel &mdl, cdouble *c
     };
     block(std::integral_constant<int, 0>());
     if constexpr (LY::NB > 1) block(std::integral_constant<int, 1>());
+}
+
+// The same with the special cases of discretize: F = 0 at a series start, F = I
+// exactly for a zero step.
+template <class LY>
+__device__ __forceinline__ void transition_fast(const DevModel &mdl, cdouble *cst, const StepScale &sc, double dt,
+                                                bool first, double (&F)[LY::D][LY::D])
+{
+    constexpr int D = LY::D;
+#pragma unroll
+    for (int i = 0; i < D; i++)
+#pragma unroll
+        for (int j = 0; j < D; j++) F[i][j] = 0.0;
+    transition_plain<LY>(mdl, cst, sc, dt, first, F);
+    const bool zero = (dt == 0.0);
+#pragma unroll
+    for (int i = 0; i < D; i++)
+#pragma unroll
+        for (int j = 0; j < D; j++) F[i][j] = first ? 0.0 : (zero ? ((i == j) ? 1.0 : 0.0) : F[i][j]);
 }
 
 // ------------------------------------------------------------------ register linear algebra

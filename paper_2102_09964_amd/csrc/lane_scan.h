@@ -243,7 +243,7 @@ __device__ __forceinline__ void lane_scan_level(T *s, CT *az, CT *zs, int w, int
 // start at the series start: a pair of filter moments, whose conditioning on a
 // later aggregate cancels when that is informative, so in FP64.
 template <int D, typename T>
-__global__ __launch_bounds__(PSSGP_WAVE *D / 2, (sizeof(T) == 8 || D >= 8 ? 1 : 2)) void lane_scan_kernel(T *lanep, T *aggp)
+__global__ __launch_bounds__(PSSGP_WAVE *D / 2, 1) void lane_scan_kernel(T *lanep, T *aggp)
 {
     constexpr int AGG = AggLayout<D>::SIZE, W = PSSGP_WAVE;
     __shared__ T s[AGG * W];
