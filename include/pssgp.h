@@ -103,9 +103,13 @@ typedef struct pssgp_model {
 typedef enum { PSSGP_F32 = 0, PSSGP_F64 = 1 } pssgp_dtype;
 
 typedef struct pssgp_options {
-    uint32_t chunk;          /* steps per lane, 0 = default (16; FP64 scans 4 to 16
-                                by the number of steps); 1..64 for FP64 scans,
-                                4..64 for FP32 scans (PSSGP_EINVAL otherwise) */
+    uint32_t chunk;          /* steps per lane, 0 = default (16; FP64 scans 4 to 16, at
+                                d = 8 8 to 16, by the number of steps); 1..64 for
+                                FP64 scans, 4..64 for FP32 scans. Quasi-periodic
+                                models: steps per team of 16 lanes, 0 = default (256;
+                                FP64 16 to 256 at d = 10, 64 to 256 at d = 14 and 18,
+                                by the number of steps), 4..4096 (PSSGP_EINVAL
+                                otherwise) */
     uint32_t deterministic;  /* accepted for compatibility; every scan combines its
                                 partial results in a fixed order, so results are
                                 always bitwise reproducible for a given chunk */
@@ -137,7 +141,8 @@ enum {
     PSSGP_STATUS_UNSORTED = 1u,     /* t[k] < t[k-1] */
     PSSGP_STATUS_NONFINITE = 2u,    /* NaN/Inf in t or an observed y */
     PSSGP_STATUS_BAD_S = 4u,        /* innovation variance <= 0 or not finite */
-    PSSGP_STATUS_CHOLESKY = 8u      /* smoother: predicted covariance not positive definite */
+    PSSGP_STATUS_CHOLESKY = 8u      /* smoother: a predicted covariance (pssgp_predict in FP32 at
+                                       d > 3: the filtered one at a lane's end) not positive definite */
 };
 
 /* Library version (major * 10000 + minor * 100 + patch). */
@@ -232,11 +237,15 @@ int pssgp_plain_predict(const pssgp_model *model, const double *t, const double 
  * Filter, log-likelihood and smoother in one call (section 3 and
  * supplement, Lemma 1; test points are missing steps): f_mean, f_var
  * dtype[n] and loglik double[1] as from pssgp_filter + pssgp_smooth,
- * but the filter builds the smoother element of every step from its own
- * FP64 prediction and hands the elements (and, for d <= 6, each lane's
- * composed smoother aggregate) to the smoother inside the workspace, in a
+ * but the filter hands over to the smoother inside the workspace, in a
  * layout where every access of a wave is contiguous, instead of writing m
- * and P. Workspace: pssgp_workspace_bytes(..., PSSGP_OP_PREDICT, opts);
+ * and P. In FP64, and in FP32 up to d = 3, it hands over the smoother
+ * element of every step, built from its own FP64 prediction (and, for
+ * d <= 6, each lane's composed smoother aggregate); in FP32 above d = 3,
+ * quasi-periodic models included, the predicted moments against the
+ * observation row of every step in FP64 and one smoother element per lane
+ * (per run of steps of a team). All inputs are read before the first
+ * output is written: outputs may overlap inputs. Workspace: pssgp_workspace_bytes(..., PSSGP_OP_PREDICT, opts);
  * the same opts (chunk) must be passed. Errors as pssgp_filter.
  */
 int pssgp_predict(const pssgp_model *model, const double *t, const void *y, const uint8_t *mask, int64_t n,

@@ -576,8 +576,9 @@ class Pipeline:
     length and dtype: workspaces and outputs are allocated once, so that
     ``run()`` only launches kernels (stream-ordered, no synchronisation).
 
-    By default both scans run in one ``pssgp_predict`` call, which hands the
-    filter moments to the smoother inside its workspace; with
+    By default both scans run in one ``pssgp_predict`` call, whose filter
+    hands over to the smoother inside its workspace (smoother elements, no
+    filter moments in memory; outputs may overlap inputs); with
     ``full_state`` (smoothed state moments wanted) or ``fused=False`` the
     filter moments are written to ``m``, ``P`` and read back by
     ``pssgp_smooth``.
@@ -702,7 +703,7 @@ class BatchedPipeline:
     kinds: per-series Matern kind (sorted by state size, at most two kinds);
     offsets: int64 [n_series + 1]; params: float64 [n_series, 3] with
     (lengthscale, variance, noise_var) per series. fused=True runs both scans
-    in one pssgp_batched_predict call (the handover in the
+    in one pssgp_batched_predict call (smoother elements handed over in the
     workspace, no filter moments in memory); fused=False runs
     pssgp_batched_filter, keeps m and P, then pssgp_batched_smooth.
     """
