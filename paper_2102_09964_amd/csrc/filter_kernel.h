@@ -399,7 +399,8 @@ __device__ __forceinline__ void fixed_point_update(const double (&K)[D], double 
 
 // Whether the fold leaves the lane scan to lane_scan_kernel: at d >= 6 in FP64
 // (filter and smoother: 2 000 steps at d = 6 357 -> 272 us, at d = 8 634 -> 379;
-// 131 101 steps at d = 8 890 -> 589 with the chunk chosen for it); in FP32 at
+// 131 101 steps at d = 8 890 -> 685 with the chunk chosen for it and the
+// symmetric form of the scan); in FP32 at
 // d = 8 up to two workgroups a CU (1 000 steps 551 -> 469, 320 000 steps 679 ->
 // 618 us; 2^20 steps 778 -> 821 to 900). There, and at d = 6 in FP32 at any size
 // (1 000 steps 249 -> 264), the workgroup of tile 0 with its FP64 conditioning

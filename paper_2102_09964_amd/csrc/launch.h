@@ -20,8 +20,9 @@ struct WsCtl {
 
 // What the filter of a fused call hands to its smoother: an element per lane
 // and, per step, P h and h m (true), or a smoother element per step. The first
-// moves less and takes fewer instructions (FP32, 2^22 steps at d = 6: filter
-// finish + smoother 473 + 167 us with an element per step, 313 + 185 us), but
+// moves less and takes fewer instructions (FP32, 2^22 steps at d = 6, chunk 64:
+// filter finish + smoother 453 + 169 us with an element per step, 288 + 164 us),
+// but
 // inside a lane it carries the smoothed moments as P^-1 (P - P^s) P^-1, whose
 // rounding is that of its largest entry: where the filtered covariance falls
 // far below the one at another step of the lane, or is nearly singular along f,

@@ -34,9 +34,11 @@
 // team (256 steps at 2^18 are one wave on every fourth SIMD), so the smoother,
 // which needs no further filter aggregate for it, works on sub-chunks.
 // 262 107 steps at 16 states (FP32, chunk 256, sub-chunks of 64 steps):
-// fold 774, ten filter levels of 67, finish 1665, join 16, ten smoother levels
-// of 37, smoother finish 193 us, the call 3.65 ms; with a smoother element per
-// step, folded and run again over the chunks, the call took 8.12 ms.
+// fold 774, ten filter levels of 64, finish 1619, join 19, ten smoother levels
+// of 38, smoother finish 183 us, the call 3.63 ms; with a smoother element per
+// step, folded and run again over the chunks, the call took 8.12 ms. FP64 with
+// an element per step, chunk 128: fold 416, eleven levels of 129, finish 2085,
+// smoother fold 773, eleven levels of 169, smoother finish 1025 us, 7.58 ms.
 // Every team of a wave runs the same number of iterations (steps past a
 // chunk's end are identity steps), so control flow is uniform.
 #include <hip/hip_runtime.h>

@@ -239,9 +239,9 @@ __device__ __forceinline__ void smoother_tile_finish(const SmoothParams<T> &p, c
 // from extended precision than an element per step in FP32), and for no other
 // (lane_handover).
 // Handover and elements together: filter finish + smoother of 2^22 steps at
-// d = 6 (FP32, chunk 64) 473 + 167 us with an element per step (63 values; a
-// Cholesky factor, two solves and a composition), 313 + 185 us in this form,
-// which is bound by its instructions (973 per step, of them 330 for F).
+// d = 6 (FP32, chunk 64) 453 + 169 us with an element per step (63 values; a
+// Cholesky factor, two solves and a composition), 288 + 164 us in this form,
+// which is bound by its instructions (930 per step).
 template <class LY, typename T, class SV>
 __device__ __forceinline__ void smoother_tile_fused(const SmoothParams<T> &p, const DevModel &mdl, cdouble *cst,
                                                     SV &sv, const STileRange &tr, int tile, T *s_out)
